@@ -4,7 +4,7 @@
 Workload: 256 environments over 8 seeded label volumes of uneven size
 (160^3 ... 320x256x384 uint8), per-env images of 64..256 scanlines x
 128..512 depth samples at 0.5 mm, random probe poses on a spine phantom,
-stepped as one HIP-graph replay of the persistent kernel per step.  Inputs
+stepped by two persistent kernels per step.  Inputs
 (volumes, poses) are resident in device memory before timing starts.
 
 Prints one JSON line (see the keys below).  Only one GPU is used; --gpus
@@ -294,7 +294,7 @@ def surrogate_leg(train_steps: int, n_envs: int = 1024, audit_frac: int = 16, ps
     for _ in range(reps):
         sg.sg_surr_infer_bf16(sess.ctx, sid, vids, probes, poses, out16, [], psnr_min, 0.25)
     net_s = (time.perf_counter() - t) / reps
-    # physics on the same workload: batched plan, graph replays
+    # physics on the same workload: batched plan, steps enqueued back to back
     offs = np.arange(n_envs, dtype=np.int64) * HW
     plan = sg.sg_batch_plan_create(sess.ctx, vids, probes, offs)
     sg.sg_batch_set_poses(sess.ctx, plan, poses)
@@ -467,7 +467,7 @@ def main():
         "data": "synthetic",
         "config": {
             "workload": "batched physics, 256 envs over 8 uneven label volumes 160^3..320x256x384, "
-                        "W 64-256 x H 128-512 at 0.5 mm, one persistent kernel per step in a HIP graph",
+                        "W 64-256 x H 128-512 at 0.5 mm, two persistent kernels per step",
             "n_envs": n,
             "pixels_per_step": pixels,
             "launch_shape": {"scanlines_per_item": spw, "tile_x": tx, "tile_y": ty, "chunks": chunks},

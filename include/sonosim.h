@@ -20,7 +20,7 @@
  *    pointers are ordinary CPU memory.  The caller owns every buffer it passes
  *    in (volumes, outputs, offsets) and must keep device buffers alive until
  *    the work that uses them has completed on the context's stream.  The
- *    library owns only its workspaces, plans, graphs and plan pose buffers.
+ *    library owns only its workspaces, plans, graphs of training steps and plan pose buffers.
  *  - Work is enqueued asynchronously on the context's stream unless stated.
  *  - Contexts are not thread-safe; use one context per thread or stream.
  *  - Image layout: a frame is [H][W] row-major FP32 (row = depth sample y,
@@ -218,7 +218,7 @@ sg_status sg_simulate_noalloc(sg_ctx* ctx, int32_t n_envs, const int32_t* vol_id
 /* ------------------------------------------------------------------------
  * Batched persistent path (environments stepped in batch mode, Sec. 4):
  * a plan fixes the environments' volumes, probes and output offsets; each
- * step replays one captured HIP graph: a persistent ray kernel pulling
+ * step enqueues two kernels: a persistent ray kernel pulling
  * (environment, scanline group) items longest-first from a device queue,
  * each item computing its plane from the device pose, then a persistent PSF
  * kernel striding over (environment, tile) items.  Poses
@@ -240,8 +240,7 @@ sg_status sg_batch_poses(sg_ctx* ctx, int32_t plan_id, double** dev_poses);
 sg_status sg_batch_set_poses(sg_ctx* ctx, int32_t plan_id, const double* host_poses);
 
 /* Enqueue one step: geometry from the device poses, then all environments'
- * frames into `out` (device; same offsets as the plan).  The first call (and
- * any call with a different `out` or after sg_autotune) captures the graph.
+ * frames into `out` (device; same offsets as the plan).
  * A pose whose plane leaves the fixed-point range produces a zero frame for
  * that environment and is reported by sg_batch_status. */
 sg_status sg_batch_step(sg_ctx* ctx, int32_t plan_id, float* out);
@@ -257,7 +256,7 @@ sg_status sg_batch_status(sg_ctx* ctx, int32_t plan_id, int32_t* n_bad);
  * bit-identical frames. */
 sg_status sg_autotune(sg_ctx* ctx, int32_t plan_id, const char* cache_path);
 
-/* Run one step without the graph, timing its persistent kernels with HIP
+/* Run one step, timing its persistent kernels with HIP
  * events on the context's stream; synchronises.  *ms_ray (host) receives the
  * time from the first ray kernel's start to the last one's end (with one
  * chunk: the ray kernel's duration); *ms_psf the time after that until the

@@ -25,6 +25,8 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
+#include <cstring>
 
 #include "sg_internal.h"
 
@@ -1062,6 +1064,26 @@ __global__ __launch_bounds__(kThreads) void k_encode_ct(PhysArgs a, const uint16
     }
 }
 
+// Uploads of launch parameters and poses (0.5 to some hundred KB per call).  Both are bound by the
+// latency of one read over the host link.  A copy by the DMA engine costs a hand-over between its queue
+// and the compute queue on either side of it: with the poses of a 256-env batch (24 KB) the next ray
+// kernel started 28 us after the previous PSF kernel, and 9 us after it with this kernel in between.
+// The by-value form reads the kernel arguments instead of a pinned buffer, so the host has no buffer
+// (and no event) to wait for before the next call.
+__global__ __launch_bounds__(kThreads) void k_upload(uint4* __restrict__ dst, const uint4* __restrict__ src, int n)
+{
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) dst[i] = src[i];
+}
+
+struct SmallUpload {
+    uint4 v[kSmallUpload / 16];
+};
+
+__global__ __launch_bounds__(kThreads) void k_upload_small(uint4* __restrict__ dst, SmallUpload src, int n)
+{
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = src.v[threadIdx.x];
+}
+
 __global__ void k_queue_reset(QueueDev* q, int n)
 {
     if ((int)threadIdx.x < n) q[threadIdx.x].next_ray = 0;
@@ -1101,10 +1123,15 @@ const void* psf_fn(int tx)
     return nullptr;
 }
 
-int blocks_per_cu(const void* fn, int threads, size_t lds)
+// resident blocks per compute unit; `known` keeps the answer of each (kernel, LDS size), the same on every
+// gfx950 (the query costs a single call about 2 us per kernel)
+int blocks_per_cu(const void* fn, int threads, size_t lds, std::atomic<int>& known)
 {
-    int n = 0;
+    int n = known.load(std::memory_order_relaxed);
+    if (n > 0) return n;
+    n = 0;
     if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds) != hipSuccess) return 0;
+    known.store(n, std::memory_order_relaxed);
     return n;
 }
 
@@ -1135,12 +1162,16 @@ const void* ray_fn(bool label_only, bool debug)
 int ray_grid(int n_cu, bool multiscale, bool label_only, bool debug)
 {
     const void* fn = multiscale ? ray_fn<true>(label_only, debug) : ray_fn<false>(label_only, debug);
-    return blocks_per_cu(fn, kThreads, 0) * n_cu;
+    static std::atomic<int> known[8];
+    return blocks_per_cu(fn, kThreads, 0, known[4 * multiscale + 2 * label_only + debug]) * n_cu;
 }
 
 int psf_grid(int tx, int max_rlat, int n_cu)
 {
-    return blocks_per_cu(psf_fn(tx), psf_threads(tx), psf_lds_bytes(tx, max_rlat)) * n_cu;
+    static std::atomic<int> known[3][kMaxPsfRadius + 1];
+    if (!psf_tile_supported(tx)) return 0;
+    std::atomic<int>& k = known[tx == 16 ? 0 : (tx == 32 ? 1 : 2)][max_rlat < 0 ? 0 : std::min(max_rlat, kMaxPsfRadius)];
+    return blocks_per_cu(psf_fn(tx), psf_threads(tx), psf_lds_bytes(tx, max_rlat), k) * n_cu;
 }
 
 hipError_t launch_ray(const PhysArgs& a, QueueDev* q, int grid, hipStream_t s)
@@ -1204,6 +1235,26 @@ hipError_t launch_encode(const PhysArgs& a, int32_t n_envs, int32_t max_pixels, 
         hipLaunchKernelGGL(k_encode<true>, dim3(bx, n_envs), dim3(kThreads), 0, s, a, enc);
     else
         hipLaunchKernelGGL(k_encode<false>, dim3(bx, n_envs), dim3(kThreads), 0, s, a, enc);
+    return hipGetLastError();
+}
+
+hipError_t launch_upload(void* dst, const void* pinned, size_t bytes, hipStream_t s)
+{
+    const int n = (int)((bytes + 15) / 16);
+    if (n <= 0) return hipSuccess;
+    const int blocks = std::min((n + kThreads - 1) / kThreads, 256);
+    hipLaunchKernelGGL(k_upload, dim3(blocks), dim3(kThreads), 0, s, (uint4*)dst, (const uint4*)pinned, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_upload_small(void* dst, const void* host, size_t bytes, hipStream_t s)
+{
+    static_assert(kSmallUpload / 16 <= kThreads, "one thread per 16 bytes");
+    if (bytes == 0) return hipSuccess;
+    if (bytes > kSmallUpload) return hipErrorInvalidValue;
+    SmallUpload u = {};
+    std::memcpy(&u, host, bytes);
+    hipLaunchKernelGGL(k_upload_small, dim3(1), dim3(kThreads), 0, s, (uint4*)dst, u, (int)((bytes + 15) / 16));
     return hipGetLastError();
 }
 

@@ -34,6 +34,15 @@ struct PinnedBuf {
     hipError_t acquire(size_t bytes);  // waits for the previous upload, then grows
 };
 
+// Uploads of launch parameters and poses take the slots in turn, so a call waits for the upload of
+// kStagingSlots calls ago, not for the previous one.
+constexpr int kStagingSlots = 4;
+struct PinnedRing {
+    PinnedBuf slot[kStagingSlots];
+    int at = 0;
+    PinnedBuf& next() { return slot[at = (at + 1) % kStagingSlots]; }
+};
+
 struct HostVolume {
     VolDev dev{};
     uint8_t* bricks = nullptr;   // library-owned bricked label map (dev.labels); freed on release
@@ -70,11 +79,6 @@ struct Plan {
     int32_t ray_off[kMaxChunks] = {}, ray_cnt[kMaxChunks] = {}, tile_off[kMaxChunks] = {}, tile_cnt[kMaxChunks] = {};
     hipStream_t aux = nullptr;                      // second stream of the chunked pipeline
     hipEvent_t ev_ray[kMaxChunks] = {}, ev_join = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    float* graph_out = nullptr;        // output pointer the graph was captured with
-    const void* cap_vols = nullptr;    // volume table the graph was captured with
-    int32_t cap_labels = 0;            // tissue table size the graph was captured with
     ~Plan();
 };
 
@@ -105,7 +109,7 @@ struct sg_ctx {
     sg::DevBuf ms_thr;    // multi-scale gate thresholds, [SG_MAX_LABELS_DEV][kMaxNoiseScales] int32
     int32_t n_labels = 0;
     sg::DevBuf scan, params, fields, queue;
-    sg::PinnedBuf staging;
+    sg::PinnedRing staging;
     std::map<int32_t, std::unique_ptr<sg::Plan>> plans;
     int32_t next_plan = 1;
     std::map<int32_t, std::unique_ptr<sg::Surrogate, sg::SurrogateDeleter>> surrogates;
@@ -147,6 +151,9 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
                         float* out, const int64_t* out_offsets, const sg_debug_planes* dbg, PhysArgs& a,
                         StageInfo& info);
 sg_status launch_physics(sg_ctx* c, const PhysArgs& a, const StageInfo& info);
+// enqueue the upload of `bytes` host bytes (host may be reused on return) to the device buffer dst
+// (16-byte aligned, room for bytes rounded up to 16)
+sg_status upload(sg_ctx* c, void* dst, const void* host, size_t bytes, const char* what);
 sg_status check_envs(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_probe* probes);
 void surrogate_release_all(sg_ctx* c);
 void recon_release_all(sg_ctx* c);

@@ -180,6 +180,11 @@ __host__ __device__ inline int plane_geometry(const double* pose, double sx, dou
 
 // launchers (physics.hip)
 hipError_t launch_queue_reset(QueueDev* q, int n_queues, hipStream_t s);   // resets q[0 .. n_queues)
+// host-to-device upload by a kernel on the stream: from pinned memory, or by value (at most kSmallUpload
+// bytes, no pinned buffer needed)
+constexpr size_t kSmallUpload = 3072;
+hipError_t launch_upload(void* dst, const void* pinned, size_t bytes, hipStream_t s);
+hipError_t launch_upload_small(void* dst, const void* host, size_t bytes, hipStream_t s);
 hipError_t launch_ray(const PhysArgs& a, QueueDev* q, int grid, hipStream_t s);
 hipError_t launch_psf(const PhysArgs& a, int tile_x, int grid, hipStream_t s);
 hipError_t launch_max_label(const uint8_t* labels, int64_t n, int32_t* d_out, hipStream_t s);

@@ -1,7 +1,6 @@
 // Host side of the C ABI declared in include/sonosim.h: contexts, volume and
 // tissue registries, argument validation, plane geometry, work lists,
-// staging, batched plans with HIP graph capture, and the launch-shape
-// autotuner.
+// staging, and the launches of a single call.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -317,7 +316,6 @@ extern "C" sg_status sg_set_stream(sg_ctx* c, void* stream)
 {
     if (!c) return fail(SG_EINVAL, "sg_set_stream: NULL context");
     c->stream = (hipStream_t)stream;
-    for (auto& kv : c->plans) kv.second->graph_out = nullptr;   // re-capture on the new stream
     return SG_OK;
 }
 
@@ -557,18 +555,32 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
     const size_t o_ray = align(o_pool + sizeof(float) * pool.size());
     const size_t o_psf = align(o_ray + sizeof(ItemRay) * rays.size());
     const size_t total = align(o_psf + sizeof(ItemPsf) * tiles.size());
-    hipError_t e = c->staging.acquire(total);
-    if (e != hipSuccess) return hip_fail(e, "pinned staging");
-    char* h = (char*)c->staging.p;
+    hipError_t e = hipSuccess;
+    // written in place: a small call's block on the stack, a larger one's in a pinned slot
+    alignas(16) char small[kSmallUpload];
+    char* h = small;
+    PinnedBuf* slot = nullptr;
+    if (total > sizeof(small)) {
+        slot = &c->staging.next();
+        if ((e = slot->acquire(total)) != hipSuccess) return hip_fail(e, "pinned staging");
+        h = (char*)slot->p;
+    }
     std::memcpy(h + o_env, envs.data(), sizeof(EnvDev) * envs.size());
     std::memcpy(h + o_pool, pool.data(), sizeof(float) * pool.size());
     std::memcpy(h + o_ray, rays.data(), sizeof(ItemRay) * rays.size());
     std::memcpy(h + o_psf, tiles.data(), sizeof(ItemPsf) * tiles.size());
     if ((e = c->params.ensure(total)) != hipSuccess) return hip_fail(e, "hipMalloc params");
     if ((e = c->fields.ensure(sizeof(float) * 3 * (size_t)scr)) != hipSuccess) return hip_fail(e, "hipMalloc scratch");
-    if ((e = c->queue.ensure(sizeof(QueueDev))) != hipSuccess) return hip_fail(e, "hipMalloc queue");
-    e = hipMemcpyAsync(c->params.p, h, total, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(c->staging.ev, c->stream);
+    if (!c->queue.p) {   // the work counter starts at zero; every PSF kernel clears it for the next call
+        if ((e = c->queue.ensure(sizeof(QueueDev))) == hipSuccess) e = launch_queue_reset((QueueDev*)c->queue.p, 1, c->stream);
+        if (e != hipSuccess) return hip_fail(e, "hipMalloc queue");
+    }
+    if (slot) {
+        e = launch_upload(c->params.p, h, total, c->stream);
+        if (e == hipSuccess) e = hipEventRecord(slot->ev, c->stream);
+    } else {
+        e = launch_upload_small(c->params.p, h, total, c->stream);
+    }
     if (e != hipSuccess) return hip_fail(e, "parameter upload");
 
     char* d = (char*)c->params.p;
@@ -601,6 +613,7 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
     a.max_rlat = max_rlat;
     a.multiscale = multiscale;
     a.any_ct = any_ct;
+    a.ray_queue = (QueueDev*)c->queue.p;
     info.tile_x = tx;
     info.max_pixels = max_px;
     return SG_OK;
@@ -611,12 +624,29 @@ sg_status launch_physics(sg_ctx* c, const PhysArgs& a, const StageInfo& info)
 {
     QueueDev* q = (QueueDev*)c->queue.p;
     hipError_t e;
-    if ((e = launch_queue_reset(q, 1, c->stream)) != hipSuccess) return hip_fail(e, "queue reset");
     if ((e = launch_ray(a, q, ray_grid(c->n_cu, a.multiscale != 0, ray_label_only(a), ray_debug(a)), c->stream)) != hipSuccess)
         return hip_fail(e, "ray kernel launch");
-    if ((e = launch_psf(a, info.tile_x, psf_grid(info.tile_x, a.max_rlat, c->n_cu), c->stream)) != hipSuccess)
+    if ((e = launch_psf(a, info.tile_x, psf_grid(info.tile_x, a.max_rlat, c->n_cu), c->stream)) != hipSuccess) {
+        (void)launch_queue_reset(q, 1, c->stream);   // the counter that this PSF kernel would have cleared
         return hip_fail(e, "PSF kernel launch");
+    }
     return SG_OK;
+}
+
+sg_status upload(sg_ctx* c, void* dst, const void* host, size_t bytes, const char* what)
+{
+    hipError_t e;
+    if (bytes <= kSmallUpload) {
+        e = launch_upload_small(dst, host, bytes, c->stream);
+    } else {
+        PinnedBuf& slot = c->staging.next();
+        e = slot.acquire((bytes + 15) & ~size_t(15));
+        if (e != hipSuccess) return hip_fail(e, "pinned staging");
+        std::memcpy(slot.p, host, bytes);
+        e = launch_upload(dst, slot.p, bytes, c->stream);
+        if (e == hipSuccess) e = hipEventRecord(slot.ev, c->stream);
+    }
+    return e == hipSuccess ? SG_OK : hip_fail(e, what);
 }
 
 }  // namespace sg

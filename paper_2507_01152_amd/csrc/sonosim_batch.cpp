@@ -1,5 +1,5 @@
-// Batched persistent path: plans, HIP graph capture/replay and the
-// launch-shape autotuner (C ABI in include/sonosim.h).
+// Batched persistent path: plans, their steps and the launch-shape autotuner
+// (C ABI in include/sonosim.h).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -17,8 +17,6 @@ namespace sg {
 
 Plan::~Plan()
 {
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
     for (hipEvent_t& ev : ev_ray)
         if (ev) (void)hipEventDestroy(ev);
     if (ev_join) (void)hipEventDestroy(ev_join);
@@ -42,15 +40,6 @@ Plan* find_plan(sg_ctx* c, int32_t id)
 {
     auto it = c->plans.find(id);
     return it == c->plans.end() ? nullptr : it->second.get();
-}
-
-void drop_graph(Plan* p)
-{
-    if (p->exec) (void)hipGraphExecDestroy(p->exec);
-    if (p->graph) (void)hipGraphDestroy(p->graph);
-    p->exec = nullptr;
-    p->graph = nullptr;
-    p->graph_out = nullptr;
 }
 
 sg_status apply_shape(sg_ctx* c, Plan* p, const LaunchShape& s)
@@ -111,7 +100,6 @@ sg_status apply_shape(sg_ctx* c, Plan* p, const LaunchShape& s)
     p->shape.chunks = K;
     p->grid_ray = gr;
     p->grid_psf = gp;
-    drop_graph(p);
     return SG_OK;
 }
 
@@ -150,9 +138,11 @@ PhysArgs plan_args(sg_ctx* c, Plan* p, float* out)
 // ray kernel's work counter for the next step) on stream s; optional events:
 // before the first ray kernel, after the last ray kernel, at the end of the
 // step.  With chunks, chunk k's PSF kernel waits for its ray kernel on the
-// plan's second stream, which the step joins at the end (the same code is
-// captured).  Every chunk holds at least one env, so each ray kernel is
-// followed by a PSF kernel that clears its counter.
+// plan's second stream, which the step joins at the end.  The two kernels are
+// launched as they are, not replayed from a graph: between a graph and the pose
+// upload or the reconstruction kernels around it the queue stood still for 6 to
+// 8 us on either side.  Every chunk holds at least one env, so each ray kernel
+// is followed by a PSF kernel that clears its counter.
 hipError_t enqueue_step(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEvent_t* ev = nullptr)
 {
     QueueDev* q = (QueueDev*)p->d_queue.p;
@@ -184,36 +174,6 @@ hipError_t enqueue_step(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEvent_
     if (e == hipSuccess) e = hipStreamWaitEvent(s, p->ev_join, 0);
     if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
     return e;
-}
-
-sg_status capture(sg_ctx* c, Plan* p, float* out)
-{
-    drop_graph(p);
-    hipStream_t cs = nullptr;
-    hipError_t e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-    if (e != hipSuccess) return hip_fail(e, "capture stream");
-    e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        hipError_t le = enqueue_step(c, p, out, cs);
-        hipGraph_t g = nullptr;
-        e = hipStreamEndCapture(cs, &g);
-        if (le != hipSuccess) e = le;
-        if (e == hipSuccess) {
-            p->graph = g;
-            e = hipGraphInstantiate(&p->exec, g, nullptr, nullptr, 0);
-        } else if (g) {
-            (void)hipGraphDestroy(g);
-        }
-    }
-    (void)hipStreamDestroy(cs);
-    if (e != hipSuccess) {
-        drop_graph(p);
-        return hip_fail(e, "graph capture");
-    }
-    p->graph_out = out;
-    p->cap_vols = c->d_vols.p;
-    p->cap_labels = c->n_labels;
-    return SG_OK;
 }
 
 std::string tune_key(sg_ctx* c, Plan* p)
@@ -336,12 +296,7 @@ extern "C" sg_status sg_batch_set_poses(sg_ctx* c, int32_t id, const double* hos
     if (!p || !host_poses) return fail(SG_EINVAL, "sg_batch_set_poses: bad plan id or NULL");
     (void)hipSetDevice(c->device);
     const size_t bytes = sizeof(double) * 12 * (size_t)p->n_user;
-    hipError_t e = c->staging.acquire(bytes);
-    if (e != hipSuccess) return hip_fail(e, "pinned staging");
-    std::memcpy(c->staging.p, host_poses, bytes);
-    e = hipMemcpyAsync(p->d_poses.p, c->staging.p, bytes, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(c->staging.ev, c->stream);
-    return e == hipSuccess ? SG_OK : hip_fail(e, "pose upload");
+    return upload(c, p->d_poses.p, host_poses, bytes, "pose upload");
 }
 
 static sg_status step_checks(sg_ctx* c, Plan* p)
@@ -385,12 +340,11 @@ extern "C" sg_status sg_batch_step(sg_ctx* c, int32_t id, float* out)
     (void)hipSetDevice(c->device);
     sg_status s = step_checks(c, p);
     if (s != SG_OK) return s;
-    if (!p->exec || p->graph_out != out || p->cap_vols != c->d_vols.p || p->cap_labels != c->n_labels) {
-        s = capture(c, p, out);
-        if (s != SG_OK) return s;
-    }
-    hipError_t e = hipGraphLaunch(p->exec, c->stream);
-    return e == hipSuccess ? SG_OK : hip_fail(e, "hipGraphLaunch");
+    const hipError_t e = enqueue_step(c, p, out, c->stream);
+    if (e == hipSuccess) return SG_OK;
+    // a step cut short may leave a ray counter that no PSF kernel cleared
+    (void)launch_queue_reset((QueueDev*)p->d_queue.p, kMaxChunks, c->stream);
+    return hip_fail(e, "step");
 }
 
 extern "C" sg_status sg_batch_status(sg_ctx* c, int32_t id, int32_t* n_bad)
@@ -463,7 +417,6 @@ extern "C" sg_status sg_autotune(sg_ctx* c, int32_t id, const char* cache_path)
         off += (int64_t)dense[i].W * dense[i].H;
     }
     auto restore = [&]() -> hipError_t {
-        drop_graph(p);   // captured with the dense offsets and the private buffer
         return hipMemcpy(p->d_envs.p, p->envs.data(), sizeof(EnvDev) * p->n_envs, hipMemcpyHostToDevice);
     };
     e = hipMemcpy(p->d_envs.p, dense.data(), sizeof(EnvDev) * p->n_envs, hipMemcpyHostToDevice);
@@ -478,11 +431,10 @@ extern "C" sg_status sg_autotune(sg_ctx* c, int32_t id, const char* cache_path)
     float best_us = 1e30f;
     for (const LaunchShape& shp : kShapes) {
         if (apply_shape(c, p, shp) != SG_OK) continue;
-        if (capture(c, p, (float*)scratch_out.p) != SG_OK) continue;
-        for (int w = 0; w < 3; ++w) (void)hipGraphLaunch(p->exec, c->stream);
+        for (int w = 0; w < 3; ++w) (void)enqueue_step(c, p, (float*)scratch_out.p, c->stream);
         const int reps = 10;
         (void)hipEventRecord(t0, c->stream);
-        for (int r = 0; r < reps; ++r) (void)hipGraphLaunch(p->exec, c->stream);
+        for (int r = 0; r < reps; ++r) (void)enqueue_step(c, p, (float*)scratch_out.p, c->stream);
         (void)hipEventRecord(t1, c->stream);
         if (hipEventSynchronize(t1) != hipSuccess) continue;
         float ms = 0.f;
