@@ -113,17 +113,16 @@ __device__ __forceinline__ double ct_corner(const VolDev& v, int32_t ix, int32_t
     return in ? (double)ld_global(v.ct, (iz * v.ny + iy) * v.nx + ix) : -1000.0;
 }
 
-// impedance from CT: max(HU + 1000, 0), HU trilinear in FP64 (successive
+// impedance from CT at Q16 position qp: max(HU + 1000, 0), HU trilinear in FP64 (successive
 // linear interpolation along x, y, z; outside corners -1000 HU)
-__device__ __forceinline__ double z_from_ct(const EnvDev& e, const VolDev& v, int x, int y)
+__device__ __forceinline__ double z_from_ct(const VolDev& v, const int32_t qp[3])
 {
     int32_t b[3];
     double w[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const int32_t q = q16(e.P0[c], e.DX[c], e.DY[c], x, y);
-        b[c] = q >> 16;
-        w[c] = (double)(q & 0xFFFF) * (1.0 / 65536.0);
+        b[c] = qp[c] >> 16;
+        w[c] = (double)(qp[c] & 0xFFFF) * (1.0 / 65536.0);
     }
     double cy[2];
 #pragma unroll
@@ -219,16 +218,6 @@ __device__ __forceinline__ int dpp_i(int old, int v)
     return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
 }
 
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ double dpp_d(double old, double v)
-{
-    const uint64_t o = __double_as_longlong(old), x = __double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)x, CTRL, ROWS, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32), (int)(uint32_t)(x >> 32), CTRL,
-                                                              ROWS, 0xf, false);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
 // inclusive scans over the 64 lanes (rows of 16 by row shifts, then the
 // row totals by row broadcasts)
 __device__ __forceinline__ float wave_scan_mul(float v)
@@ -256,14 +245,6 @@ __device__ __forceinline__ float wave_scan_add(float v)
 __device__ __forceinline__ float lane_f(float v, int lane)
 {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
-__device__ __forceinline__ double lane_d(double v, int lane)
-{
-    const uint64_t x = __double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
 // store the pair for ring slot `slot` (< kRing) and its mirror
@@ -432,7 +413,6 @@ __device__ void ray_scanline(const PhysArgs& a, const EnvDev& e, const VolDev& v
     uint32_t boff;
     int32_t vox = voxel_at(e, v, x, lane, boff);
     int lab = label_of(v, vox, boff);
-    double Z = ct ? z_from_ct(e, v, x, lane) : 0.0;
     int32_t q[3];    // Q16 position of (x, y0 + lane)
 #pragma unroll
     for (int c = 0; c < 3; ++c) q[c] = q16(e.P0[c], e.DX[c], e.DY[c], x, lane);
@@ -443,14 +423,13 @@ __device__ void ray_scanline(const PhysArgs& a, const EnvDev& e, const VolDev& v
         const int y0 = k * kWave;
         const int y = y0 + lane;
         const bool act = y < H;
-        // gather the next chunk's labels (and CT) ahead of use
+        // gather the next chunk's labels ahead of use
         int32_t qn[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) qn[c] = (int32_t)((uint32_t)q[c] + (uint32_t)e.DY[c] * (uint32_t)kWave);
         uint32_t boff_n;
         const int32_t vox_n = voxel_at_q(v, qn, boff_n);
         const int lab_n = label_of(v, vox_n, boff_n);
-        const double Zct_n = ct ? z_from_ct(e, v, x, y + kWave) : 0.0;
 
         // scatterer of this chunk's voxels (computed for every lane, selected below)
         uint32_t w[4];
@@ -485,17 +464,30 @@ __device__ void ray_scanline(const PhysArgs& a, const EnvDev& e, const VolDev& v
                 t = p.y;
             }
         } else {
-            const double Zc = ct ? Z : (double)tt.Z;
-            const double Z_first_n = ct ? lane_d(Zct_n, 0) : (double)tab[lab_first_n].Z;
-            const double Z_nr = dpp_d<kWaveShl1>(Z_first_n, Zc);
-            if (G && Zc != Z_nr) {
-                if (Zc == 0.0 || Z_nr == 0.0 || __builtin_isinf(Zc) || __builtin_isinf(Z_nr)) {
-                    r = Z_nr > Zc ? 1.f : -1.f;
-                    t = 0.f;
+            // r and t matter only at a label boundary, so the impedances are formed there alone: a boundary
+            // lane takes its own row's and the next row's (with CT eight gathers and seven FP64 interpolations
+            // each; formed for every pixel they were half of the kernel's time on 64 CT frames of 128 x 256)
+            if (G) {
+                double Zc, Z_nr;
+                if (ct) {
+                    int32_t qb[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) qb[c] = (int32_t)((uint32_t)q[c] + (uint32_t)e.DY[c]);
+                    Zc = z_from_ct(v, q);
+                    Z_nr = z_from_ct(v, qb);
                 } else {
-                    const double s = Zc + Z_nr;
-                    r = (float)((Z_nr - Zc) / s);
-                    t = (float)((2.0 * Zc / s) * (2.0 * Z_nr / s));
+                    Zc = (double)tt.Z;
+                    Z_nr = (double)tab[lab_nr].Z;
+                }
+                if (Zc != Z_nr) {
+                    if (Zc == 0.0 || Z_nr == 0.0 || __builtin_isinf(Zc) || __builtin_isinf(Z_nr)) {
+                        r = Z_nr > Zc ? 1.f : -1.f;
+                        t = 0.f;
+                    } else {
+                        const double s = Zc + Z_nr;
+                        r = (float)((Z_nr - Zc) / s);
+                        t = (float)((2.0 * Zc / s) * (2.0 * Z_nr / s));
+                    }
                 }
             }
         }
@@ -555,7 +547,6 @@ __device__ void ray_scanline(const PhysArgs& a, const EnvDev& e, const VolDev& v
         lab_last_prev = __builtin_amdgcn_readlane(lab, kWave - 1);
         vox = vox_n;
         lab = lab_n;
-        Z = Zct_n;
 #pragma unroll
         for (int c = 0; c < 3; ++c) q[c] = qn[c];
         wave_sync_lds();
