@@ -200,7 +200,7 @@ sg_status sg_simulate(sg_ctx* ctx, int32_t n_envs, const int32_t* vol_ids,
  * kernels and frames (bit for bit), without debug planes, but it allocates
  * nothing -- no hipMalloc / hipFree / pinned or other allocating call.  The
  * per-plane records, PSF taps, work lists, work counter and the FP32 field
- * planes between the two kernels live in a file-scope device array of
+ * planes between the two kernels live in file-scope device memory of about
  * SG_NOALLOC_SCRATCH_BYTES on each GPU, set up by sg_create and held until
  * the process ends; the records are staged in a static host array.  Each
  * call reuses its GPU's array, which keeps the last call's contents: calls

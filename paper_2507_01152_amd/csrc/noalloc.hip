@@ -20,14 +20,15 @@ namespace sg {
 namespace {
 
 constexpr size_t kParamBytes = size_t(2) << 20;     // records: envs | taps | ray items | PSF items
-constexpr size_t kQueueOff = kParamBytes;           // the ray kernel's work counter
 constexpr size_t kFieldOff = kParamBytes + 4096;    // three FP32 field planes
 constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
+__device__ QueueDev scratch_queue;   // the ray kernel's work counters
 
 std::mutex g_mu;                       // guards everything below
 void* g_scratch[kMaxDevices];          // device address of `scratch` on each GPU
+void* g_queue[kMaxDevices];            // and of `scratch_queue`
 hipEvent_t g_uploaded[kMaxDevices];    // recorded after that device's last upload from g_stage
 hipEvent_t g_last = nullptr;           // the upload from g_stage that may still be reading it
 alignas(256) unsigned char g_stage[kParamBytes];   // host staging of the records
@@ -46,11 +47,15 @@ hipError_t noalloc_init(int device)
     void* p = nullptr;
     hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e != hipSuccess) return e;
+    void* q = nullptr;
+    e = hipGetSymbolAddress(&q, HIP_SYMBOL(scratch_queue));
+    if (e != hipSuccess) return e;
     if (!g_uploaded[device]) {
         e = hipEventCreateWithFlags(&g_uploaded[device], hipEventDisableTiming);
         if (e != hipSuccess) return e;
     }
     g_scratch[device] = p;
+    g_queue[device] = q;
     return hipSuccess;
 }
 
@@ -178,8 +183,8 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
     a.max_rlat = max_rlat;
     a.multiscale = multiscale;
     a.any_ct = any_ct;
-    // the work counter starts at zero: cleared by a kernel (no memset node under graph capture)
-    QueueDev* q = reinterpret_cast<QueueDev*>(base + kQueueOff);
+    // the work counters start at zero: cleared by a kernel (no memset node under graph capture)
+    QueueDev* q = reinterpret_cast<QueueDev*>(g_queue[c->device]);
     if ((e = launch_queue_reset(q, 1, c->stream)) != hipSuccess) return hip_fail(e, "queue reset");
     if ((e = launch_ray(a, q, ray_grid(c->n_cu, multiscale != 0, ray_label_only(a), false), c->stream)) != hipSuccess)
         return hip_fail(e, "ray kernel launch");

@@ -565,13 +565,17 @@ __device__ void ray_scanline(const PhysArgs& a, const EnvDev& e, const VolDev& v
     wave_sync_lds();
 }
 
-// Work items of the ray kernel: block b takes item b first (no atomic: the
-// blocks of a launch would otherwise all meet on the counter at once), then
-// items gridDim.x + the counter's successive values.
-__device__ __forceinline__ int next_item(int32_t* counter, int* s_item)
+// Work items of the ray kernel: block b takes item b first (no atomic), then
+// the items that its counter hands out (QueueDev).  The counter's blocks are
+// b % kRayQueues, + kRayQueues, ...: their first items precede its further ones.
+__device__ __forceinline__ int next_item(QueueDev* q, int* s_item)
 {
     __syncthreads();
-    if (threadIdx.x == 0) *s_item = (int)gridDim.x + atomicAdd(counter, 1);
+    if (threadIdx.x == 0) {
+        const int g = (int)blockIdx.x % kRayQueues;
+        const int blocks = ((int)gridDim.x - g + kRayQueues - 1) / kRayQueues;
+        *s_item = g + kRayQueues * (blocks + atomicAdd(&q->q[g].next, 1));
+    }
     __syncthreads();
     return *s_item;
 }
@@ -633,7 +637,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(LAB &&
         for (int i = threadIdx.x; i < a.n_labels * a.n_labels; i += kThreads) s_pair[i] = a.pair_rt[i];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);   // wave-uniform: scalar per-scanline values
-    for (int item = (int)blockIdx.x;; item = next_item(&q->next_ray, &s_item)) {
+    for (int item = (int)blockIdx.x;; item = next_item(q, &s_item)) {
         if (item >= a.n_ray) break;
         const ItemRay it = a.ray_items[item];
         EnvDev e = a.envs[it.env];
@@ -697,7 +701,8 @@ __global__ __launch_bounds__(TX / kSx * kWave) void k_psf(PhysArgs a)
     // tile needs two barriers (staged -> filter, output written -> stores): the
     // next tile's staging and taps follow the second one, which every wave
     // passes only after filtering.
-    if (a.ray_queue && blockIdx.x == 0 && tid == 0) a.ray_queue->next_ray = 0;   // for the next step's ray kernel
+    if (a.ray_queue && blockIdx.x == 0)   // for the next step's ray kernel
+        for (int i = tid; i < kRayQueues; i += kPT) a.ray_queue->q[i].next = 0;
     const int r_max = a.max_rlat < kRB ? kRB : a.max_rlat;
     float* sY = lds + kAS * (2 * (TX + 2 * r_max) + TX);   // [kTileRows][TX + 1]
     for (int item = blockIdx.x; item < a.n_psf; item += gridDim.x) {
@@ -1077,7 +1082,7 @@ __global__ __launch_bounds__(kThreads) void k_upload_small(uint4* __restrict__ d
 
 __global__ void k_queue_reset(QueueDev* q, int n)
 {
-    if ((int)threadIdx.x < n) q[threadIdx.x].next_ray = 0;
+    for (int i = threadIdx.x; i < n * kRayQueues; i += blockDim.x) q[i / kRayQueues].q[i % kRayQueues].next = 0;
 }
 
 // linear [nz][ny][nx] label map -> bricked layout, one thread per destination byte (padding voxels 0)

@@ -84,10 +84,16 @@ struct DebugDev {
 // label volumes with at most this many labels take r and t from a pair table
 constexpr int kPairLabels = 16;
 
-// work-queue state of the two persistent kernels (device)
+// Work counters of a ray kernel launch (device), each on a line of its own.  Block b draws from counter
+// b % kRayQueues, which hands out the items i with i % kRayQueues = b % kRayQueues.  One counter for all blocks
+// serialised them: its atomics took 10 to 12 ns each (they pass between the XCDs), 28 us of the 60 us that the
+// 3840 items of 256 volumetric probes took.
+constexpr int kRayQueues = 64;
 struct QueueDev {
-    int32_t next_ray;    // next ray work item
-    int32_t pad[3];
+    struct {
+        int32_t next;    // items of the counter's share taken beyond its blocks' first ones
+        int32_t pad[31];
+    } q[kRayQueues];
 };
 
 struct PhysArgs {
