@@ -2,11 +2,12 @@
 // include/sonosim.h): per-step surface points from the plan's image planes
 // and their voxelisation in the current probe frame.
 //
-//  * update  -- one wave per (image plane, scanline): its lanes take the
-//               scanline's nearest labels (the physics path's Q16 geometry) 64
-//               rows at a time, a ballot finds the first bone pixel, and one
-//               lane applies the keyed miss test and appends the point (FP64,
-//               volume mm) to its env's list with one atomic.
+//  * update  -- a block per 16 scanlines of an image plane: a wave's lanes take
+//               the nearest labels of four scanlines (the physics path's Q16
+//               geometry) 64 rows at a time, ballots find the first bone pixels,
+//               and a lane per scanline applies the keyed miss test and appends
+//               its point (FP64, volume mm) to the env's list, with one atomic
+//               for the block.
 //  * observe -- one workgroup per env: clears the env's 40^3 grid, then maps
 //               every stored point into the current probe frame and marks its
 //               cell (racing stores of the same value 1 are benign).
@@ -64,6 +65,13 @@ __device__ __forceinline__ void philox_ctr(uint32_t c0, uint32_t c1, uint32_t c2
     w[3] = c3;
 }
 
+// A block takes kUpScan neighbouring scanlines of one image plane, a wave kUpWave of them side by side: the
+// label gathers of a 64-row step of all its scanlines are in flight together, and the block appends its points
+// with one atomic.  The kernel is bound by the latency of these gathers and by the atomics (an env's list has
+// one counter, and the envs' counters share lines): with a wave and an atomic per scanline 100 envs of
+// 150 x 200 took 25 us.
+constexpr int kUpWave = 4, kUpScan = 4 * kUpWave;
+
 __global__ __launch_bounds__(256) void k_recon_update(const EnvDev* __restrict__ envs, int n_planes,
                                                       const VolDev* __restrict__ vols, const double* __restrict__ poses,
                                                       const uint8_t* __restrict__ bone, int step, uint32_t k0, uint32_t k1,
@@ -72,21 +80,29 @@ __global__ __launch_bounds__(256) void k_recon_update(const EnvDev* __restrict__
 {
 #pragma clang fp contract(off)
     __shared__ uint8_t s_bone[256];
+    __shared__ int s_row[kUpScan];   // first bone row of each scanline, -1: none
     s_bone[threadIdx.x] = bone[threadIdx.x];
     __syncthreads();
-    // one wave per scanline; its lanes look at 64 rows at a time
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int k = blockIdx.y;   // image plane (internal env)
     if (k >= n_planes) return;
     const EnvDev e = envs[k];
-    const int x = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (!e.valid || x >= e.W) return;
+    const int x0 = (int)blockIdx.x * kUpScan;
+    if (!e.valid || x0 >= e.W) return;
     const VolDev v = vols[e.vol];
-    int yb = -1;
-    for (int y0 = 0; y0 < e.H && yb < 0; y0 += 64) {
+    int row[kUpWave];
+    bool open = false;   // some scanline has rows left to look at
+#pragma unroll
+    for (int s = 0; s < kUpWave; ++s) {
+        row[s] = -1;
+        open = open || x0 + wave * kUpWave + s < e.W;
+    }
+    for (int y0 = 0; y0 < e.H && open; y0 += 64) {
         const int y = y0 + lane;
-        bool is_bone = false;
-        if (y < e.H) {
+        int lab[kUpWave];
+#pragma unroll
+        for (int s = 0; s < kUpWave; ++s) {
+            const int x = x0 + wave * kUpWave + s;
             int32_t q[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c)
@@ -94,18 +110,35 @@ __global__ __launch_bounds__(256) void k_recon_update(const EnvDev* __restrict__
             const int32_t ix = (int32_t)((uint32_t)q[0] + 32768u) >> 16;
             const int32_t iy = (int32_t)((uint32_t)q[1] + 32768u) >> 16;
             const int32_t iz = (int32_t)((uint32_t)q[2] + 32768u) >> 16;
-            const bool in =
-                (uint32_t)ix < (uint32_t)v.nx && (uint32_t)iy < (uint32_t)v.ny && (uint32_t)iz < (uint32_t)v.nz;
-            const int lab = in ? (int)v.labels[brick_offset(v, ix, iy, iz)] : 0;
-            is_bone = s_bone[lab] != 0;
+            const bool in = row[s] < 0 && y < e.H && x < e.W && (uint32_t)ix < (uint32_t)v.nx &&
+                            (uint32_t)iy < (uint32_t)v.ny && (uint32_t)iz < (uint32_t)v.nz;
+            lab[s] = in ? (int)v.labels[brick_offset(v, ix, iy, iz)] : 0;
         }
-        const unsigned long long b = __ballot(is_bone);
-        if (b) yb = y0 + __ffsll((long long)b) - 1;
+        open = false;
+#pragma unroll
+        for (int s = 0; s < kUpWave; ++s) {
+            const int x = x0 + wave * kUpWave + s;
+            const unsigned long long b = __ballot(y < e.H && x < e.W && s_bone[lab[s]] != 0);
+            if (row[s] < 0 && b) row[s] = y0 + __ffsll((long long)b) - 1;
+            open = open || (row[s] < 0 && x < e.W);
+        }
     }
-    if (yb < 0 || lane != 0) return;
+#pragma unroll
+    for (int s = 0; s < kUpWave; ++s)
+        if (lane == s) s_row[wave * kUpWave + s] = row[s];
+    __syncthreads();
+    if (wave != 0) return;
+    const int x = x0 + lane;
+    const int yb = lane < kUpScan && x < e.W ? s_row[lane] : -1;
     uint32_t w[4];
     philox_ctr((uint32_t)x | ((uint32_t)e.plane << 16), (uint32_t)e.pose_env, (uint32_t)step, kReconTag, k0, k1, w);
-    if (!((unsigned long long)w[0] < keep)) return;
+    const bool hit = yb >= 0 && (unsigned long long)w[0] < keep;
+    const unsigned long long hits = __ballot(hit);
+    if (!hits) return;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&counts[e.pose_env], __popcll(hits));
+    base = __shfl(base, 0);
+    if (!hit) return;
     const double* pose = poses + 12 * e.pose_env;
     double a = -0.5 * (double)(e.W - 1);
     a = a * e.dx64;
@@ -123,7 +156,7 @@ __global__ __launch_bounds__(256) void k_recon_update(const EnvDev* __restrict__
         s = s + pose[4 * c + 3];
         p[c] = s;
     }
-    const int idx = atomicAdd(&counts[e.pose_env], 1);
+    const int64_t idx = (int64_t)base + __popcll(hits & ((1ull << lane) - 1ull));
     if (idx < capacity) {
         double* o = pts + ((int64_t)e.pose_env * capacity + idx) * 3;
         o[0] = p[0];
@@ -228,7 +261,7 @@ extern "C" sg_status sg_recon_update(sg_ctx* c, int32_t id, int32_t step)
     (void)hipSetDevice(c->device);
     int maxW = 1;
     for (const EnvDev& e : p->envs) maxW = std::max(maxW, (int)e.W);
-    const dim3 grid((unsigned)((maxW + 3) / 4), (unsigned)p->n_envs);   // a wave per scanline
+    const dim3 grid((unsigned)((maxW + kUpScan - 1) / kUpScan), (unsigned)p->n_envs);
     hipLaunchKernelGGL(k_recon_update, grid, dim3(256), 0, c->stream, (const EnvDev*)p->d_envs.p, p->n_envs,
                        (const VolDev*)c->d_vols.p, (const double*)p->d_poses.p, (const uint8_t*)r->bone.p, step,
                        (uint32_t)r->seed, (uint32_t)(r->seed >> 32), r->keep, r->capacity, (double*)r->points.p,

@@ -50,3 +50,32 @@ def test_every_item_is_taken_once(sess, n):
         sg.sg_simulate(sess.ctx, np.repeat(vid, n), many.probes, many.poses, single, offs)
     assert np.array_equal(single.cpu().numpy().reshape(n, -1), np.broadcast_to(ref, (n, ref.size)))
     sg.sg_batch_plan_destroy(sess.ctx, plan)
+
+
+# 16 scanlines a block, four a wave, 64 rows a step; with air among the bone labels the rows outside the volume
+# are surface points too
+@pytest.mark.parametrize("bone", [(2, 3), (0, 3)])
+@pytest.mark.parametrize("H", [1, 64, 65, 130])
+def test_surface_points_of_ragged_frames(sess, H, bone):
+    import oracle
+    from paper_2507_01152_amd import sonosim as sg
+    widths = [1, 3, 15, 16, 17, 33]
+    wl = synth.ellipsoid_workload(seed=9, n_envs=len(widths), n=32)
+    wl.probes = [Probe(W=w, H=H, dx=0.7, dy=0.7) for w in widths]
+    wl.probes[3] = Probe(W=16, H=H, dx=0.7, dy=0.7, n_elev=3, elev=4.0)
+    vids = sess.load(wl)
+    offs, total = wl.out_offsets()
+    plan = sg.sg_batch_plan_create(sess.ctx, vids, wl.probes, offs)
+    sg.sg_batch_set_poses(sess.ctx, plan, wl.poses)
+    sg.sg_batch_step(sess.ctx, plan, torch.empty(total, device="cuda"))
+    rid = sg.sg_recon_create(sess.ctx, plan, 64, bone, 0.2, seed=5)
+    sg.sg_recon_update(sess.ctx, rid, 1)
+    stored, over = sg.sg_recon_counts(sess.ctx, rid, wl.n_envs)
+    for e in range(wl.n_envs):
+        ref = oracle.recon_points(wl.volumes[e], wl.probes[e], wl.poses[e], e, 1, 5, 0.2, bone)
+        got = sg.sg_recon_points(sess.ctx, rid, e, 64)
+        key = lambda a: a[np.lexsort(a.T[::-1])]
+        assert stored[e] == len(ref) and over[e] == 0
+        assert np.array_equal(key(got), key(ref)), e
+    sg.sg_recon_destroy(sess.ctx, rid)
+    sg.sg_batch_plan_destroy(sess.ctx, plan)
