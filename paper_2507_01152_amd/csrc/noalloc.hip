@@ -98,7 +98,7 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
     static_assert(sizeof(ItemRay) == sizeof(ItemPsf), "one item array");
     const int64_t item_cap = (int64_t)((kParamBytes - o_items) / sizeof(ItemRay));
 
-    int64_t pool_used = 0, scr = 0;
+    int64_t pool_used = 0, scr = 0, scanlines = 0;
     int n_int = 0, max_rlat = 0, multiscale = 0, any_ct = 0;
     for (int i = 0; i < n; ++i) {
         for (int k = 0; k < 12; ++k)
@@ -117,6 +117,7 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
                 return fail(SG_ERANGE, "env %d plane %d: image plane outside the fixed-point range (|Q16| > 2^30)",
                             i, j);
             scr += (int64_t)probes[i].W * ed.ld;
+            scanlines += probes[i].W;
             max_rlat = std::max(max_rlat, ed.rlat);
             ++n_int;
         }
@@ -133,13 +134,14 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
         if (envs[x].W != envs[y].W) return envs[x].W > envs[y].W;
         return x < y;
     });
-    // work lists of sg_simulate's launch shape: groups of kRayWaves scanlines, PSF tiles of 32 x 64
-    constexpr int kTx = 32;
+    // work lists of sg_simulate's launch shape
+    const LaunchShape shape = default_shape(scanlines, c->n_cu);
+    const int tile = shape.tx, group = kRayWaves * shape.spw;
     ItemRay* rays = reinterpret_cast<ItemRay*>(g_stage + o_items);
     int64_t nr = 0;
     for (int k = 0; k < n_int; ++k) {
         const int e = order[k];
-        for (int x0 = 0; x0 < envs[e].W; x0 += kRayWaves) {
+        for (int x0 = 0; x0 < envs[e].W; x0 += group) {
             if (nr >= item_cap) return fail(SG_ERANGE, "sg_simulate_noalloc: work lists exceed the scratch");
             rays[nr++] = ItemRay{e, x0};
         }
@@ -148,7 +150,7 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
     int64_t nt = 0;
     for (int k = 0; k < n_int; ++k) {
         const int e = order[k];
-        const int tx = (envs[e].W + kTx - 1) / kTx, ty = (envs[e].H + 63) / 64;
+        const int tx = (envs[e].W + tile - 1) / tile, ty = (envs[e].H + 63) / 64;
         for (int j = 0; j < ty; ++j)
             for (int i = 0; i < tx; ++i) {
                 if (nr + nt >= item_cap) return fail(SG_ERANGE, "sg_simulate_noalloc: work lists exceed the scratch");
@@ -179,7 +181,7 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
     a.fT = a.fR + scr;
     a.fE = a.fT + scr;
     a.out = out;
-    a.scanlines_per_wave = 1;
+    a.scanlines_per_wave = shape.spw;
     a.max_rlat = max_rlat;
     a.multiscale = multiscale;
     a.any_ct = any_ct;
@@ -188,7 +190,7 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
     if ((e = launch_queue_reset(q, 1, c->stream)) != hipSuccess) return hip_fail(e, "queue reset");
     if ((e = launch_ray(a, q, ray_grid(c->n_cu, multiscale != 0, ray_label_only(a), false), c->stream)) != hipSuccess)
         return hip_fail(e, "ray kernel launch");
-    if ((e = launch_psf(a, kTx, psf_grid(kTx, max_rlat, c->n_cu), c->stream)) != hipSuccess)
+    if ((e = launch_psf(a, tile, psf_grid(tile, max_rlat, c->n_cu), c->stream)) != hipSuccess)
         return hip_fail(e, "PSF kernel launch");
     return SG_OK;
 }

@@ -52,7 +52,7 @@ struct HostVolume {
 
 struct LaunchShape {
     int spw = 1;      // scanlines per wave in a ray item
-    int tx = 32;      // PSF tile width (scanlines); tiles are 64 rows high
+    int tx = 64;      // PSF tile width (scanlines); tiles are 64 rows high
     int chunks = 1;   // env chunks: the PSF kernel of chunk k runs beside the ray kernel of chunk k + 1
 };
 constexpr int kMaxChunks = 4;
@@ -137,6 +137,18 @@ int probe_planes(const sg_probe& p);                 // image planes of a probe 
 double plane_elevation(const sg_probe& p, int j);   // elevation b of plane j, mm
 void build_items(const std::vector<EnvDev>& envs, const std::vector<int>& order, int spw, int tx,
                  std::vector<ItemRay>& rays, std::vector<ItemPsf>& tiles);
+// launch shape of a call, and of a plan before it is tuned: `scanlines` of all planes together.  Fewer scanlines
+// per ray item spread a small call over the GPU (64 frames of 128 x 256: 31, 33, 39 us of ray kernel with 4, 8,
+// 16), more save item changes once every resident block (about six per compute unit) has several items (256
+// volumetric probes, 12,800 items of 4: 62, 49, 47 us).  Tiles of 64 scanlines are the fastest from one frame
+// (8.2 against 8.5 us with 32) to 256 (32 against 39 us).
+inline LaunchShape default_shape(int64_t scanlines, int n_cu)
+{
+    const int64_t items = scanlines / kRayWaves, resident = 6 * (int64_t)n_cu;
+    LaunchShape s;
+    s.spw = items <= 2 * resident ? 1 : (items <= 6 * resident ? 2 : 4);
+    return s;
+}
 sg_status sync_volumes(sg_ctx* c);
 // entry point without allocation (noalloc.hip): its device scratch and limits
 constexpr size_t kNoAllocBytes = SG_NOALLOC_SCRATCH_BYTES;
@@ -144,7 +156,7 @@ constexpr int kNoAllocMaxPlanes = SG_NOALLOC_MAX_PLANES;
 hipError_t noalloc_init(int device);   // with `device` current; once per device (later calls return at once)
 
 struct StageInfo {
-    int tile_x = 32;
+    int tile_x = 64;
     int max_pixels = 0;
 };
 sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_probe* probes, const double* poses,

@@ -509,7 +509,7 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
     // one internal env per image plane (volumetric probes have several)
     std::vector<EnvDev> envs;
     std::vector<float> pool;
-    int64_t scr = 0;
+    int64_t scr = 0, scanlines = 0;
     int max_rlat = 0, max_px = 0, multiscale = 0, any_ct = 0;
     for (int i = 0; i < n; ++i) {
         for (int k = 0; k < 12; ++k)
@@ -528,6 +528,7 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
                 return fail(SG_ERANGE, "env %d plane %d: image plane outside the fixed-point range (|Q16| > 2^30)",
                             i, j);
             scr += (int64_t)probes[i].W * ed.ld;
+            scanlines += probes[i].W;
             max_rlat = std::max(max_rlat, ed.rlat);
             max_px = std::max(max_px, probes[i].W * probes[i].H);
             envs.push_back(ed);
@@ -545,8 +546,8 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
     });
     std::vector<ItemRay> rays;
     std::vector<ItemPsf> tiles;
-    const int spw = 1, tx = 32;
-    build_items(envs, order, spw, tx, rays, tiles);
+    const LaunchShape shape = default_shape(scanlines, c->n_cu);
+    build_items(envs, order, shape.spw, shape.tx, rays, tiles);
 
     // one staging block: envs | taps | ray items | psf items
     auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
@@ -609,12 +610,12 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
         a.dbg.intensity = dbg->intensity;
         a.dbg.scatter = dbg->scatter;
     }
-    a.scanlines_per_wave = spw;
+    a.scanlines_per_wave = shape.spw;
     a.max_rlat = max_rlat;
     a.multiscale = multiscale;
     a.any_ct = any_ct;
     a.ray_queue = (QueueDev*)c->queue.p;
-    info.tile_x = tx;
+    info.tile_x = shape.tx;
     info.max_pixels = max_px;
     return SG_OK;
 }
