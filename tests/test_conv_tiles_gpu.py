@@ -1,0 +1,95 @@
+"""Conv products at the edges of the kernels' tiles and of the rules that
+choose them (GPU), against torch in FP64 on the CPU.
+
+Bars: bf16 products are exact in FP32, so an FP32 sum of K terms lies within
+(K + 2) u sum|terms| of the exact sum (u = 2^-24, any order); a bf16 store
+adds at most 2^-8 of the stored magnitude.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+U, BF = 2.0 ** -24, 2.0 ** -8
+
+
+@pytest.fixture(scope="module")
+def sess():
+    from paper_2507_01152_amd.session import Session
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    s = Session(0)
+    yield s
+    s.close()
+
+
+def _conv(x, w, stride, up):
+    """NHWC x, [Co][k][k][C] w, FP64, pad k // 2."""
+    x = x.permute(0, 3, 1, 2)
+    if up:
+        x = x.repeat_interleave(2, 2).repeat_interleave(2, 3)
+    return torch.nn.functional.conv2d(x, w.permute(0, 3, 1, 2), stride=stride, padding=w.shape[1] // 2).permute(0, 2, 3, 1)
+
+
+def _check(got, exact, bound, what):
+    err = (got.cpu().double() - exact).abs()
+    assert bool((err <= bound).all()), (what, float((err / bound.clamp_min(1e-300)).max()))
+
+
+def _layer(sess, n, h, w, c, co, k=3, stride=1, up=0, seed=0):
+    """Forward (bf16 and FP32), data gradient (written and added into) and weight gradient of one layer."""
+    from paper_2507_01152_amd import sonosim as sg
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn((n, h, w, c), generator=g).bfloat16()
+    wt = (torch.randn((co, k, k, c), generator=g) * 0.1).bfloat16()
+    b = torch.randn(co, generator=g)
+    x64, w64 = x.double().requires_grad_(True), wt.double().requires_grad_(True)
+    v = _conv(x64, w64, stride, up)
+    dy = torch.randn(v.shape, generator=g).bfloat16()
+    dx, dw = torch.autograd.grad(v, (x64, w64), dy.double())
+    xa, wa = x.double().abs().requires_grad_(True), wt.double().abs().requires_grad_(True)
+    va = _conv(xa, wa, stride, up)
+    dxa, dwa = torch.autograd.grad(va, (xa, wa), dy.double().abs())
+    v, va = v.detach(), va.detach()
+    d = sg.conv_desc(n, h, w, c, co, k, stride, k // 2, up)
+    X, Wt, B, DY = (t.cuda() for t in (x, wt, b, dy))
+    y, y32 = torch.empty_like(DY), torch.empty(DY.shape, device="cuda")
+    sg.sg_conv_forward(sess.ctx, d, X, Wt, B, True, y=y, y_f32=y32)
+    exact = torch.relu(v + b.double())
+    bound = (k * k * c + 3) * U * (va + b.double().abs())
+    _check(y32, exact, bound + 1e-30, "y_f32")
+    _check(y, exact, bound + BF * (exact + bound) + 1e-30, "y")
+    old = torch.randn(x.shape, generator=g).cuda()
+    D = torch.full(x.shape, 7.0, device="cuda")
+    sg.sg_conv_backward_data(sess.ctx, d, DY, Wt, D)
+    kd = (4 if up else 1) * k * k * co
+    _check(D, dx, (kd + 6) * U * dxa + 1e-30, "dx")
+    D = old.clone()
+    sg.sg_conv_backward_data(sess.ctx, d, DY, Wt, D, accumulate=True)
+    _check(D, dx + old.cpu().double(), (kd + 8) * U * (dxa + old.cpu().double().abs()) + 1e-30, "dx added")
+    dW, dB = torch.empty(wt.shape, device="cuda"), torch.empty(co, device="cuda")
+    sg.sg_conv_backward_weight(sess.ctx, d, X, DY, dW, dB)
+    m = dy.numel() // co
+    _check(dW, dw, (m + 8) * U * dwa + 1e-30, "dw")
+    _check(dB, dy.double().sum((0, 1, 2)), (m + 8) * U * dy.double().abs().sum((0, 1, 2)) + 1e-30, "db")
+
+
+# few rows: the smallest tiles (64 x 16, 64 x 32, 32 x 64), rows around their edges, columns past one tile
+@pytest.mark.parametrize("m", [1, 31, 33, 64, 65, 129])
+@pytest.mark.parametrize("c,co", [(40, 8), (40, 16), (64, 24), (32, 40), (96, 64), (64, 72), (32, 136)])
+def test_smallest_gemm_tiles(sess, m, c, co):
+    _layer(sess, 1, 1, m, c, co, seed=m + co)
+
+
+# enough blocks for the next larger tiles (64 x 64, 128 x 64, 128 x 32, 256 x 16), ragged in rows
+@pytest.mark.parametrize("h,w,c,co", [(127, 131, 40, 128), (257, 129, 40, 72), (255, 259, 40, 32), (259, 509, 40, 8)])
+def test_larger_gemm_tiles(sess, h, w, c, co):
+    _layer(sess, 1, h, w, c, co, seed=h)
+
+
+# stride 2 (four parity classes, one of them without rows on a side of one pixel) and 1 x 1
+@pytest.mark.parametrize("n,h,w,c,co,k,stride", [(1, 2, 3, 40, 64, 3, 2), (3, 17, 16, 64, 40, 3, 2), (2, 33, 7, 128, 136, 3, 2),
+                                                (2, 9, 11, 64, 72, 1, 1)])
+def test_stride_and_pointwise(sess, n, h, w, c, co, k, stride):
+    _layer(sess, n, h, w, c, co, k, stride, seed=n)
