@@ -184,13 +184,15 @@ sg_status wgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* x, const uint16_
                 DevBuf& parts)
 {
     ConvGeom g = geom_of(sh, 2);
-    const int cs_blocks0 = blocks_for(g.Kw, 512);
+    // blocks of the bias gradient's column sums, by elements (about four 8-channel chunks per thread): by pixels
+    // alone 131072 pixels of 64 channels got 32 blocks (23 us; 4.8 with 512) and 9805 of 72 got 3 (21.6 us; 4.0 with 44)
+    const int cs_blocks = blocks_for(g.Kw * sh.Co / 2, 512);
     WgradTilePlan tp;
     if (wgrad_tile_plan(g, &tp)) {   // stride 1: direct tiled kernel, one partial per block and channel group
-        const size_t need = sizeof(float) * std::max<int64_t>(wgrad_tile_part_floats(tp), (int64_t)cs_blocks0 * sh.Co);
+        const size_t need = sizeof(float) * std::max<int64_t>(wgrad_tile_part_floats(tp), (int64_t)cs_blocks * sh.Co);
         SG_TRY(check(parts.ensure(need), "wgrad workspace"));
         SG_TRY(check(wgrad_tile(g, x, dy, (float*)parts.p, tp, dw, c->stream), "wgrad launch"));
-        if (db) SG_TRY(check(colsum_bf16(dy, g.Kw, sh.Co, (float*)parts.p, cs_blocks0, db, c->stream), "bias grad"));
+        if (db) SG_TRY(check(colsum_bf16(dy, g.Kw, sh.Co, (float*)parts.p, cs_blocks, db, c->stream), "bias grad"));
         return SG_OK;
     }
     const int bm = wgrad_tile_m((int)g.M);
@@ -202,7 +204,6 @@ sg_status wgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* x, const uint16_
     if (splits > nkt) splits = nkt;
     const int64_t k_chunk = ((nkt + splits - 1) / splits) * 32;
     splits = (g.Kw + k_chunk - 1) / k_chunk;
-    const int cs_blocks = blocks_for(g.Kw, 512);
     const size_t need = sizeof(float) * std::max<int64_t>(splits * g.M * g.N, (int64_t)cs_blocks * sh.Co);
     SG_TRY(check(parts.ensure(need), "wgrad workspace"));
     ConvArgs a;
