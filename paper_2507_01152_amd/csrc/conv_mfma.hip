@@ -117,8 +117,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
         g.par = par;
         g.Hc = g0.hc4[par];
         g.Wc = g0.wc4[par];
-        g.f_hinwin = g0.f_hw4[par];
-        g.f_win = g0.f_w4[par];
+        g.f_hw = g0.f_hw4[par];
+        g.f_w = g0.f_w4[par];
         g.M = (g0.Kw / ((int64_t)g0.Ho * g0.Wo)) * g.Hc * g.Wc;
         g.K = (pa + 1) * (pb + 1) * g0.Co;
         if ((int64_t)blockIdx.x * BM >= g.M) return;   // this class has fewer row tiles
@@ -201,13 +201,16 @@ __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
                     a_wb[i] = wo * g.stride - g.pad;
                     a_base[i] = (int64_t)n * g.H * g.W * g.C;
                 } else {
-                    // pixel (h, w) of image n; a parity class counts only its own pixels
+                    // pixel (h, w) of image n; a parity class counts only its own pixels; an upsampled input's
+                    // rows are quads, the four fine pixels of one stored pixel
                     const bool pc = g.par >= 0;
-                    const int n = (int)fdiv((uint32_t)m, g.f_hinwin);
-                    const int rem = m - n * (pc ? g.Hc * g.Wc : Hin * Win);
-                    const int qh = (int)fdiv((uint32_t)rem, g.f_win);
-                    const int qw = rem - qh * (pc ? g.Wc : Win);
-                    const int h = pc ? 2 * qh + (g.par >> 1) : qh, w = pc ? 2 * qw + (g.par & 1) : qw;
+                    const int q = g.up ? m >> 2 : m;
+                    const int n = (int)fdiv((uint32_t)q, g.f_hw);
+                    const int rem = q - n * (pc ? g.Hc * g.Wc : g.H * g.W);
+                    const int qh = (int)fdiv((uint32_t)rem, g.f_w);
+                    const int qw = rem - qh * (pc ? g.Wc : g.W);
+                    const int h = pc ? 2 * qh + (g.par >> 1) : (g.up ? 2 * qh + ((m >> 1) & 1) : qh);
+                    const int w = pc ? 2 * qw + (g.par & 1) : (g.up ? 2 * qw + (m & 1) : qw);
                     a_hb[i] = h + g.pad;
                     a_wb[i] = w + g.pad;
                     a_base[i] = (int64_t)n * g.Ho * g.Wo * g.Co;
@@ -610,15 +613,41 @@ __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
         if (row >= g.M) return -1;
         if constexpr (MODE == kDgrad) {
             if (g.par >= 0) {
-                const int n = (int)fdiv((uint32_t)row, g.f_hinwin);
+                const int n = (int)fdiv((uint32_t)row, g.f_hw);
                 const int rem = (int)row - n * g.Hc * g.Wc;
-                const int qh = (int)fdiv((uint32_t)rem, g.f_win);
+                const int qh = (int)fdiv((uint32_t)rem, g.f_w);
                 const int qw = rem - qh * g.Wc;
                 return ((int64_t)n * g.H + 2 * qh + (g.par >> 1)) * g.W + 2 * qw + (g.par & 1);
             }
         }
         return row;
     };
+    if (MODE == kDgrad && g.up) {
+        // a lane's four rows are one stored pixel's quad: summed here, so the fine gradient (67 MB for 131072
+        // pixels of 128 channels) never leaves the registers; written out and summed by a kernel of its own, the
+        // layer of 32768 stored pixels took 41 + 16 us, with this epilogue 38
+        float pre[FM][FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const int64_t row = (int64_t)m_base + wm * TM + i * 16 + (lane >> 4) * 4;   // M is a multiple of 4
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const int col = n_base + wn * TN + j * 16 + (lane & 15);
+                pre[i][j] = (a.accumulate && col < g.N && row < g.M) ? a.out_f32[(row >> 2) * g.C + col] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const int64_t row = (int64_t)m_base + wm * TM + i * 16 + (lane >> 4) * 4;
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                const int col = n_base + wn * TN + j * 16 + (lane & 15);
+                const float v = (acc[i][j][0] + acc[i][j][1]) + (acc[i][j][2] + acc[i][j][3]);
+                if (col < g.N && row < g.M) a.out_f32[(row >> 2) * g.C + col] = a.accumulate ? pre[i][j] + v : v;
+            }
+        }
+        return;
+    }
     if (MODE == kDgrad && a.accumulate) {
         // per row tile, the old values are all loaded before the tile's first store (a load issued
         // after a store waits for it)
@@ -1297,24 +1326,6 @@ __global__ void k_mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out,
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const float v = (y == nullptr || bf2f(y[i]) > 0.f) ? g[i] : 0.f;
         out[i] = f2bf(v);
-    }
-}
-
-// coarse[n][h][w][c] (+)= sum of the 2x2 fine block (backward of the x2 upsample)
-__global__ void k_pool2x2_sum(const float* fine, float* coarse, int N, int H, int W, int C, int accumulate)
-{
-    const int64_t total = (int64_t)N * H * W * C;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i % C);
-        const int64_t p = i / C;
-        const int w = (int)(p % W);
-        const int64_t q = p / W;
-        const int h = (int)(q % H);
-        const int n = (int)(q / H);
-        const int64_t base = (((int64_t)n * 2 * H + 2 * h) * 2 * W + 2 * w) * C + c;
-        const int64_t rs = (int64_t)2 * W * C;
-        const float s = (fine[base] + fine[base + C]) + (fine[base + rs] + fine[base + rs + C]);
-        coarse[i] = accumulate ? coarse[i] + s : s;
     }
 }
 
@@ -2407,14 +2418,6 @@ int proj_bwd_blocks() { return kProjBlocks; }
 hipError_t mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out, int64_t n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_mask_to_bf16, dim3((unsigned)grid_for(n)), dim3(256), 0, s, g, y, out, n);
-    return hipGetLastError();
-}
-
-hipError_t pool2x2_sum(const float* fine, float* coarse, int N, int H, int W, int C, int accumulate, hipStream_t s)
-{
-    const int64_t n = (int64_t)N * H * W * C;
-    hipLaunchKernelGGL(k_pool2x2_sum, dim3((unsigned)grid_for(n)), dim3(256), 0, s, fine, coarse, N, H, W, C,
-                       accumulate);
     return hipGetLastError();
 }
 

@@ -116,7 +116,7 @@ struct sg_ctx {
     int32_t next_surr = 1;
     std::map<int32_t, std::unique_ptr<sg::Recon, sg::ReconDeleter>> recons;
     int32_t next_recon = 1;
-    sg::DevBuf op_wt, op_fine, op_parts;   // workspaces of the conv op entry points
+    sg::DevBuf op_wt, op_parts;   // workspaces of the conv op entry points
 };
 
 namespace sg {

@@ -78,7 +78,7 @@ struct Surrogate {
     int64_t step = 0;
     int cap = 0, cap_grad = 0, last_n = 0;
     DevBuf act[kNumT], gact[kNumT];
-    DevBuf dpre, fine, parts, yhat, target, gy, loss, psnr, idx;
+    DevBuf dpre, parts, yhat, target, gy, loss, psnr, idx;
     DevBuf bias_parts;   // per-block bias-gradient partials of every layer of a backward pass, reduced at its end
     DevBuf dscan;   // bf16 gradient at the depth map's output (the integral's backward), n x H x W x kScanC
     DevBuf out32;   // FP32 frames of bf16 inference
@@ -219,8 +219,7 @@ sg_status wgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* x, const uint16_
 }
 
 // data gradient of one conv into dx (stored input resolution)
-sg_status dgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* dy, const uint16_t* wt, float* dx, int accumulate,
-                DevBuf& fine)
+sg_status dgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* dy, const uint16_t* wt, float* dx, int accumulate)
 {
     ConvGeom g = geom_of(sh, 1);
     // few channels: the tiled forward conv of dy with mirrored taps (an upsampled layer's 2 x 2 sums in
@@ -232,13 +231,6 @@ sg_status dgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* dy, const uint16
     std::memset(&a, 0, sizeof(a));
     a.a = dy;
     a.b = wt;
-    if (sh.up) {
-        SG_TRY(check(fine.ensure(sizeof(float) * (size_t)g.M * sh.C), "dgrad workspace"));
-        a.out_f32 = (float*)fine.p;
-        a.accumulate = 0;
-        SG_TRY(check(conv_gemm(1, g, a, 1, c->stream), "dgrad launch"));
-        return check(pool2x2_sum((float*)fine.p, dx, sh.N, sh.H, sh.W, sh.C, accumulate, c->stream), "upsample grad");
-    }
     a.out_f32 = dx;
     a.accumulate = accumulate;
     return check(conv_gemm(1, g, a, 1, c->stream), "dgrad launch");
@@ -423,7 +415,7 @@ sg_status backward(sg_ctx* c, Surrogate& s, int n)
                      s.parts));
         if (L > 0) {
             SG_TRY(dgrad(c, sh, (const uint16_t*)s.dpre.p, (const uint16_t*)s.wt.p + s.w_off[L],
-                         (float*)s.gact[d.in].p, written[d.in] ? 1 : 0, s.fine));
+                         (float*)s.gact[d.in].p, written[d.in] ? 1 : 0));
             written[d.in] = true;
         }
     }
@@ -605,7 +597,7 @@ sg_status disc_backward(sg_ctx* c, Surrogate& s, const uint16_t* z, int frames, 
             SG_TRY(wgrad(c, sh, x, (const uint16_t*)s.d_dpre.p, grad + s.dw_off[L], nullptr, s.parts));
         if (L > 0 || input_grad)
             SG_TRY(dgrad(c, sh, (const uint16_t*)s.d_dpre.p, (const uint16_t*)s.d_wt.p + s.dw_off[L],
-                         (float*)s.d_g[L].p + disc_at(s, L, off), 0, s.fine));
+                         (float*)s.d_g[L].p + disc_at(s, L, off), 0));
     }
     return SG_OK;
 }
@@ -740,7 +732,7 @@ extern "C" sg_status sg_conv_backward_data(sg_ctx* c, const sg_conv_desc* d, con
     const int taps = sh.k * sh.k;
     SG_TRY(check(c->op_wt.ensure(sizeof(uint16_t) * (size_t)sh.Co * taps * sh.C), "weight workspace"));
     SG_TRY(check(transpose_w(w, (uint16_t*)c->op_wt.p, sh.Co, taps, sh.C, c->stream), "weight transpose"));
-    return dgrad(c, sh, dy, (const uint16_t*)c->op_wt.p, dx, accumulate ? 1 : 0, c->op_fine);
+    return dgrad(c, sh, dy, (const uint16_t*)c->op_wt.p, dx, accumulate ? 1 : 0);
 }
 
 extern "C" sg_status sg_conv_backward_weight(sg_ctx* c, const sg_conv_desc* d, const uint16_t* x, const uint16_t* dy,
@@ -909,7 +901,7 @@ namespace {
 // every buffer a training step touches: a captured step stays valid while none of them moved
 std::vector<const void*> buffer_ptrs(const Surrogate& s)
 {
-    std::vector<const void*> v = {s.master.p, s.mom1.p, s.mom2.p, s.grad.p, s.wb.p, s.wt.p, s.dpre.p, s.fine.p,
+    std::vector<const void*> v = {s.master.p, s.mom1.p, s.mom2.p, s.grad.p, s.wb.p, s.wt.p, s.dpre.p,
                                   s.parts.p, s.yhat.p, s.target.p, s.gy.p, s.loss.p, s.dscan.p, s.steps.p, s.coef.p,
                                   s.segs.p, s.hist.p, s.bias_parts.p, s.d_master.p, s.d_mom1.p, s.d_mom2.p, s.d_grad.p, s.d_wb.p,
                                   s.d_wt.p, s.d_logits.p, s.d_glog.p, s.d_dpre.p, s.d_bias_scratch.p, s.d_segs.p};

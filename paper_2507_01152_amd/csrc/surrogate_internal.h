@@ -37,11 +37,11 @@ struct ConvGeom {
     int32_t H, W;   // stored input size (before the optional x2 upsampling)
     int32_t Ho, Wo; // output size
     int32_t kh, kw, stride, pad, up;
-    FastDiv f_c, f_co, f_kw, f_stride, f_howo, f_wo, f_hinwin, f_win;
+    FastDiv f_c, f_co, f_kw, f_stride, f_howo, f_wo, f_hw, f_w;
     int32_t kb;     // elements per row of the GEMM's B operand (forward W, data gradient WT): K, or 9 Co
     // data gradient of a stride-2, pad-1 3x3 conv split by output parity (par = 2 (h % 2) + (w % 2), or
     // -1): rows are the Hc x Wc pixels (2 i + h % 2, 2 j + w % 2) of each image, K the Co x taps that
-    // reach them (f_hinwin and f_win then divide by Hc Wc and Wc).  par = 4: all four classes in one
+    // reach them (f_hw and f_w then divide by Hc Wc and Wc).  par = 4: all four classes in one
     // launch, class blockIdx.z, with its sizes and divisors in the arrays below
     int32_t par, Hc, Wc;
     int32_t hc4[4], wc4[4];
@@ -108,8 +108,8 @@ inline ConvGeom geom_of(const ConvShape& s, int mode)
     g.f_stride = make_fastdiv((uint32_t)s.stride);
     g.f_howo = make_fastdiv((uint32_t)(g.Ho * g.Wo));
     g.f_wo = make_fastdiv((uint32_t)g.Wo);
-    g.f_hinwin = make_fastdiv((uint32_t)(s.Hin() * s.Win()));
-    g.f_win = make_fastdiv((uint32_t)s.Win());
+    g.f_hw = make_fastdiv((uint32_t)(s.H * s.W));
+    g.f_w = make_fastdiv((uint32_t)s.W);
     if (mode == 0) {
         g.M = (int64_t)s.N * g.Ho * g.Wo;
         g.N = s.Co;
@@ -187,7 +187,6 @@ hipError_t proj_bwd(const uint16_t* dp, const uint16_t* x, const uint16_t* w, fl
                     float* part, float* dw, hipStream_t s);
 hipError_t depth_scan_bwd(const float* g, int ld, int c_off, float* g_skip, uint16_t* dp, float* part,
                           float* bias_grad, int N, int H, int W, float scale, hipStream_t s);
-hipError_t pool2x2_sum(const float* fine, float* coarse, int N, int H, int W, int C, int accumulate, hipStream_t s);
 hipError_t colsum_bf16(const uint16_t* x, int64_t rows, int cols, float* part, int blocks, float* out,
                        hipStream_t s);
 hipError_t sum_parts(const float* part, int64_t n, int splits, float* out, hipStream_t s);

@@ -93,3 +93,13 @@ def test_larger_gemm_tiles(sess, h, w, c, co):
                                                 (2, 9, 11, 64, 72, 1, 1)])
 def test_stride_and_pointwise(sess, n, h, w, c, co, k, stride):
     _layer(sess, n, h, w, c, co, k, stride, seed=n)
+
+
+# inputs read upsampled: the data gradient's quads of fine pixels, over every tile of the GEMM
+@pytest.mark.parametrize("n,h,w,c,co,k,stride", [(1, 1, 1, 40, 40, 3, 1), (3, 5, 7, 64, 64, 3, 1), (1, 3, 11, 24, 40, 3, 1),
+                                                (2, 9, 8, 16, 64, 3, 1), (2, 7, 5, 136, 72, 3, 1), (1, 65, 63, 72, 40, 3, 1),
+                                                (1, 129, 65, 40, 64, 3, 1), (2, 91, 93, 136, 40, 3, 1),
+                                                (1, 181, 182, 24, 40, 3, 1), (1, 182, 183, 8, 40, 3, 1), (2, 6, 5, 48, 40, 5, 1),
+                                                (2, 6, 5, 48, 40, 3, 2)])
+def test_upsampled_layers(sess, n, h, w, c, co, k, stride):
+    _layer(sess, n, h, w, c, co, k, stride, up=1, seed=h)
