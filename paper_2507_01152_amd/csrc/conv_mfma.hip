@@ -107,6 +107,7 @@ __device__ __forceinline__ void dma16(const uint16_t* src, uint16_t* dst_wave)
 }
 // s_waitcnt immediate with expcnt and lgkmcnt at their maxima: OR in a vmcnt below 16
 constexpr int kWaitVm0 = 0x0F70;
+constexpr int kWaitLgkm0 = 0xC07F;   // lgkmcnt 0, vmcnt and expcnt at their maxima
 
 template <int MODE, int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
@@ -1007,232 +1008,226 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 // Direct 3x3 weight gradient (pad 1; stride 1, or 2 with S2): dW[co][r][s][ci] = sum over
 // output pixels p of dy[p][co] x[p + (r - 1, s - 1)][ci], for a group of CI in
 // {8, 16, 24, 32} input and CO in {16, 32} output channels (block y: input
-// group, block z: output group, of a layer with g.C and g.Co channels).  A block stages, per tile of
-// 8 x 32 output pixels, the 10 x 34 halo of x and the tile of dy once in LDS,
-// both transposed to channel planes (pixels contiguous; a thread packs two
-// neighbouring pixels per 4-byte LDS store), so the MFMA operands of one
-// output row are 32 consecutive pixels of a channel: A = dy (m = co), B = x
-// shifted by the tap's column (n = ci), built from one aligned 16-byte and
-// one 4-byte LDS read by byte alignment in registers.  A wave takes one 16-channel group of co and
-// 8 CO / 64 consecutive output rows with all nine taps (every offset a
-// compile-time constant, each staged x row read once per column shift for
-// all its output rows) and keeps its accumulators in registers across the
-// block's tiles; the next tile's chunks are loaded into
-// registers while the current one is multiplied.  Tiles are dealt out with a
-// static stride; at the end the four waves are summed in LDS in a fixed order
-// and the block writes one partial dW, which a fixed-order reduction sums.
-// UP: x is read upsampled x2 (fine pixel (h, w) is stored pixel (h/2, w/2)).
-// S2: stride 2 (x pixel (2 h + r - 1, 2 w + s - 1) meets output pixel (h, w)).
-constexpr int kWgH = 8, kWgW = 32;
-constexpr int kWgXR = kWgH + 2, kWgXC = kWgW + 2;   // staged halo rows and columns
-constexpr int kWgPitch = 40;                        // LDS row pitch (bf16)
-constexpr int kWgXPlane = kWgXR * kWgPitch + 8;     // 204 dwords per channel: banks 12 apart
-constexpr int kWgDPlane = kWgH * kWgPitch + 8;      // 164 dwords per channel: banks 4 apart
-// stride 2: tiles of 4 x 32 outputs; their 9 x 65 input window is staged with the even and the odd
-// columns in separate halves of an 80-element row, so the operands of all three column taps are
-// aligned reads again (tap 0: even half; tap 1: odd half; tap 2: even half one column on)
-constexpr int kWgH2 = 4;
-constexpr int kWgXR2 = 2 * kWgH2 + 1, kWgRow2 = 80, kWgQ2 = 17;   // rows, row length, 4-column items
-constexpr int kWgXPlane2 = kWgXR2 * kWgRow2 + 8;                  // 364 dwords: banks 44 apart
-constexpr int kWgDPlane2 = kWgH2 * kWgPitch + 8;                  // 84 dwords: banks 20 apart
+// group, block z: output group, of a layer with g.C and g.Co channels).  The
+// contraction runs over pixels while memory holds channels together: a block
+// copies, per tile of 8 (stride 2: 4) x 32 output pixels, the halo of x and the
+// tile of dy as they are into LDS (DMA, the next tile's while this one is
+// multiplied; UP: the stored pixels only, fine pixel (h, w) being stored pixel
+// (h / 2, w / 2)) and reads the MFMA operands transposed from there
+// (ds_read_b64_tr_b16: four pixels of a lane's channel; lanes 16 k .. 16 k + 15
+// of a wave hold the addresses of pixels 8 k + i / 4 and channels 4 (i % 4)).
+// The three column shifts of a row come from one set of reads by byte alignment.
+// A wave owns RW output rows and all 9 CI CO sums; at the end the four waves'
+// sums are added in wave order through LDS.
+// Bound by LDS accesses and the latency between a tile's phases, not by memory.
+// With register transposes into channel planes (4-byte LDS stores, three of
+// them for each operand read, and 11 million bank-conflict cycles) 128 -> 64
+// channels on 131072 pixels, read upsampled, took 42 us, 64 -> 64 channels on
+// 131072 pixels 31 us and 32 -> 16 on 2097152 pixels, upsampled, 51 us; now 24,
+// 21 and 25 us.
+constexpr int kWgW = 32;                              // output columns per tile
+constexpr int kWgH = 8, kWgH2 = 4;                    // output rows per tile, stride 1 and 2
+template <int CI, int CO, bool UP, bool S2>
+struct WgTile {
+    static constexpr int TH = S2 ? kWgH2 : kWgH, RW = TH / 4;
+    static constexpr int XR = UP ? TH / 2 + 2 : (S2 ? 2 * TH + 1 : TH + 2);        // staged rows of x
+    static constexpr int XC = UP ? kWgW / 2 + 2 : (S2 ? 2 * kWgW + 2 : kWgW + 2);  // and columns (the first at -1)
+    static constexpr int XN = XR * XC * (CI / 8), DN = TH * kWgW * (CO / 8);       // 16-byte chunks
+    static constexpr int XNP = (XN + 63) / 64 * 64;   // whole waves; dy follows, so reads past x stay in the stage
+    static constexpr int STAGE = (XNP + DN) * 8;      // bf16
+};
+
+// Work groups per compute unit by the registers a thread needs: 9, 18 or 36 quads of sums and the tile's
+// operands (direct: stride 1, not upsampled, the most operands).  With 2 for all, 16 x 16 groups took 30.3
+// instead of 29.8 us (2097152 pixels), upsampled 32 x 16 ones 27.8 instead of 25.4; 3 for direct 24 x 16 ones
+// would spill (47.5 instead of 45.9 us).
+constexpr int wgrad_blocks_per_cu(int ci, int co, bool direct)
+{
+    const int groups = (ci + 15) / 16 * (co / 16);
+    return groups == 1 ? 4 : (groups == 2 && !(direct && ci > 16) ? 3 : 2);
+}
 
 template <int CI, int CO, bool UP, bool S2>
-__global__ __launch_bounds__(256) void k_wgrad3x3_tile(ConvGeom g, const uint16_t* __restrict__ x,
-                                                       const uint16_t* __restrict__ dy, float* __restrict__ part)
+__global__ __launch_bounds__(256, wgrad_blocks_per_cu(CI, CO, !UP && !S2)) void k_wgrad3x3_tile(ConvGeom g, const uint16_t* __restrict__ x,
+                                                          const uint16_t* __restrict__ dy, float* __restrict__ part)
 {
     static_assert(!(UP && S2), "stride 2 reads its input directly");
-    constexpr int NB = (CI + 15) / 16, CB = CO / 16, CIP = NB * 16;
-    constexpr int CI8 = CI / 8, CO8 = CO / 8;
-    constexpr int TH = S2 ? kWgH2 : kWgH;               // output rows per tile
-    constexpr int XROW = S2 ? kWgRow2 : kWgPitch;       // LDS elements per staged input row
-    constexpr int XPL = S2 ? kWgXPlane2 : kWgXPlane, DPL = S2 ? kWgDPlane2 : kWgDPlane;
-    constexpr int RW = TH * CB / 4;   // output rows per wave (the waves split co groups x row groups)
-    // items of one tile's operands and each thread's share: stride 1, 8 channels of two neighbouring
-    // pixels; stride 2 input, 8 channels of four neighbouring pixels
-    constexpr int XN = S2 ? kWgXR2 * kWgQ2 * CI8 : kWgXR * (kWgXC / 2) * CI8, DN = TH * (kWgW / 2) * CO8;
-    constexpr int XE = S2 ? 4 : 2;    // pixels per input item
-    constexpr int XI = (XN + 255) / 256, DI = (DN + 255) / 256;
-    constexpr int SX = CIP * XPL, SD = CO * DPL, NW = CO * 9 * CI;
-    static_assert(NW * 4 <= (SX + SD) * 2, "the cross-wave sum reuses the operand planes");
-    __shared__ __attribute__((aligned(16))) uint16_t smem[SX + SD];
-    uint16_t* sX = smem;
-    uint16_t* sD = smem + SX;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    using T = WgTile<CI, CO, UP, S2>;
+    constexpr int NB = (CI + 15) / 16, ND = CO / 16, NA = 9 * NB * ND;
+    constexpr int CI8 = CI / 8, CO8 = CO / 8, RW = T::RW, XC = T::XC;
+    constexpr int XI = (T::XNP + 255) / 256, DI = (T::DN + 255) / 256;   // DMA loads per thread and stage
+    static_assert(T::DN % 256 == 0, "whole blocks of dy chunks");
+    static_assert(!S2 || CI <= 16, "stride 2 reads every other pixel: 64-byte ones would use half of the LDS banks");
+    __shared__ __attribute__((aligned(16))) uint16_t smem[T::STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lk = lane >> 4;
-    const int Hin = UP ? 2 * g.H : g.H, Win = UP ? 2 * g.W : g.W;
-    const int tiles_x = (g.Wo + kWgW - 1) / kWgW, tiles_y = (g.Ho + TH - 1) / TH;
-    const int64_t per_img = (int64_t)tiles_x * tiles_y;
-    const int64_t total = (g.Kw / ((int64_t)g.Ho * g.Wo)) * per_img;   // Kw = N * Ho * Wo
+    const int tiles_x = (g.Wo + kWgW - 1) / kWgW, tiles_y = (g.Ho + T::TH - 1) / T::TH;
+    const uint32_t per_img = (uint32_t)tiles_x * tiles_y;
+    const uint32_t total = (uint32_t)(g.Kw / ((int64_t)g.Ho * g.Wo)) * per_img;   // <= Kw = N * Ho * Wo < 2^31
     const uint16_t* xg = x + blockIdx.y * CI;    // the block's input channel group
     const uint16_t* dyg = dy + blockIdx.z * CO;  // and output channel group
-    if constexpr (CIP != CI) {   // channels CI .. CIP - 1 stay zero
-        for (int i = tid; i < (CIP - CI) * XPL; i += 256) sX[CI * XPL + i] = 0;
+    const uint64_t zp = reinterpret_cast<uint64_t>(g_zero_buf);
+    const uint32_t zhi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(zp >> 32));
+    const uint32_t zlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)zp);
+    const uint16_t* zsrc = reinterpret_cast<const uint16_t*>(((uint64_t)zhi << 32) | zlo);
+    // this thread's chunks: row and column in the tile (rows past the staged ones: none), channel offset
+    int xy[XI];
+#pragma unroll
+    for (int k = 0; k < XI; ++k) {
+        const int px = (tid + 256 * k) / CI8;
+        xy[k] = ((px / XC) << 16) | (px % XC);
     }
-    const int cbw = wave % CB, r0 = (wave / CB) * RW;   // the wave's co group and first output row
-    f32x4 acc[9][NB];
+    auto issue = [&](uint32_t t) __attribute__((always_inline)) {
+        const uint32_t n = t / per_img, t_in = t - n * per_img;
+        const int ty = (int)(t_in / (uint32_t)tiles_x), tx = (int)t_in - ty * tiles_x;
+        const int ho0 = ty * T::TH, wo0 = tx * kWgW;
+        const int h0 = (UP ? ho0 >> 1 : (S2 ? 2 * ho0 : ho0)) - 1, w0 = (UP ? wo0 >> 1 : (S2 ? 2 * wo0 : wo0)) - 1;
+        const uint16_t* xb = xg + (((int64_t)n * g.H + h0) * g.W + w0) * g.C;
+        const uint16_t* db = dyg + (((int64_t)n * g.Ho + ho0) * g.Wo + wo0) * g.Co;
+#pragma unroll
+        for (int k = 0; k < XI; ++k) {
+            if (wave * 64 + 256 * k >= T::XNP) continue;
+            const int r = xy[k] >> 16, c = xy[k] & 0xFFFF;
+            const int q = (tid + 256 * k) % CI8;
+            const bool ok = (int)((unsigned)(h0 + r) < (unsigned)g.H) & (int)((unsigned)(w0 + c) < (unsigned)g.W) &
+                            (int)(256 * k + 255 < T::XN || tid + 256 * k < T::XN);
+            dma16(ok ? xb + (int64_t)(r * g.W + c) * g.C + q * 8 : zsrc, smem + (wave * 64 + 256 * k) * 8);
+        }
+#pragma unroll
+        for (int k = 0; k < DI; ++k) {
+            const int r = (tid + 256 * k) / (CO8 * kWgW), c = tid / CO8 % kWgW;
+            const bool ok = (int)(ho0 + r < g.Ho) & (int)(wo0 + c < g.Wo);
+            dma16(ok ? db + (int64_t)(r * g.Wo + c) * g.Co + (tid % CO8) * 8 : zsrc,
+                  smem + (T::XNP + wave * 64 + 256 * k) * 8);
+        }
+    };
+    f32x4 acc[9][ND][NB];
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    u32x4 xv[XI][XE], dv[DI][2];
-    auto load = [&](int64_t t) {
-        const int64_t n = t / per_img;
-        const int t_in = (int)(t - n * per_img);
-        const int ty = t_in / tiles_x, tx = t_in - ty * tiles_x;
-        const int ho0 = ty * TH, wo0 = tx * kWgW;
+        for (int d = 0; d < ND; ++d)
 #pragma unroll
-        for (int k = 0; k < XI; ++k) {
-            const int i = tid + 256 * k;
-            const int c8 = i % CI8, pr = i / CI8;
-            constexpr int XQ = S2 ? kWgQ2 : kWgXC / 2;
-            const int hy = pr / XQ, wx = XE * (pr - hy * XQ);
-            const int hi = (S2 ? 2 * ho0 : ho0) - 1 + hy;
-#pragma unroll
-            for (int e = 0; e < XE; ++e) {
-                const int wi = (S2 ? 2 * wo0 : wo0) - 1 + wx + e;
-                xv[k][e] = zero;
-                if (i < XN && hi >= 0 && wi >= 0 && hi < Hin && wi < Win) {
-                    const int hs = UP ? hi >> 1 : hi, ws = UP ? wi >> 1 : wi;
-                    xv[k][e] = *reinterpret_cast<const u32x4*>(xg + ((n * g.H + hs) * g.W + ws) * g.C + c8 * 8);
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < DI; ++k) {
-            const int i = tid + 256 * k;
-            const int c8 = i % CO8, pr = i / CO8;
-            const int r = pr / (kWgW / 2), c = 2 * (pr - r * (kWgW / 2));
-            const int ho = ho0 + r;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int wo = wo0 + c + e;
-                dv[k][e] = zero;
-                if (i < DN && ho < g.Ho && wo < g.Wo)
-                    dv[k][e] = *reinterpret_cast<const u32x4*>(dyg + ((n * g.Ho + ho) * g.Wo + wo) * g.Co + c8 * 8);
-            }
-        }
+            for (int b = 0; b < NB; ++b) acc[t][d][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // operand addresses (bf16 elements of a stage): lane i of a group reads pixel i / 4, channels 4 (i % 4)
+    const int r0 = wave * RW, pi = lr >> 2, pc = (lr & 3) * 4;
+    const int a_d = T::XNP * 8 + (r0 * kWgW + 8 * lk + pi) * CO + pc;
+    const int a_x = ((UP ? r0 / 2 : (S2 ? 2 * r0 : r0)) * XC + (UP ? 4 : (S2 ? 16 : 8)) * lk + (S2 ? 2 : 1) * pi) * CI + pc;
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    auto tr = [&](const uint16_t* p) __attribute__((always_inline)) -> uint2 {
+        return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                             (__attribute__((address_space(3))) s16x4*)p));
     };
-    // transpose into the channel planes: channel 2j of a pixel pair is the low halves of dword j,
-    // channel 2j + 1 the high halves (LDS positions do not depend on the tile)
-    auto store = [&]() {
+    constexpr int NXR = UP ? RW / 2 + 2 : (S2 ? 2 * RW + 1 : RW + 2);   // staged rows the wave's outputs read
+    constexpr int NR = UP ? 2 : (S2 ? 5 : 3);                           // reads per staged row and 16 channels
+    constexpr int P = (S2 ? 2 : 1) * CI;                                // elements between a lane's pixels
+    uint2 rd[RW][ND][2], rx[NXR][NB][NR];
+    auto read = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < XI; ++k) {
-            const int i = tid + 256 * k;
-            if (i < XN) {
-                const int c8 = i % CI8, pr = i / CI8;
-                constexpr int XQ = S2 ? kWgQ2 : kWgXC / 2;
-                const int hy = pr / XQ, q = pr - hy * XQ;
-                if constexpr (S2) {
-                    // columns 4q .. 4q + 3: even ones to half 0 at 2q, 2q + 1; odd ones to half 1
-                    uint32_t* d = reinterpret_cast<uint32_t*>(&sX[(c8 * 8) * XPL + hy * XROW + 2 * q]);
+        for (int rs = 0; rs < RW; ++rs)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        d[(2 * j) * (XPL / 2)] = __builtin_amdgcn_perm(xv[k][2][j], xv[k][0][j], 0x05040100u);
-                        d[(2 * j + 1) * (XPL / 2)] = __builtin_amdgcn_perm(xv[k][2][j], xv[k][0][j], 0x07060302u);
-                        d[(2 * j) * (XPL / 2) + kWgPitch / 2] =
-                            __builtin_amdgcn_perm(xv[k][3][j], xv[k][1][j], 0x05040100u);
-                        d[(2 * j + 1) * (XPL / 2) + kWgPitch / 2] =
-                            __builtin_amdgcn_perm(xv[k][3][j], xv[k][1][j], 0x07060302u);
-                    }
-                } else {
-                    uint32_t* d = reinterpret_cast<uint32_t*>(&sX[(c8 * 8) * XPL + hy * XROW + 2 * q]);
+            for (int d = 0; d < ND; ++d)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        d[(2 * j) * (XPL / 2)] = __builtin_amdgcn_perm(xv[k][1][j], xv[k][0][j], 0x05040100u);
-                        d[(2 * j + 1) * (XPL / 2)] = __builtin_amdgcn_perm(xv[k][1][j], xv[k][0][j], 0x07060302u);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < DI; ++k) {
-            const int i = tid + 256 * k;
-            if (i < DN) {
-                const int c8 = i % CO8, pr = i / CO8;
-                const int r = pr / (kWgW / 2), c = 2 * (pr - r * (kWgW / 2));
-                uint32_t* d = reinterpret_cast<uint32_t*>(&sD[(c8 * 8) * DPL + r * kWgPitch + c]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    d[(2 * j) * (DPL / 2)] = __builtin_amdgcn_perm(dv[k][1][j], dv[k][0][j], 0x05040100u);
-                    d[(2 * j + 1) * (DPL / 2)] = __builtin_amdgcn_perm(dv[k][1][j], dv[k][0][j], 0x07060302u);
-                }
-            }
-        }
-    };
-    const uint16_t* pa = &sD[(cbw * 16 + lr) * DPL + r0 * kWgPitch + 8 * lk];                // A: output row r0
-    const uint16_t* pbx = &sX[lr * XPL + (S2 ? 2 * r0 : r0) * XROW + 8 * lk];              // B: its first input row
-    if ((int64_t)blockIdx.x < total) load(blockIdx.x);
-    for (int64_t t = blockIdx.x; t < total; t += gridDim.x) {
-        __syncthreads();   // the previous tile's operands have been read
-        store();
-        __syncthreads();
-        if (t + gridDim.x < total) load(t + gridDim.x);
-        bf16x8 fa[RW];
-#pragma unroll
-        for (int rs = 0; rs < RW; ++rs) fa[rs] = *reinterpret_cast<const bf16x8*>(pa + rs * kWgPitch);
-        // staged row xr feeds output row r0 + rs through tap row xr - rs (stride 2: xr - 2 rs)
-        constexpr int NXR = S2 ? 2 * RW + 1 : RW + 2;
+                for (int m = 0; m < 2; ++m) rd[rs][d][m] = tr(smem + a_d + (rs * kWgW + 4 * m) * CO + d * 16);
 #pragma unroll
         for (int xr = 0; xr < NXR; ++xr)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                // stride 1: staged columns 8 lk .. 8 lk + 9 of the row give the three column shifts;
-                // stride 2: even columns 8 lk .. 8 lk + 8 and odd columns 8 lk .. 8 lk + 7
-                const uint16_t* src = pbx + nb * 16 * XPL + xr * XROW;
-                const u32x4 lo = *reinterpret_cast<const u32x4*>(src);
-                const uint32_t ex = *reinterpret_cast<const uint32_t*>(src + 8);
-                const u32x4 sft = {__builtin_amdgcn_alignbyte(lo[1], lo[0], 2u), __builtin_amdgcn_alignbyte(lo[2], lo[1], 2u),
-                                   __builtin_amdgcn_alignbyte(lo[3], lo[2], 2u), __builtin_amdgcn_alignbyte(ex, lo[3], 2u)};
-                u32x4 sh[3];
-                if constexpr (S2) {
-                    sh[0] = lo;
-                    sh[1] = *reinterpret_cast<const u32x4*>(src + kWgPitch);
-                    sh[2] = sft;
-                } else {
-                    sh[0] = lo;
-                    sh[1] = sft;
-                    sh[2] = u32x4{lo[1], lo[2], lo[3], ex};
-                }
+            for (int b = 0; b < NB; ++b) {
+                const uint16_t* p = smem + a_x + xr * XC * CI + b * 16;
 #pragma unroll
-                for (int dc = 0; dc < 3; ++dc) {
-                    const bf16x8 fb = __builtin_bit_cast(bf16x8, sh[dc]);
-#pragma unroll
-                    for (int rs = 0; rs < RW; ++rs) {
-                        const int dr = xr - (S2 ? 2 : 1) * rs;
-                        if (dr < 0 || dr > 2) continue;
-                        acc[3 * dr + dc][nb] =
-                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[rs], fb, acc[3 * dr + dc][nb], 0, 0, 0);
-                    }
-                }
+                for (int m = 0; m < NR; ++m) rx[xr][b][m] = tr(m < 3 ? p + 4 * m * P : p + CI + 4 * (m - 3) * P);
             }
-    }
-    // sum over the row groups, in wave order, in the [Co][3][3][Ci] layout: lane (lr, lk),
-    // element q is co = 16 cbw + 4 lk + q, ci = 16 nb + lr (waves below CB start their co group)
-    float* red = reinterpret_cast<float*>(smem);
-    for (int w = 0; w < 4; ++w) {
-        __syncthreads();
-        if (wave == w) {
+    };
+    auto multiply = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int tap = 0; tap < 9; ++tap)
+        for (int xr = 0; xr < NXR; ++xr)
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const int ci = nb * 16 + lr;
-                    if (ci >= CI) continue;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        float& r = red[((cbw * 16 + 4 * lk + q) * 9 + tap) * CI + ci];
-                        r = (w < CB ? 0.f : r) + acc[tap][nb][q];
+            for (int b = 0; b < NB; ++b) {
+                const uint2 u = rx[xr][b][0], v = rx[xr][b][1];
+                u32x4 sh[3];
+                if constexpr (UP) {
+                    // stored columns a(-1) .. a4 of the lane's fine columns 0 .. 7 (a0 a0 a1 a1 a2 a2 a3 a3)
+                    const uint32_t m = __builtin_amdgcn_alignbyte(u.y, u.x, 2u), q = __builtin_amdgcn_alignbyte(v.x, u.y, 2u);
+                    sh[0] = u32x4{u.x, m, u.y, q};
+                    sh[1] = u32x4{__builtin_amdgcn_perm(u.x, u.x, 0x07060706u), __builtin_amdgcn_perm(u.y, u.y, 0x05040504u),
+                                  __builtin_amdgcn_perm(u.y, u.y, 0x07060706u), __builtin_amdgcn_perm(v.x, v.x, 0x05040504u)};
+                    sh[2] = u32x4{m, u.y, q, v.x};
+                } else {
+                    const uint2 w = rx[xr][b][2];
+                    const u32x4 sft = {__builtin_amdgcn_alignbyte(u.y, u.x, 2u), __builtin_amdgcn_alignbyte(v.x, u.y, 2u),
+                                       __builtin_amdgcn_alignbyte(v.y, v.x, 2u), __builtin_amdgcn_alignbyte(w.x, v.y, 2u)};
+                    sh[0] = u32x4{u.x, u.y, v.x, v.y};
+                    if constexpr (S2) {
+                        sh[1] = u32x4{rx[xr][b][3].x, rx[xr][b][3].y, rx[xr][b][4].x, rx[xr][b][4].y};
+                        sh[2] = sft;
+                    } else {
+                        sh[1] = sft;
+                        sh[2] = u32x4{u.y, v.x, v.y, w.x};
                     }
                 }
-        }
+#pragma unroll
+                for (int dc = 0; dc < 3; ++dc)
+#pragma unroll
+                    for (int rs = 0; rs < RW; ++rs)
+#pragma unroll
+                        for (int dr = 0; dr < 3; ++dr) {
+                            // staged row (from the wave's first) of output row rs, tap row dr
+                            const int row = UP ? (rs + dr + 1) / 2 : (S2 ? 2 * rs + dr : rs + dr);
+                            if (row != xr) continue;
+#pragma unroll
+                            for (int d = 0; d < ND; ++d) {
+                                const u32x4 fa = {rd[rs][d][0].x, rd[rs][d][0].y, rd[rs][d][1].x, rd[rs][d][1].y};
+                                acc[3 * dr + dc][d][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8, fa), __builtin_bit_cast(bf16x8, sh[dc]),
+                                    acc[3 * dr + dc][d][b], 0, 0, 0);
+                            }
+                        }
+            }
+    };
+    // A stage is read after every wave's own DMA has landed (vmcnt) and the barrier; a wave takes its operands
+    // of the whole tile into registers, so after the next barrier the next tile is fetched into the same stage
+    // while this one is multiplied.  (With a second stage instead, the compiler waits for the fetch in flight
+    // before the first LDS read.)  The empty asm statements keep LDS accesses on their side of the barriers
+    auto barrier = [&]() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    if (blockIdx.x < total) issue(blockIdx.x);
+    for (uint32_t t = blockIdx.x; t < total; t += gridDim.x) {
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        barrier();
+        read();
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        barrier();
+        if (t + gridDim.x < total) issue(t + gridDim.x);
+        multiply();
     }
-    __syncthreads();
-    // the blocks with this blockIdx.x (one per channel-group pair) fill partial blockIdx.x of the whole dW
+    // sums of the four waves, in wave order: RC of the NA accumulator quads at a time pass through LDS, a
+    // quad as 16 bytes per lane (no bank conflicts); lane (lr, lk), element q is co = 16 d + 4 lk + q,
+    // ci = 16 b + lr.  The blocks with this blockIdx.x (one per channel-group pair) fill partial blockIdx.x
+    // of the whole dW
+    constexpr int RC = (int)(sizeof(smem) / 4096) < NA ? (int)(sizeof(smem) / 4096) : NA;
+    f32x4* red = reinterpret_cast<f32x4*>(smem);
     float* pb = part + (int64_t)blockIdx.x * ((int64_t)g.Co * 9 * g.C);
-    for (int i = tid; i < NW; i += 256) {
-        const int ci = i % CI, q = i / CI;   // q = co * 9 + tap
-        pb[((int64_t)(blockIdx.z * CO) * 9 + q) * g.C + blockIdx.y * CI + ci] = red[i];
+    const f32x4* fl = &acc[0][0][0];
+#pragma unroll
+    for (int c0 = 0; c0 < NA; c0 += RC) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < RC; ++j)
+            if (c0 + j < NA) red[(wave * RC + j) * 64 + lane] = fl[c0 + j];
+        __syncthreads();
+        for (int j = wave; j < RC && c0 + j < NA; j += 4) {
+            f32x4 v = red[j * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < 4; ++w) v += red[(w * RC + j) * 64 + lane];
+            const int id = c0 + j, b = id % NB, d = id / NB % ND, tap = id / (NB * ND);
+            const int ci = b * 16 + lr;
+            if (ci >= CI) continue;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                pb[((int64_t)(blockIdx.z * CO + d * 16 + 4 * lk + q) * 9 + tap) * g.C + blockIdx.y * CI + ci] = v[q];
+        }
     }
 }
 
@@ -2273,7 +2268,9 @@ bool wgrad_tile_plan(const ConvGeom& g, WgradTilePlan* plan)
     const bool s2 = g.stride == 2 && !g.up && g.Ho == (g.H - 1) / 2 + 1 && g.Wo == (g.W - 1) / 2 + 1;
     if (!(g.kh == 3 && g.kw == 3 && g.pad == 1 && (s1 || s2))) return false;
     int ci_g = 0, co_g = 0;
-    if (g.C == 8 || g.C == 16 || g.C == 24 || g.C == 32)
+    if (s2 && (g.C == 24 || g.C == 32 || (g.C % 32 == 0 && g.Wo >= 16)))
+        ci_g = g.C == 24 ? 8 : 16;   // (the staged halo of 32 channels needs more registers than there are)
+    else if (g.C == 8 || g.C == 16 || g.C == 24 || g.C == 32)
         ci_g = g.C;
     else if (g.C % 32 == 0 && g.Wo >= 16)   // wider layers in groups of 32 (tiles at least half full)
         ci_g = 32;
@@ -2287,7 +2284,8 @@ bool wgrad_tile_plan(const ConvGeom& g, WgradTilePlan* plan)
         const int th = g.stride == 2 ? kWgH2 : kWgH;
         const int64_t tiles = (g.Kw / ((int64_t)g.Ho * g.Wo)) * (int64_t)((g.Ho + th - 1) / th) *
                               ((g.Wo + kWgW - 1) / kWgW);
-        const int64_t want = std::max<int64_t>(1, (512 + gy * gz - 1) / (gy * gz));   // about 512 blocks
+        const int64_t fill = 256 * wgrad_blocks_per_cu(ci_g, co_g, g.stride == 1 && !g.up);   // every block resident at once
+        const int64_t want = std::max<int64_t>(1, (fill + gy * gz - 1) / (gy * gz));
         plan->gx = (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), want);
         plan->gy = gy;
         plan->gz = gz;
@@ -2303,31 +2301,31 @@ int64_t wgrad_tile_part_floats(const WgradTilePlan& p)
 }
 
 namespace {
-template <int CI, int CO, bool UP>
-hipError_t launch_wgrad_tile3(const ConvGeom& g, const uint16_t* x, const uint16_t* dy, float* part,
-                              const WgradTilePlan& p, hipStream_t s)
+template <int CI, int CO>
+hipError_t launch_wgrad_tile(const ConvGeom& g, const uint16_t* x, const uint16_t* dy, float* part,
+                             const WgradTilePlan& p, hipStream_t s)
 {
+    const dim3 grid(p.gx, p.gy, p.gz);
     if (g.stride == 2) {
-        if constexpr (UP) return hipErrorInvalidValue;
-        else
-            hipLaunchKernelGGL((k_wgrad3x3_tile<CI, CO, false, true>), dim3(p.gx, p.gy, p.gz), dim3(256), 0, s, g,
-                               x, dy, part);
+        if constexpr (CI > 16) return hipErrorInvalidValue;
+        else hipLaunchKernelGGL((k_wgrad3x3_tile<CI, CO, false, true>), grid, dim3(256), 0, s, g, x, dy, part);
+    } else if (g.up) {
+        hipLaunchKernelGGL((k_wgrad3x3_tile<CI, CO, true, false>), grid, dim3(256), 0, s, g, x, dy, part);
     } else {
-        hipLaunchKernelGGL((k_wgrad3x3_tile<CI, CO, UP, false>), dim3(p.gx, p.gy, p.gz), dim3(256), 0, s, g, x, dy,
-                           part);
+        hipLaunchKernelGGL((k_wgrad3x3_tile<CI, CO, false, false>), grid, dim3(256), 0, s, g, x, dy, part);
     }
     return hipGetLastError();
 }
 
-template <int CO, bool UP>
-hipError_t launch_wgrad_tile2(const ConvGeom& g, const uint16_t* x, const uint16_t* dy, float* part,
-                              const WgradTilePlan& p, hipStream_t s)
+template <int CO>
+hipError_t launch_wgrad_tile_co(const ConvGeom& g, const uint16_t* x, const uint16_t* dy, float* part,
+                                const WgradTilePlan& p, hipStream_t s)
 {
     switch (p.ci_g) {
-    case 8: return launch_wgrad_tile3<8, CO, UP>(g, x, dy, part, p, s);
-    case 16: return launch_wgrad_tile3<16, CO, UP>(g, x, dy, part, p, s);
-    case 24: return launch_wgrad_tile3<24, CO, UP>(g, x, dy, part, p, s);
-    case 32: return launch_wgrad_tile3<32, CO, UP>(g, x, dy, part, p, s);
+    case 8: return launch_wgrad_tile<8, CO>(g, x, dy, part, p, s);
+    case 16: return launch_wgrad_tile<16, CO>(g, x, dy, part, p, s);
+    case 24: return launch_wgrad_tile<24, CO>(g, x, dy, part, p, s);
+    case 32: return launch_wgrad_tile<32, CO>(g, x, dy, part, p, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -2340,11 +2338,8 @@ hipError_t wgrad_tile(const ConvGeom& g, const uint16_t* x, const uint16_t* dy, 
     if (!wgrad_tile_plan(g, &q) || q.gx != p.gx || q.gy != p.gy || q.gz != p.gz || q.ci_g != p.ci_g ||
         q.co_g != p.co_g)
         return hipErrorInvalidValue;
-    hipError_t e;
-    if (p.co_g == 16)
-        e = g.up ? launch_wgrad_tile2<16, true>(g, x, dy, part, p, s) : launch_wgrad_tile2<16, false>(g, x, dy, part, p, s);
-    else
-        e = g.up ? launch_wgrad_tile2<32, true>(g, x, dy, part, p, s) : launch_wgrad_tile2<32, false>(g, x, dy, part, p, s);
+    const hipError_t e = p.co_g == 16 ? launch_wgrad_tile_co<16>(g, x, dy, part, p, s)
+                                      : launch_wgrad_tile_co<32>(g, x, dy, part, p, s);
     if (e != hipSuccess) return e;
     return reduce_parts(part, (int64_t)g.Co * 9 * g.C, p.gx, dw, s);
 }

@@ -103,3 +103,17 @@ def test_stride_and_pointwise(sess, n, h, w, c, co, k, stride):
                                                 (2, 6, 5, 48, 40, 3, 2)])
 def test_upsampled_layers(sess, n, h, w, c, co, k, stride):
     _layer(sess, n, h, w, c, co, k, stride, up=1, seed=h)
+
+
+# the tiled weight gradient: every channel group, each way of reading the input, tiles of 8 (stride 2: 4)
+# x 32 output pixels cut at each side, more tiles than blocks (the last shapes)
+@pytest.mark.parametrize("c,co", [(8, 16), (16, 32), (24, 16), (24, 32), (32, 32), (64, 96), (96, 16)])
+@pytest.mark.parametrize("n,h,w,stride,up", [(2, 1, 17, 1, 0), (1, 9, 33, 1, 0), (3, 8, 64, 1, 0), (2, 17, 31, 2, 0), (1, 10, 67, 2, 0),
+                                            (1, 32, 66, 2, 0), (2, 1, 9, 1, 1), (1, 5, 17, 1, 1), (1, 12, 32, 1, 1)])
+def test_tiled_weight_gradient(sess, n, h, w, c, co, stride, up):
+    _layer(sess, n, h, w, c, co, 3, stride, up, seed=c + h)
+
+
+@pytest.mark.parametrize("n,h,w,c,co,stride,up", [(9, 67, 250, 16, 16, 1, 0), (70, 33, 65, 32, 32, 2, 0), (40, 18, 33, 32, 32, 1, 1)])
+def test_tiled_weight_gradient_many_tiles(sess, n, h, w, c, co, stride, up):
+    _layer(sess, n, h, w, c, co, 3, stride, up, seed=n)
