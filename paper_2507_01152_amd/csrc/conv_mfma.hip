@@ -1010,6 +1010,177 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
     }
 }
 
+// 3x3 convolution (stride 1, pad 1) of many channels: a block computes 16 x 16 output pixels of one image for
+// 64 output channels.  The im2col GEMM fetches every input pixel nine times from L2 (453 MB for 128 -> 64
+// channels on 131072 pixels, at 15 TB/s: that, not the matrix cores, bounds it); here the tile's input with its
+// halo is fetched once into LDS (all C channels; with UP the stored pixels, 10 x 10 of them) and only the
+// weights stream, 64 K of the 64 channels a step, through a three-stage ring of LDS DMA.  Eight waves of 64
+// pixels x 32 channels; K runs over taps and channels in the GEMM's order, so the results are its bits.  Bound by
+// LDS reads (six for eight products) and the steps' latency; 131072 pixels of 128 -> 64 upsampled 28.4 -> 23.5 us,
+// of 64 -> 64 22.6 -> 15.8 us.
+// The 16 rows of an MFMA operand are 2 x 8 pixels in 2 x 2 quads (row 4 q + 2 dy + dx): with UP four of them read
+// one or two stored pixels.
+constexpr int kHaloT = 16, kHaloN = 64, kHaloK = 64, kHaloThreads = 512;
+
+template <int C, bool UP>
+__global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, ConvArgs a)
+{
+    constexpr int XC = UP ? kHaloT / 2 + 2 : kHaloT + 2, C8 = C / 8;   // staged rows and columns
+    constexpr int NX = XC * XC * C8, NXP = (NX + 63) / 64 * 64;        // 16-byte chunks of the halo
+    constexpr int SW = kHaloN * kHaloK;                                // bf16 of a weight stage
+    constexpr int TP = kHaloN + 8;                                     // row of the output tile
+    constexpr int OPS = NXP * 8 + 3 * SW, OUT = kHaloT * kHaloT * TP;
+    static_assert(C % kHaloK == 0 && (kHaloN * kHaloK) / 8 == kHaloThreads, "one weight chunk per thread and step");
+    __shared__ __attribute__((aligned(16))) uint16_t smem[OPS > OUT ? OPS : OUT];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4, wm = wv >> 1, wn = wv & 1;
+    // blocks of one pixel tile (its channel groups) follow each other on one XCD
+    uint32_t b = blockIdx.x;
+    const uint32_t nblk = gridDim.x;
+    if ((nblk & 7) == 0) b = (b & 7) * (nblk >> 3) + (b >> 3);
+    const uint32_t ng = (uint32_t)g.Co / kHaloN;
+    const uint32_t tile = b / ng;
+    const int n_base = (int)(b - tile * ng) * kHaloN;
+    const int tiles_x = (g.Wo + kHaloT - 1) / kHaloT, tiles_y = (g.Ho + kHaloT - 1) / kHaloT;
+    const int n = (int)(tile / (uint32_t)(tiles_x * tiles_y)), t_in = (int)tile - n * tiles_x * tiles_y;
+    const int ho0 = t_in / tiles_x * kHaloT, wo0 = t_in % tiles_x * kHaloT;
+    const uint64_t zp = reinterpret_cast<uint64_t>(g_zero_buf);
+    const uint32_t zhi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(zp >> 32));
+    const uint32_t zlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)zp);
+    const uint16_t* zsrc = reinterpret_cast<const uint16_t*>(((uint64_t)zhi << 32) | zlo);
+    // chunk q of staged pixel (r, c) sits in slot q ^ key: the 2 x 8 pixels of an operand read then lie in 16
+    // distinct 16-byte groups of 256 bytes
+    auto key = [](int r, int c) { return C8 == 8 ? ((c >> 1) & 3) | ((r & 1) << 2) : (c & 7) | ((r & 1) << 3); };
+    const int h0 = (UP ? ho0 / 2 : ho0) - 1, w0 = (UP ? wo0 / 2 : wo0) - 1;
+    const uint16_t* xb = a.a + (((int64_t)n * g.H + h0) * g.W + w0) * C;
+#pragma unroll
+    for (int k = 0; k < (NXP + kHaloThreads - 1) / kHaloThreads; ++k) {
+        if ((k + 1) * kHaloThreads > NXP && wv * 64 + k * kHaloThreads >= NXP) continue;
+        const int i = tid + k * kHaloThreads, px = i / C8, r = px / XC, c = px - r * XC;
+        const int q = (i % C8) ^ key(r, c);
+        const bool ok = (int)(i < NX) & (int)((unsigned)(h0 + r) < (unsigned)g.H) & (int)((unsigned)(w0 + c) < (unsigned)g.W);
+        dma16(ok ? xb + (int64_t)(r * g.W + c) * C + q * 8 : zsrc, smem + (wv * 64 + k * kHaloThreads) * 8);
+    }
+    // weight stage: row tid / 8 (output channel), chunk q in slot q ^ (row / 2 % 8)
+    const uint16_t* wsrc = a.b + (int64_t)(n_base + (tid >> 3)) * g.kb + ((tid & 7) ^ ((tid >> 4) & 7)) * 8;
+    uint16_t* sW = smem + NXP * 8;
+    auto issue = [&](int kt, int st) __attribute__((always_inline)) { dma16(wsrc + kt * kHaloK, sW + st * SW + wv * 512); };
+    float bias_r[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) bias_r[j] = a.bias ? a.bias[n_base + wn * 32 + j * 16 + lr] : 0.f;
+    f32x4 acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // row tile i of the wave: output rows 4 wm + 2 (i / 2) + rb, columns 8 (i % 2) + cl
+    const int rb = (lr >> 1) & 1, cl = 2 * (lr >> 2) + (lr & 1);
+    const uint16_t* wrow = sW + (wn * 32 + lr) * kHaloK;
+    constexpr int NK = 9 * C / kHaloK, KT = C / kHaloK;   // steps, and steps per tap
+    issue(0, 0);
+    issue(1, 1);
+    int st = 0, st2 = 2, kt = 0;
+#pragma unroll 1
+    for (int t = 0; t < 9; ++t) {
+        const int r = t / 3, s = t % 3;
+        // staged pixel of row tile 0 and its key; those of the others follow (i % 2: 8 columns on, UP 4; i / 2: 2
+        // rows on, UP 1)
+        const int sr = UP ? 2 * wm + ((rb + r + 1) >> 1) : 4 * wm + rb + r;
+        const int sc = UP ? (cl + s + 1) >> 1 : cl + s;
+        const int kx = key(sr, sc) ^ lk;
+        const uint16_t* xrow = smem + (sr * XC + sc) * C;
+#pragma unroll
+        for (int kc = 0; kc < KT; ++kc, ++kt) {
+            if (kt + 1 < NK) __builtin_amdgcn_s_waitcnt(kWaitVm0 | 1);   // this step's stage (and the halo) has landed
+            else __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (kt + 2 < NK) issue(kt + 2, st2);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                bf16x8 fa[4], fb[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    fb[j] = *reinterpret_cast<const bf16x8*>(wrow + st * SW + j * 16 * kHaloK + (((u * 4 + lk) ^ (lr >> 1)) * 8));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    constexpr int B8 = C8 == 8 ? 1 : 2;   // key bit of column bit 2 (UP)
+                    const int ko = UP ? ((i & 1) << B8) ^ ((i >> 1) << (B8 + 1)) : 0;
+                    fa[i] = *reinterpret_cast<const bf16x8*>(xrow + ((i >> 1) * (UP ? 1 : 2) * XC + (i & 1) * (UP ? 4 : 8)) * C +
+                                                             ((kx ^ ko ^ ((kc * 2 + u) * 4)) * 8));
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+            }
+            st = st == 2 ? 0 : st + 1;
+            st2 = st2 == 2 ? 0 : st2 + 1;
+        }
+    }
+    // lane (lr, lk), element e of acc[i][j]: output pixel (4 wm + 2 (i / 2) + e / 2, 8 (i % 2) + 2 lk + e % 2),
+    // channel n_base + 32 wn + 16 j + lr
+    uint16_t* sT = smem;
+    __syncthreads();
+    auto write_tile = [&](auto act_c) __attribute__((always_inline)) {
+        constexpr int ACT = decltype(act_c)::value;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int co = wn * 32 + j * 16 + lr;
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    const int rr = 4 * wm + 2 * (i >> 1) + (e >> 1), cc = 8 * (i & 1) + 2 * lk;
+                    const float y0 = activate_c<ACT>(acc[i][j][e] + bias_r[j]);
+                    const float y1 = activate_c<ACT>(acc[i][j][e + 1] + bias_r[j]);
+                    const uint32_t pk = pack_bf16x2(y0, y1);
+                    sT[(rr * kHaloT + cc) * TP + co] = (uint16_t)pk;
+                    sT[(rr * kHaloT + cc + 1) * TP + co] = (uint16_t)(pk >> 16);
+                    if (a.out_f32) {
+                        const int ho = ho0 + rr, wo = wo0 + cc;
+                        float* o = a.out_f32 + (((int64_t)n * g.Ho + ho) * g.Wo + wo) * g.Co + n_base + co;
+                        if (ho < g.Ho && wo < g.Wo) o[0] = y0;
+                        if (ho < g.Ho && wo + 1 < g.Wo) o[g.Co] = y1;
+                    }
+                }
+            }
+    };
+    if (a.relu == 1) write_tile(std::integral_constant<int, 1>{});
+    else if (a.relu == 2) write_tile(std::integral_constant<int, 2>{});
+    else write_tile(std::integral_constant<int, 0>{});
+    __syncthreads();
+    // 16-byte chunks; the skip tensor's are all loaded before the first store (a load after a store waits)
+    constexpr int CPT = kHaloT * kHaloT * kHaloN / 8 / kHaloThreads;
+    const int ld2 = a.ld_out2 ? a.ld_out2 : g.Co;
+    const bool skip = a.skip && a.out2_bf16;
+    const int c8 = tid % (kHaloN / 8) * 8;
+    u32x4 kv[CPT];
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        const int px = (tid + u * kHaloThreads) / (kHaloN / 8), ho = ho0 + px / kHaloT, wo = wo0 + px % kHaloT;
+        kv[u] = u32x4{0u, 0u, 0u, 0u};
+        if (skip && ho < g.Ho && wo < g.Wo)
+            kv[u] = *reinterpret_cast<const u32x4*>(a.skip + (((int64_t)n * g.Ho + ho) * g.Wo + wo) * g.Co + n_base + c8);
+    }
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        const int px = (tid + u * kHaloThreads) / (kHaloN / 8), ho = ho0 + px / kHaloT, wo = wo0 + px % kHaloT;
+        if (ho >= g.Ho || wo >= g.Wo) continue;
+        const int64_t op = ((int64_t)n * g.Ho + ho) * g.Wo + wo;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(&sT[px * TP + c8]);
+        if (a.out_bf16) *reinterpret_cast<u32x4*>(a.out_bf16 + op * g.Co + n_base + c8) = v;
+        if (skip) {
+            u32x4 o;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = add_bf16x2(v[q], kv[u][q]);
+            *reinterpret_cast<u32x4*>(a.out2_bf16 + op * ld2 + n_base + c8) = o;
+        }
+    }
+}
+
 // Direct 3x3 weight gradient (pad 1; stride 1, or 2 with S2): dW[co][r][s][ci] = sum over
 // output pixels p of dy[p][co] x[p + (r - 1, s - 1)][ci], for a group of CI in
 // {8, 16, 24, 32} input and CO in {16, 32} output channels (block y: input
@@ -2222,6 +2393,42 @@ hipError_t dgrad_parity(const ConvGeom& g, const uint16_t* dy, const uint16_t* w
     return conv_gemm(kDgrad, c, a, 1, s);
 }
 
+namespace {
+int64_t halo_blocks(const ConvGeom& g)
+{
+    return (int64_t)((g.Ho + kHaloT - 1) / kHaloT) * ((g.Wo + kHaloT - 1) / kHaloT) *
+           (g.Kw / ((int64_t)g.Ho * g.Wo)) * (g.Co / kHaloN);   // Kw = N * Ho * Wo
+}
+
+// The halo kernel's layers.  Its blocks are large: below one per compute unit the GEMM's smaller tiles are as fast
+// (128 -> 64 upsampled, 128 blocks 13.4 against 12.9 us, 256 blocks 15.0 against 18.0, 4096 blocks 164 against 214).
+// 128 channels not upsampled take 107 KB of LDS, one block per compute unit: with many blocks the GEMM's 128 x 128
+// tiles are faster again (128 -> 128, 256 blocks 15.0 against 18.4 us, 512 28.2 against 30.0, 2048 106 against 102).
+bool halo_supported(const ConvGeom& g)
+{
+    const bool shape = g.kh == 3 && g.kw == 3 && g.stride == 1 && g.pad == 1 && g.Co % kHaloN == 0 &&
+                       g.Ho == (g.up ? 2 * g.H : g.H) && g.Wo == (g.up ? 2 * g.W : g.W);
+    if (!shape || g.Wo < kHaloT || g.Ho < kHaloT || !(g.C == 64 || g.C == 128 || (g.C == 256 && g.up))) return false;
+    const int64_t blocks = halo_blocks(g);
+    return blocks >= 256 && !(g.C == 128 && !g.up && blocks >= 1024);
+}
+
+template <bool UP>
+hipError_t launch_halo(const ConvGeom& g, const ConvArgs& a, hipStream_t s)
+{
+    const int64_t blocks = halo_blocks(g);
+    if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    const dim3 gr((unsigned)blocks), bl(kHaloThreads);
+    if (g.C == 64) hipLaunchKernelGGL((k_conv3x3_halo<64, UP>), gr, bl, 0, s, g, a);
+    else if (g.C == 128) hipLaunchKernelGGL((k_conv3x3_halo<128, UP>), gr, bl, 0, s, g, a);
+    else {
+        if constexpr (UP) hipLaunchKernelGGL((k_conv3x3_halo<256, UP>), gr, bl, 0, s, g, a);
+        else return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits, hipStream_t s)
 {
     if (a.head_out && (mode != kFwd || !conv_tile_supported(g) || g.Co != 16 || !a.head_w || !a.head_b))
@@ -2231,6 +2438,8 @@ hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits,
         return hipErrorInvalidValue;
     if (mode == kFwd && conv_tile_supported(g))
         return g.Co == 16 ? launch_tile_co<16>(g, a, s) : launch_tile_co<32>(g, a, s);
+    if (mode == kFwd && halo_supported(g))
+        return g.up ? launch_halo<true>(g, a, s) : launch_halo<false>(g, a, s);
     if (mode == kWgrad) {
         if (g.M <= 16) return launch_gemm<kWgrad, 16, 128, 1, 4>(g, a, splits, s);
         if (g.M <= 32) return launch_gemm<kWgrad, 32, 128, 1, 4>(g, a, splits, s);

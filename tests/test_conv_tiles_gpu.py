@@ -117,3 +117,13 @@ def test_tiled_weight_gradient(sess, n, h, w, c, co, stride, up):
 @pytest.mark.parametrize("n,h,w,c,co,stride,up", [(9, 67, 250, 16, 16, 1, 0), (70, 33, 65, 32, 32, 2, 0), (40, 18, 33, 32, 32, 1, 1)])
 def test_tiled_weight_gradient_many_tiles(sess, n, h, w, c, co, stride, up):
     _layer(sess, n, h, w, c, co, 3, stride, up, seed=n)
+
+
+# 64 and more channels with the input tile and its halo in LDS (from 256 blocks of 16 x 16 pixels x 64
+# channels on): tiles cut at each side, several channel groups, upsampled inputs (the stored halo), and the
+# shapes next to the rule's lines
+@pytest.mark.parametrize("n,h,w,c,co,up", [(64, 17, 31, 64, 64, 0), (32, 33, 18, 64, 128, 0), (65, 18, 16, 128, 128, 0),
+                                          (256, 16, 16, 128, 64, 0), (255, 16, 16, 64, 64, 0), (1030, 16, 16, 128, 64, 0),
+                                          (256, 8, 8, 64, 64, 1), (33, 17, 13, 128, 64, 1), (70, 9, 9, 256, 64, 1), (64, 8, 16, 256, 128, 1)])
+def test_halo_layers(sess, n, h, w, c, co, up):
+    _layer(sess, n, h, w, c, co, up=up, seed=h + w)
