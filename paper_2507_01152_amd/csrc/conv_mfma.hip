@@ -1181,6 +1181,240 @@ __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, Co
     }
 }
 
+// Two 3x3 convolutions (stride 1, pad 1, ReLU) in one pass, for inference, where nothing reads the tensor between
+// them: the first (C -> CM channels; UP: its input read upsampled x2, its output added to skip) and the second
+// ((CM + EX) -> CO; EX further input channels come from extra).  These layers are bound by memory, and the tensor
+// between is written and read once per pass otherwise (64 to 96 bytes a pixel).  A block stages the first input's
+// tile with a halo of two pixels and both weights (DMA), computes the 18 x 34 pixels of the tensor between that
+// its 16 x 32 outputs need into LDS (bf16, zero outside the image, the second conv's padding) and continues from
+// there; the halo costs a fifth of the first conv again.  K order and roundings are k_conv3x3_tile's: same bits.
+// 41943040 pixels, 8 -> 16 -> 16 channels: 333 + 453 us as two passes, 549 us here; 32 upsampled -> 16 (+ 8) -> 16
+// and the head: 759 + 545 and 54 us for the clamp, 1140 us here (LDS reads bound it now: a 16-channel product
+// needs one read each).  64 upsampled -> 32 -> 32 on a quarter of the pixels takes 131 KB of LDS, one block per
+// compute unit, and is slower (893 against 386 + 266 us), so those stay apart.
+template <int C, bool UP, int CM, int EX, int CO>
+__global__ __launch_bounds__(512, 4) void k_conv3x3_pair(PairArgs a)
+{
+    constexpr int TH = 16, TW = 32, NT = 512, IW = TW + 2, NP = (TH + 2) * IW;   // NP: pixels between
+    constexpr int HP = UP ? TH / 2 + 2 : TH + 4, WP = UP ? TW / 2 + 2 : TW + 4;  // staged input pixels
+    constexpr int C8 = C / 8, PS = C8 % 2 == 0 ? C + 8 : C, K8 = 9 * C8, NKS = (K8 + 3) / 4, KP = NKS * 32 + 8;
+    constexpr int CT = CM + EX, T8 = CT / 8, PT = T8 % 2 == 0 ? CT + 8 : CT, L8 = 9 * T8, NLS = (L8 + 3) / 4,
+                  LP = NLS * 32 + 8;
+    constexpr int FM = CM / 16, FO = CO / 16, NF = (NP + 127) / 128;   // NF: row tiles of a wave in the first conv
+    constexpr int SPP = PS / 8, KPS = KP / 8, LPS = LP / 8;
+    constexpr int NXS = HP * WP * SPP, NWS = CM * KPS, NVS = CO * LPS;   // 16-byte slots
+    constexpr int XS = (NXS + 63) / 64 * 512, WS = (NWS + 63) / 64 * 512, VS = (NVS + 63) / 64 * 512;
+    constexpr int OS = TH * TW * CO;
+    __shared__ __attribute__((aligned(16))) uint16_t sX[XS + WS > OS ? XS + WS : OS];   // input, weights; then output
+    __shared__ __attribute__((aligned(16))) uint16_t sV[VS];
+    __shared__ __attribute__((aligned(16))) uint16_t sT[NP * PT];
+    uint16_t* sW = sX + XS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lr = lane & 15, lk = lane >> 4;
+    const int Ho = a.H, Wo = a.W, Hs = UP ? Ho >> 1 : Ho, Ws = UP ? Wo >> 1 : Wo;
+    const int tiles_x = (Wo + TW - 1) / TW, tiles_y = (Ho + TH - 1) / TH;
+    uint32_t b = blockIdx.x;   // neighbouring tiles on the same XCD
+    const uint32_t nb = gridDim.x;
+    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+    const int n = (int)(b / (uint32_t)(tiles_x * tiles_y)), t_in = (int)b - n * tiles_x * tiles_y;
+    const int ho0 = t_in / tiles_x * TH, wo0 = t_in % tiles_x * TW;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    float bias1[FM], bias2[FO];
+#pragma unroll
+    for (int j = 0; j < FM; ++j) bias1[j] = a.b1[16 * j + lr];
+#pragma unroll
+    for (int j = 0; j < FO; ++j) bias2[j] = a.b2[16 * j + lr];
+    const uint64_t zp = reinterpret_cast<uint64_t>(g_zero_buf);
+    const uint32_t zhi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(zp >> 32));
+    const uint32_t zlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)zp);
+    const uint16_t* zsrc = reinterpret_cast<const uint16_t*>(((uint64_t)zhi << 32) | zlo);
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int h0 = UP ? ho0 / 2 - 1 : ho0 - 2, w0 = UP ? wo0 / 2 - 1 : wo0 - 2;
+#pragma unroll
+    for (int u = 0; u < (NXS + NT - 1) / NT; ++u) {
+        const int base = wv * 64 + NT * u, j = base + lane;
+        const int pix = j / SPP, c8 = j - pix * SPP, hy = pix / WP, wx = pix - hy * WP;
+        const bool ok = (int)(j < NXS) & (int)(c8 < C8) & (int)((unsigned)(h0 + hy) < (unsigned)Hs) &
+                        (int)((unsigned)(w0 + wx) < (unsigned)Ws);
+        const int64_t off = (((int64_t)n * Hs + h0 + hy) * Ws + w0 + wx) * C + c8 * 8;
+        if (base < NXS) dma16(ok ? a.x + off : zsrc, &sX[base * 8]);
+    }
+    auto weights = [&](const uint16_t* w, uint16_t* dst, auto slots_c, auto row_c, auto k8_c) __attribute__((always_inline)) {
+        constexpr int SL = decltype(slots_c)::value, RS = decltype(row_c)::value, KK = decltype(k8_c)::value;
+#pragma unroll
+        for (int u = 0; u < (SL + NT - 1) / NT; ++u) {
+            const int base = wv * 64 + NT * u, j = base + lane, co = j / RS, k8 = j - co * RS;
+            const bool ok = (int)(j < SL) & (int)(k8 < KK);
+            if (base < SL) dma16(ok ? w + (int64_t)co * (8 * KK) + k8 * 8 : zsrc, dst + base * 8);
+        }
+    };
+    weights(a.w1, sW, std::integral_constant<int, NWS>{}, std::integral_constant<int, KPS>{}, std::integral_constant<int, K8>{});
+    weights(a.w2, sV, std::integral_constant<int, NVS>{}, std::integral_constant<int, LPS>{}, std::integral_constant<int, L8>{});
+    // chunks of the tensor between that this thread completes (skip and extra, zero outside the image), their
+    // loads in flight with the DMA; pixel p of it is (ho0 - 1 + p / IW, wo0 - 1 + p % IW)
+    constexpr int M8 = CM / 8, SI = (NP * M8 + NT - 1) / NT, EI = EX ? (NP * (EX / 8) + NT - 1) / NT : 0;
+    static_assert(EX == 0 || EX == 8, "one further chunk per pixel");
+    auto inside = [&](int p, int64_t& px) __attribute__((always_inline)) -> bool {
+        const int h = ho0 - 1 + p / IW, w = wo0 - 1 + p % IW;
+        px = ((int64_t)n * Ho + h) * Wo + w;
+        return (int)(p < NP) & (int)((unsigned)h < (unsigned)Ho) & (int)((unsigned)w < (unsigned)Wo);
+    };
+    u32x4 kv[UP ? SI : 1], ev[EX ? EI : 1];
+    if constexpr (UP) {
+#pragma unroll
+        for (int u = 0; u < SI; ++u) {
+            const int i = tid + NT * u;
+            int64_t px;
+            kv[u] = inside(i / M8, px) ? *reinterpret_cast<const u32x4*>(a.skip + px * CM + i % M8 * 8) : zero;
+        }
+    }
+    if constexpr (EX) {
+#pragma unroll
+        for (int u = 0; u < EI; ++u) {
+            int64_t px;
+            ev[u] = inside(tid + NT * u, px) ? *reinterpret_cast<const u32x4*>(a.extra + px * EX) : zero;
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __syncthreads();
+    // first conv: wave w takes the row tiles w, w + 8, ... of 16 consecutive pixels between
+    {
+        f32x4 acc[NF][FM];
+        int pr[NF], pc[NF];   // row and column of this lane's pixel (past the last: the last)
+#pragma unroll
+        for (int i = 0; i < NF; ++i) {
+            const int p = min((wave + 8 * i) * 16 + lr, NP - 1);
+            pr[i] = p / IW;
+            pc[i] = p - pr[i] * IW;
+#pragma unroll
+            for (int j = 0; j < FM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll 3
+        for (int ks = 0; ks < NKS; ++ks) {
+            const int k8 = ks * 4 + lk;
+            int r = 0, s = 0, c0 = 0;
+            if (k8 < K8) {   // beyond K the weights are zero; read tap 0
+                const int tap = k8 / C8;
+                c0 = (k8 - tap * C8) * 8;
+                r = tap / 3;
+                s = tap - r * 3;
+            }
+            bf16x8 fb[FM];
+#pragma unroll
+            for (int j = 0; j < FM; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(&sW[(16 * j + lr) * KP + k8 * 8]);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) {
+                const int q = UP ? ((pr[i] + r) >> 1) * WP + ((pc[i] + s) >> 1) : (pr[i] + r) * WP + pc[i] + s;
+                const bf16x8 fa = *reinterpret_cast<const bf16x8*>(&sX[q * PS + c0]);
+#pragma unroll
+                for (int j = 0; j < FM; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb[j], acc[i][j], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; q += 2) {
+                    const int p = (wave + 8 * i) * 16 + 4 * lk + q;
+                    const uint32_t pk = pack_bf16x2(fmaxf(acc[i][j][q] + bias1[j], 0.f), fmaxf(acc[i][j][q + 1] + bias1[j], 0.f));
+                    if (p < NP) {   // NP is even
+                        sT[p * PT + 16 * j + lr] = (uint16_t)pk;
+                        sT[(p + 1) * PT + 16 * j + lr] = (uint16_t)(pk >> 16);
+                    }
+                }
+    }
+    static_assert(NP % 2 == 0, "pairs of pixels");
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < SI; ++u) {
+        const int i = tid + NT * u, p = i / M8;
+        int64_t px;
+        const bool in = inside(p, px);
+        if (p >= NP || (!UP && in)) continue;
+        u32x4* t = reinterpret_cast<u32x4*>(&sT[p * PT + i % M8 * 8]);
+        u32x4 o = zero;
+        if constexpr (UP) {
+            if (in) {
+                const u32x4 v = *t;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) o[q] = add_bf16x2(v[q], kv[u][q]);
+            }
+        }
+        *t = o;
+    }
+    if constexpr (EX) {
+#pragma unroll
+        for (int u = 0; u < EI; ++u)
+            if (tid + NT * u < NP) *reinterpret_cast<u32x4*>(&sT[(tid + NT * u) * PT + CM]) = ev[u];
+    }
+    __syncthreads();
+    // second conv, as k_conv3x3_tile from its staged halo tile
+    f32x4 acc[4][FO];
+#pragma unroll
+    for (int gi = 0; gi < 4; ++gi)
+#pragma unroll
+        for (int j = 0; j < FO; ++j) acc[gi][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 3
+    for (int ks = 0; ks < NLS; ++ks) {
+        const int k8 = ks * 4 + lk;
+        int tofs = 0;
+        if (k8 < L8) {
+            const int tap = k8 / T8, r = tap / 3;
+            tofs = (r * IW + tap - r * 3) * PT + (k8 - tap * T8) * 8;
+        }
+        bf16x8 fb[FO];
+#pragma unroll
+        for (int j = 0; j < FO; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(&sV[(16 * j + lr) * LP + k8 * 8]);
+#pragma unroll
+        for (int gi = 0; gi < 4; ++gi) {
+            const bf16x8 fa = *reinterpret_cast<const bf16x8*>(
+                &sT[((2 * wave + (gi >> 1)) * IW + (gi & 1) * 16 + lr) * PT + tofs]);
+#pragma unroll
+            for (int j = 0; j < FO; ++j)
+                acc[gi][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb[j], acc[gi][j], 0, 0, 0);
+        }
+    }
+    uint16_t* sO = sX;   // [TH * TW][CO] (the input and its weights were last read before the barriers above)
+#pragma unroll
+    for (int gi = 0; gi < 4; ++gi)
+#pragma unroll
+        for (int j = 0; j < FO; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+                const int o = ((2 * wave + (gi >> 1)) * TW + (gi & 1) * 16 + 4 * lk + q) * CO + 16 * j + lr;
+                const uint32_t pk = pack_bf16x2(fmaxf(acc[gi][j][q] + bias2[j], 0.f), fmaxf(acc[gi][j][q + 1] + bias2[j], 0.f));
+                sO[o] = (uint16_t)pk;
+                sO[o + CO] = (uint16_t)(pk >> 16);
+            }
+    __syncthreads();
+    if (a.out) {
+        constexpr int O8 = CO / 8;
+#pragma unroll
+        for (int u = 0; u < O8; ++u) {
+            const int i = tid + NT * u, pix = i / O8, ho = ho0 + pix / TW, wo = wo0 + pix % TW;
+            if (ho < Ho && wo < Wo)
+                *reinterpret_cast<u32x4*>(a.out + (((int64_t)n * Ho + ho) * Wo + wo) * CO + i % O8 * 8) =
+                    *reinterpret_cast<const u32x4*>(&sO[pix * CO + i % O8 * 8]);
+        }
+    }
+    if constexpr (CO == 16) {
+        if (a.head_out) {   // the 1x1 head with one output, clamped to [0, 1]
+            const int ho = ho0 + tid / TW, wo = wo0 + tid % TW;
+            if (ho < Ho && wo < Wo) {
+                float sum = 0.f;
+#pragma unroll
+                for (int co = 0; co < CO; ++co) sum += bf2f(a.head_w[co]) * bf2f(sO[tid * CO + co]);
+                const float y = fminf(fmaxf(sum + a.head_b[0], 0.f), 1.f);
+                const int64_t px = ((int64_t)n * Ho + ho) * Wo + wo;
+                a.head_out[px] = y;
+                if (a.head_bf16) a.head_bf16[px] = f2bf(y);
+            }
+        }
+    }
+}
+
 // Direct 3x3 weight gradient (pad 1; stride 1, or 2 with S2): dW[co][r][s][ci] = sum over
 // output pixels p of dy[p][co] x[p + (r - 1, s - 1)][ci], for a group of CI in
 // {8, 16, 24, 32} input and CO in {16, 32} output channels (block y: input
@@ -2221,12 +2455,6 @@ __global__ void k_psnr_idx(const float* yhat, const float* y, const int32_t* idx
     }
 }
 
-__global__ void k_clamp01(const float* x, float* y, int64_t n)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = fminf(fmaxf(x[i], 0.f), 1.f);
-}
-
 int64_t grid_for(int64_t n, int64_t per = 256)
 {
     int64_t b = (n + per - 1) / per;
@@ -2307,6 +2535,21 @@ hipError_t launch_tile_co(const ConvGeom& g, const ConvArgs& a, hipStream_t s)
     case 24: return launch_tile<24, CO, false>(g, a, s);
     default: return launch_tile<32, CO, false>(g, a, s);
     }
+}
+
+hipError_t conv_pair(int C, int up, int CM, int EX, int CO, const PairArgs& a, hipStream_t s)
+{
+    const int64_t blocks = (int64_t)a.N * ((a.H + 15) / 16) * ((a.W + 31) / 32);
+    if (blocks < 1 || blocks > 0x7FFFFFFFll || !a.out == !a.head_out || (up && (a.H % 2 || a.W % 2)))
+        return hipErrorInvalidValue;
+    const dim3 gr((unsigned)blocks), bl(512);
+    if (C == 8 && !up && CM == 16 && EX == 0 && CO == 16)
+        hipLaunchKernelGGL((k_conv3x3_pair<8, false, 16, 0, 16>), gr, bl, 0, s, a);
+    else if (C == 32 && up && CM == 16 && EX == 8 && CO == 16)
+        hipLaunchKernelGGL((k_conv3x3_pair<32, true, 16, 8, 16>), gr, bl, 0, s, a);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 bool dgrad_tile_supported(const ConvGeom& g)
@@ -2740,12 +2983,6 @@ hipError_t psnr_indexed(const float* yhat, const float* y, const int32_t* idx, i
 {
     if (n_frames <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_psnr_idx, dim3(n_frames), dim3(256), 0, s, yhat, y, idx, frame, psnr);
-    return hipGetLastError();
-}
-
-hipError_t clamp01(const float* x, float* y, int64_t n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_clamp01, dim3((unsigned)grid_for(n)), dim3(256), 0, s, x, y, n);
     return hipGetLastError();
 }
 

@@ -297,8 +297,79 @@ sg_status refresh_bf16(sg_ctx* c, Surrogate& s)
                  "bf16 head");
 }
 
-// train: also keep the pre-skip outputs of the decoder layers (ReLU masks of the backward)
-sg_status forward(sg_ctx* c, Surrogate& s, int n, bool train)
+// inference: layers L and L + 1 in one pass (the tensor between them is not stored); the pair with the last
+// layer writes the clamped frames, FP32 and, unless null, bf16
+sg_status forward_pair(sg_ctx* c, Surrogate& s, int L, int n, float* frames, uint16_t* frames_bf16)
+{
+    const LayerDef &d = kLayers[L], &e = kLayers[L + 1];
+    const int lv = kTL[d.out];
+    PairArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.N = n;
+    a.H = s.H >> lv;
+    a.W = s.W >> lv;
+    a.x = (const uint16_t*)s.act[d.in].p;
+    a.w1 = (const uint16_t*)s.wb.p + s.w_off[L];
+    a.b1 = (const float*)s.master.p + s.b_off[L];
+    if (d.skip >= 0) a.skip = (const uint16_t*)s.act[d.skip].p;
+    if (d.out2 == kScanDst) a.extra = (const uint16_t*)s.act[kScanTmp].p;
+    a.w2 = (const uint16_t*)s.wb.p + s.w_off[L + 1];
+    a.b2 = (const float*)s.master.p + s.b_off[L + 1];
+    if (L + 1 == kNumL - 1) {
+        a.head_w = (const uint16_t*)s.wb.p + s.head_w;
+        a.head_b = (const float*)s.master.p + s.head_b;
+        a.head_out = frames;
+        a.head_bf16 = frames_bf16;
+    } else {
+        a.out = (uint16_t*)s.act[e.out].p;
+    }
+    return check(conv_pair(d.Ci, d.up, d.Co, e.Ci - d.Co, e.Co, a, c->stream), "forward convs");
+}
+
+// the layers of inference that take one pass with the next one
+bool starts_pair(int L) { return kLayers[L].out == T1 || kLayers[L].out == U0; }
+
+// the 1x1 map of E0 and its depth integral (dense, joined to S0 later)
+sg_status forward_scan(sg_ctx* c, Surrogate& s, int n)
+{
+    return check(depth_map_scan_fwd((const uint16_t*)s.act[kScanSrc].p, (const uint16_t*)s.wb.p + s.proj_w,
+                                    (const float*)s.master.p + s.proj_b, (uint16_t*)s.act[kScanTmp].p, n, s.H, s.W,
+                                    kScanScale, kScanC, 0, c->stream),
+                 "depth integral");
+}
+
+// inference: the clamped frames, FP32 and, unless null, bf16
+sg_status forward_frames(sg_ctx* c, Surrogate& s, int n, float* frames, uint16_t* frames_bf16)
+{
+    for (int L = 0; L < kNumL; ++L) {
+        int last = L;
+        if (starts_pair(L)) {
+            SG_TRY(forward_pair(c, s, L, n, frames, frames_bf16));
+            last = ++L;
+        } else {
+            const LayerDef& d = kLayers[L];
+            ConvArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.a = (const uint16_t*)s.act[d.in].p;
+            a.b = (const uint16_t*)s.wb.p + s.w_off[L];
+            a.bias = (const float*)s.master.p + s.b_off[L];
+            a.relu = 1;
+            if (d.skip >= 0) {   // the output itself is read by the backward only
+                a.skip = (const uint16_t*)s.act[d.skip].p;
+                a.out2_bf16 = (uint16_t*)s.act[d.out2].p;
+                a.ld_out2 = kTC[d.out2];
+            } else {
+                a.out_bf16 = (uint16_t*)s.act[d.out].p;
+            }
+            SG_TRY(check(conv_gemm(0, geom_of(layer_shape(s, L, n), 0), a, 1, c->stream), "forward conv"));
+        }
+        if (kLayers[last].out == kScanSrc) SG_TRY(forward_scan(c, s, n));
+    }
+    return SG_OK;
+}
+
+// training: every tensor is stored, also the pre-skip outputs of the decoder layers (ReLU masks of the backward)
+sg_status forward(sg_ctx* c, Surrogate& s, int n)
 {
     bool head_fused = false;
     for (int L = 0; L < kNumL; ++L) {
@@ -310,13 +381,12 @@ sg_status forward(sg_ctx* c, Surrogate& s, int n, bool train)
         a.b = (const uint16_t*)s.wb.p + s.w_off[L];
         a.bias = (const float*)s.master.p + s.b_off[L];
         a.relu = 1;
-        a.out_bf16 = (d.skip >= 0 && !train) ? nullptr : (uint16_t*)s.act[d.out].p;
+        a.out_bf16 = (uint16_t*)s.act[d.out].p;
         if (L == kNumL - 1 && d.Co == kHeadC && conv_tile_supported(geom_of(sh, 0))) {
-            // the 1x1 head in the last conv's epilogue; its input is kept for the backward only
+            // the 1x1 head in the last conv's epilogue
             a.head_w = (const uint16_t*)s.wb.p + s.head_w;
             a.head_b = (const float*)s.master.p + s.head_b;
             a.head_out = (float*)s.yhat.p;
-            if (!train) a.out_bf16 = nullptr;
             head_fused = true;
         }
         if (d.skip >= 0) {
@@ -336,11 +406,7 @@ sg_status forward(sg_ctx* c, Surrogate& s, int n, bool train)
                                           s.act[kScanTmp].p, sizeof(uint16_t) * kScanC, sizeof(uint16_t) * kScanC,
                                           (size_t)n * s.H * s.W, hipMemcpyDeviceToDevice, c->stream),
                          "depth integral copy"));
-        if (d.out == kScanSrc)   // 1x1 map of E0 and its depth integral (dense, copied into S0 later)
-            SG_TRY(check(depth_map_scan_fwd((const uint16_t*)s.act[kScanSrc].p, (const uint16_t*)s.wb.p + s.proj_w,
-                                            (const float*)s.master.p + s.proj_b, (uint16_t*)s.act[kScanTmp].p, n, s.H,
-                                            s.W, kScanScale, kScanC, 0, c->stream),
-                         "depth integral"));
+        if (d.out == kScanSrc) SG_TRY(forward_scan(c, s, n));
     }
     if (head_fused) return SG_OK;
     return check(head_fwd((const uint16_t*)s.act[D0].p, (const uint16_t*)s.wb.p + s.head_w,
@@ -927,7 +993,7 @@ void drop_graph(Surrogate& s)
 // forward, L1 (and adversarial) loss, backward, Adam and the loss log on the batch in act[X] / target
 sg_status train_body(sg_ctx* c, Surrogate& s, int32_t n)
 {
-    SG_TRY(forward(c, s, n, true));
+    SG_TRY(forward(c, s, n));
     const int64_t P = (int64_t)n * s.H * s.W;
     const int lb = blocks_for(P);
     SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)lb), "loss workspace"));
@@ -1143,9 +1209,9 @@ extern "C" sg_status sg_audit_decide(int32_t n_audit, const float* psnr, float p
 
 namespace sg {
 namespace {
-// audited inference into FP32 frames `out` (device, n x H x W); synchronises
+// audited inference into FP32 frames `out` (device, n x H x W) and, unless null, their bf16; synchronises
 sg_status infer_impl(sg_ctx* c, Surrogate* s, int32_t n, const int32_t* vol_ids, const sg_probe* probes,
-                     const double* poses, float* out, const int32_t* audit_envs, int32_t n_audit, float psnr_min,
+                     const double* poses, float* out, uint16_t* out_bf16, const int32_t* audit_envs, int32_t n_audit, float psnr_min,
                      float max_fail_frac, float* psnr_out, int32_t* n_fallback)
 {
     if (n < 1 || n_audit < 0 || n_audit > n || (n_audit > 0 && (!audit_envs || !psnr_out)))
@@ -1161,8 +1227,7 @@ sg_status infer_impl(sg_ctx* c, Surrogate* s, int32_t n, const int32_t* vol_ids,
     SG_TRY(ensure_capacity(*s, n, false));
     const int64_t HW = (int64_t)s->H * s->W;
     SG_TRY(encode_and_render(c, *s, n, vol_ids, probes, poses, nullptr));
-    SG_TRY(forward(c, *s, n, false));
-    SG_TRY(check(clamp01((const float*)s->yhat.p, out, (int64_t)n * HW, c->stream), "clamp"));
+    SG_TRY(forward_frames(c, *s, n, out, out_bf16));
     *n_fallback = 0;
     if (n_audit == 0) return check(hipStreamSynchronize(c->stream), "infer");
     // render the audited envs with the physics path
@@ -1200,6 +1265,7 @@ sg_status infer_impl(sg_ctx* c, Surrogate* s, int32_t n, const int32_t* vol_ids,
         for (int i = 0; i < n; ++i) offs[i] = (int64_t)i * HW;
         SG_TRY(stage_physics(c, n, vol_ids, probes, poses, out, offs.data(), nullptr, a, info));
         SG_TRY(launch_physics(c, a, info));
+        if (out_bf16) SG_TRY(check(mask_to_bf16(out, nullptr, out_bf16, n * HW, c->stream), "bf16 frames"));
         *n_fallback = n;
     } else {
         int nf = 0;
@@ -1208,6 +1274,10 @@ sg_status infer_impl(sg_ctx* c, Surrogate* s, int32_t n, const int32_t* vol_ids,
             SG_TRY(check(hipMemcpyAsync(out + (int64_t)av[i] * HW, (const float*)s->target.p + (int64_t)i * HW,
                                         sizeof(float) * HW, hipMemcpyDeviceToDevice, c->stream),
                          "fallback copy"));
+            if (out_bf16)
+                SG_TRY(check(mask_to_bf16(out + (int64_t)av[i] * HW, nullptr, out_bf16 + (int64_t)av[i] * HW, HW,
+                                          c->stream),
+                             "bf16 frame"));
             ++nf;
         }
         *n_fallback = nf;
@@ -1224,7 +1294,7 @@ extern "C" sg_status sg_surr_infer(sg_ctx* c, int32_t id, int32_t n, const int32
     Surrogate* s = find_surr(c, id);
     if (!s || !vol_ids || !probes || !poses || !out || !n_fallback)
         return fail(SG_EINVAL, "sg_surr_infer: bad id or NULL");
-    return infer_impl(c, s, n, vol_ids, probes, poses, out, audit_envs, n_audit, psnr_min, max_fail_frac, psnr_out,
+    return infer_impl(c, s, n, vol_ids, probes, poses, out, nullptr, audit_envs, n_audit, psnr_min, max_fail_frac, psnr_out,
                       n_fallback);
 }
 
@@ -1241,10 +1311,8 @@ extern "C" sg_status sg_surr_infer_bf16(sg_ctx* c, int32_t id, int32_t n, const 
     SG_TRY(check_frames(*s, n, probes));
     const int64_t P = (int64_t)n * s->H * s->W;
     SG_TRY(check(s->out32.ensure(sizeof(float) * (size_t)P), "FP32 frames"));
-    SG_TRY(infer_impl(c, s, n, vol_ids, probes, poses, (float*)s->out32.p, audit_envs, n_audit, psnr_min,
-                      max_fail_frac, psnr_out, n_fallback));
-    SG_TRY(check(mask_to_bf16((const float*)s->out32.p, nullptr, out_bf16, P, c->stream), "bf16 frames"));
-    return check(hipStreamSynchronize(c->stream), "infer");
+    return infer_impl(c, s, n, vol_ids, probes, poses, (float*)s->out32.p, out_bf16, audit_envs, n_audit, psnr_min,
+                      max_fail_frac, psnr_out, n_fallback);
 }
 
 namespace {

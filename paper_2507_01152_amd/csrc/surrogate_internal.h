@@ -130,6 +130,26 @@ inline ConvGeom geom_of(const ConvShape& s, int mode)
 }
 
 hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits, hipStream_t s);
+// two 3x3 convs (pad 1, ReLU) of N H x W frames in one pass, C -> CM and CM + EX -> CO channels (see
+// k_conv3x3_pair; C, up, CM, EX, CO: 8 0 16 0 16 or 32 1 16 8 16)
+struct PairArgs {
+    int32_t N, H, W;         // output size of both convs (up: x is H / 2 x W / 2)
+    const uint16_t* x;
+    const uint16_t* w1;      // [CM][9][C]
+    const float* b1;
+    const uint16_t* skip;    // up: [pixel][CM], added to the first conv's output
+    const uint16_t* extra;   // EX: [pixel][EX], the second conv's last input channels
+    const uint16_t* w2;      // [CO][9][CM + EX]
+    const float* b2;
+    uint16_t* out;           // [pixel][CO], or null with head_out
+    // CO = 16: head_out[pixel] = min(max(head_b[0] + sum_co head_w[co] bf16(out[pixel][co]), 0), 1), and its
+    // bf16 in head_bf16 unless that is null
+    const uint16_t* head_w;
+    const float* head_b;
+    float* head_out;
+    uint16_t* head_bf16;
+};
+hipError_t conv_pair(int C, int up, int CM, int EX, int CO, const PairArgs& a, hipStream_t s);
 // forward shapes served by the LDS-tiled direct 3x3 kernel (stride 1, pad 1, C in {8, 16, 24, 32},
 // Co in {16, 32}); the fused head needs Co = 16
 bool conv_tile_supported(const ConvGeom& g);
@@ -229,6 +249,5 @@ hipError_t psnr_frames(const float* yhat, const float* y, int n_frames, int64_t 
 hipError_t psnr_indexed(const float* yhat, const float* y, const int32_t* idx, int n_frames, int64_t frame,
                         float* psnr, hipStream_t s);
 hipError_t transpose_w(const uint16_t* w, uint16_t* wt, int Co, int taps, int Ci, hipStream_t s);
-hipError_t clamp01(const float* x, float* y, int64_t n, hipStream_t s);
 
 }  // namespace sg

@@ -127,3 +127,28 @@ def test_tiled_weight_gradient_many_tiles(sess, n, h, w, c, co, stride, up):
                                           (256, 8, 8, 64, 64, 1), (33, 17, 13, 128, 64, 1), (70, 9, 9, 256, 64, 1), (64, 8, 16, 256, 128, 1)])
 def test_halo_layers(sess, n, h, w, c, co, up):
     _layer(sess, n, h, w, c, co, up=up, seed=h + w)
+
+
+# inference passes two layers at a time where nothing stores the tensor between them: the frames are the training
+# forward's outputs clamped to [0, 1] (same K order and roundings: equal bits), their bf16 the rounded frames,
+# also where audited frames were replaced; one image tile, ragged tiles, several
+@pytest.mark.parametrize("n,h,w", [(1, 16, 16), (2, 32, 48), (3, 112, 80)])
+def test_inference_passes(sess, n, h, w):
+    from paper_2507_01152_amd import sonosim as sg
+    from test_surrogate_gpu import _pairs
+    wl = _pairs(n, h, w, seed=n)
+    vids = sess.load(wl)
+    sid = sg.sg_surr_create(sess.ctx, h, w, seed=5)
+    out = torch.empty((n, h, w), dtype=torch.float32, device="cuda")
+    out16 = torch.empty((n, h, w), dtype=torch.bfloat16, device="cuda")
+    sg.sg_surr_infer(sess.ctx, sid, vids, wl.probes, wl.poses, out, [], 30.0)
+    sg.sg_surr_infer_bf16(sess.ctx, sid, vids, wl.probes, wl.poses, out16, [], 30.0)
+    assert torch.equal(out.bfloat16(), out16)
+    sg.sg_surr_train_step(sess.ctx, sid, vids, wl.probes, wl.poses, 0.0)
+    yhat = sg.sg_surr_tensor(sess.ctx, sid, sg.SURR_T_YHAT, 0).reshape(n, h, w)
+    assert np.array_equal(np.clip(yhat, 0, 1), out.cpu().numpy())
+    for audit, frac in (([n - 1], 1.0), (list(range(n)), 0.0)):   # one frame replaced; all of them
+        _, nf = sg.sg_surr_infer(sess.ctx, sid, vids, wl.probes, wl.poses, out, audit, np.inf, frac)
+        _, nf16 = sg.sg_surr_infer_bf16(sess.ctx, sid, vids, wl.probes, wl.poses, out16, audit, np.inf, frac)
+        assert nf == nf16 == len(audit) and torch.equal(out.bfloat16(), out16)
+    sg.sg_surr_destroy(sess.ctx, sid)
