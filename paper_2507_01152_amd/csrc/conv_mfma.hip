@@ -1642,20 +1642,28 @@ __global__ __launch_bounds__(256, wgrad_blocks_per_cu(CI, CO, !UP && !S2)) void 
 }
 
 // Backward of the 1x1 map p = W x (W: KC x C, bf16) feeding the depth
-// integral: g[pixel][c] += sum_k dp[pixel][k] W[k][c] (written once, after
-// the FP32 sum over k) and the per-block partials of dW[k][c] = sum over
-// pixels of dp[pixel][k] x[pixel][c].  Four threads share a pixel, each
+// integral and of the skip sum next to it, from the gradient gs [pixel][ld]
+// whose first C channels belong to u + x (u: a conv's output): the gradient at
+// x, g[pixel][c] = gs[pixel][c] + sum_k dp[pixel][k] W[k][c] (FP32 sum over
+// k), u's masked gradient dpre = bf16(gs [u > 0]), the per-block partials of
+// dW[k][c] = sum over pixels of dp[pixel][k] x[pixel][c] and, in bias_part,
+// of dpre's column sums.  Four threads share a pixel, each
 // owning C / 4 channels, so a thread keeps KC x C / 4 accumulators; the
 // pixels are dealt out in a fixed order and reduced in a fixed order.
+// Bound by memory: gs copied to g, g read and written again and gs read a
+// third time for dpre, 2097152 pixels took 119 (with the integral) + 60 + 60 us, now 65 + 103.
 constexpr int kProjBlocks = 1024;
 template <int KC, int C>
 __global__ __launch_bounds__(256) void k_proj_bwd(const uint16_t* __restrict__ dp, const uint16_t* __restrict__ x,
-                                                  const uint16_t* __restrict__ w, float* __restrict__ g, int64_t P,
-                                                  float* __restrict__ part)
+                                                  const uint16_t* __restrict__ w, const float* __restrict__ gs, int ld,
+                                                  const uint16_t* __restrict__ u, float* __restrict__ g,
+                                                  uint16_t* __restrict__ dpre, int64_t P, float* __restrict__ part,
+                                                  float* __restrict__ bias_part)
 {
     constexpr int CQ = C / 4;
-    static_assert(C % 16 == 0 && KC == 8, "four 4-channel groups per thread quad; 8 map channels");
-    __shared__ float red[4][KC * C];
+    static_assert(C == 16 && KC == 8, "four 4-channel groups per thread quad; 8 map channels");
+    __shared__ float red[4][KC * C], redb[4][C];
+    float bsum[CQ] = {0.f, 0.f, 0.f, 0.f};
     const int q = threadIdx.x & 3, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float wr[KC][CQ], acc[KC][CQ];
 #pragma unroll
@@ -1684,24 +1692,24 @@ __global__ __launch_bounds__(256) void k_proj_bwd(const uint16_t* __restrict__ d
             xs[j + 2] = __uint_as_float(v.y << 16);
             xs[j + 3] = __uint_as_float(v.y & 0xFFFF0000u);
         }
-        float* gp = g + p * C + q * CQ;
+        const float4 gv = *reinterpret_cast<const float4*>(gs + p * ld + q * CQ);
+        const uint2 uv = *reinterpret_cast<const uint2*>(u + p * C + q * CQ);
+        const float gsv[CQ] = {gv.x, gv.y, gv.z, gv.w};
+        const float us[CQ] = {__uint_as_float(uv.x << 16), __uint_as_float(uv.x & 0xFFFF0000u),
+                              __uint_as_float(uv.y << 16), __uint_as_float(uv.y & 0xFFFF0000u)};
+        float go[CQ];
+        uint32_t b[CQ];
 #pragma unroll
-        for (int j = 0; j < CQ; j += 4) {
-            float4 gv = *reinterpret_cast<const float4*>(gp + j);
-            float s[4];
+        for (int e = 0; e < CQ; ++e) {
+            float t = 0.f;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float t = 0.f;
-#pragma unroll
-                for (int k = 0; k < KC; ++k) t = fmaf(d[k], wr[k][j + e], t);
-                s[e] = t;
-            }
-            gv.x += s[0];
-            gv.y += s[1];
-            gv.z += s[2];
-            gv.w += s[3];
-            *reinterpret_cast<float4*>(gp + j) = gv;
+            for (int k = 0; k < KC; ++k) t = fmaf(d[k], wr[k][e], t);
+            go[e] = gsv[e] + t;
+            b[e] = f2bf(us[e] > 0.f ? gsv[e] : 0.f);
+            bsum[e] += bf2f((uint16_t)b[e]);
         }
+        *reinterpret_cast<float4*>(g + p * C + q * CQ) = make_float4(go[0], go[1], go[2], go[3]);
+        *reinterpret_cast<uint2*>(dpre + p * C + q * CQ) = make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
 #pragma unroll
         for (int k = 0; k < KC; ++k)
 #pragma unroll
@@ -1717,7 +1725,17 @@ __global__ __launch_bounds__(256) void k_proj_bwd(const uint16_t* __restrict__ d
             for (int m = 4; m < 64; m <<= 1) v += __shfl_xor(v, m);
             if (lane < 4) red[wave][k * C + q * CQ + j] = v;
         }
+#pragma unroll
+    for (int j = 0; j < CQ; ++j) {
+        float v = bsum[j];
+#pragma unroll
+        for (int m = 4; m < 64; m <<= 1) v += __shfl_xor(v, m);
+        if (lane < 4) redb[wave][q * CQ + j] = v;
+    }
     __syncthreads();
+    if (threadIdx.x < C)
+        bias_part[(int64_t)blockIdx.x * C + threadIdx.x] =
+            ((redb[0][threadIdx.x] + redb[1][threadIdx.x]) + redb[2][threadIdx.x]) + redb[3][threadIdx.x];
     for (int i = threadIdx.x; i < KC * C; i += 256)
         part[(int64_t)blockIdx.x * (KC * C) + i] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
 }
@@ -2000,13 +2018,12 @@ __global__ __launch_bounds__(256) void k_depth_map_scan_fwd1(const uint16_t* __r
 
 // Backward of k_depth_map_scan_fwd after the 1x1 map, through a tensor g
 // [pixel][ld] (FP32) whose channels [c_off, c_off + 8) are the integral's
-// gradient:  dp[n][v][x][k] = bf16(scale * sum_{y > v} g[n][y][x][c_off + k]),
-// channels [0, c_off) copied to g_skip [pixel][c_off] (c_off multiple of 4),
+// gradient:  dp[n][v][x][k] = bf16(scale * sum_{y > v} g[n][y][x][c_off + k])
 // and per-block column sums of the bf16 dp (bias gradient partials) in
 // part[block][8].
 __global__ __launch_bounds__(256) void k_depth_scan_bwd(const float* __restrict__ g, int ld, int c_off,
-                                                        float* __restrict__ g_skip, uint16_t* __restrict__ dp,
-                                                        float* __restrict__ part, int N, int H, int W, float scale)
+                                                        uint16_t* __restrict__ dp, float* __restrict__ part, int N,
+                                                        int H, int W, float scale)
 {
     __shared__ float tot[kScanSeg][kScanC][kScanCols + 1];
     __shared__ float red[kScanC][256];
@@ -2061,8 +2078,6 @@ __global__ __launch_bounds__(256) void k_depth_scan_bwd(const float* __restrict_
             const int y = y0 - q;
             if (y < ya) break;
             const int64_t px = pc + (int64_t)y * W;
-            for (int cc = 0; cc < c_off; cc += 4)
-                *reinterpret_cast<float4*>(g_skip + px * c_off + cc) = *reinterpret_cast<const float4*>(g + px * ld + cc);
             u32x4 o;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -2182,44 +2197,58 @@ __global__ __launch_bounds__(256) void k_head_fwd(const uint16_t* x, const uint1
     }
 }
 
-// head backward (C = 16): dx[p][c] = w[c] g[p]; per-block partials of
-// dw[c] = sum_p x[p][c] g[p] (c < 16) and db = sum_p g[p] (entry 16)
-__global__ __launch_bounds__(256) void k_head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float* dx,
-                                                  int64_t P, int C, int64_t rows_per_block, float* part)
+// head backward (C = 16): dx[p][c] = w[c] g[p] (FP32), the layer's masked gradient dpre = bf16(dx [x > 0]), and
+// per-block partials of dw[c] = sum_p x[p][c] g[p] (c < 16), db = sum_p g[p] (entry 16) and, in bias_part, of the
+// column sums of dpre.  Bound by memory (56 bytes in and out of a pixel's 16 channels); dpre in a pass of its own
+// (k_mask_colsum), 2097152 pixels took 54 + 55 us, now 73.
+__global__ __launch_bounds__(256) void k_head_bwd(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+                                                  const float* __restrict__ g, float* __restrict__ dx,
+                                                  uint16_t* __restrict__ dpre, int64_t P, int64_t rows_per_block,
+                                                  float* __restrict__ part, float* __restrict__ bias_part)
 {
-    __shared__ float red[17][256];
-    float wf[16], acc[17];
+    constexpr int NR = 33;   // dw, db, column sums of dpre
+    __shared__ float red[NR][257];   // (a row more than the threads: the sums below read NR different banks)
+    float wf[16], acc[NR];
 #pragma unroll
     for (int c = 0; c < 16; ++c) wf[c] = bf2f(w[c]);
 #pragma unroll
-    for (int c = 0; c < 17; ++c) acc[c] = 0.f;
+    for (int c = 0; c < NR; ++c) acc[c] = 0.f;
     const int64_t p0 = (int64_t)blockIdx.x * rows_per_block;
     const int64_t p1 = min(P, p0 + rows_per_block);
     for (int64_t p = p0 + threadIdx.x; p < p1; p += blockDim.x) {
         const float gp = g[p];
-        const uint4 v0 = *reinterpret_cast<const uint4*>(x + p * 16);
-        const uint4 v1 = *reinterpret_cast<const uint4*>(x + p * 16 + 8);
-        const uint16_t* h0 = reinterpret_cast<const uint16_t*>(&v0);
-        const uint16_t* h1 = reinterpret_cast<const uint16_t*>(&v1);
+        const u32x4 v[2] = {*reinterpret_cast<const u32x4*>(x + p * 16), *reinterpret_cast<const u32x4*>(x + p * 16 + 8)};
+        u32x4 o[2];
+        float d[16];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] += bf2f(h0[c]) * gp;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[8 + c] += bf2f(h1[c]) * gp;
+        for (int c = 0; c < 16; c += 2) {
+            const uint32_t u = v[c / 8][c % 8 / 2];
+            const float xl = __uint_as_float(u << 16), xh = __uint_as_float(u & 0xFFFF0000u);
+            acc[c] += xl * gp;
+            acc[c + 1] += xh * gp;
+            d[c] = wf[c] * gp;
+            d[c + 1] = wf[c + 1] * gp;
+            const uint32_t b = (uint32_t)f2bf(xl > 0.f ? d[c] : 0.f) | ((uint32_t)f2bf(xh > 0.f ? d[c + 1] : 0.f) << 16);
+            o[c / 8][c % 8 / 2] = b;
+            acc[17 + c] += __uint_as_float(b << 16);
+            acc[18 + c] += __uint_as_float(b & 0xFFFF0000u);
+        }
         acc[16] += gp;
-        float4* d = reinterpret_cast<float4*>(dx + p * 16);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            d[q] = make_float4(wf[4 * q] * gp, wf[4 * q + 1] * gp, wf[4 * q + 2] * gp, wf[4 * q + 3] * gp);
+            *reinterpret_cast<float4*>(dx + p * 16 + 4 * q) = make_float4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+        *reinterpret_cast<u32x4*>(dpre + p * 16) = o[0];
+        *reinterpret_cast<u32x4*>(dpre + p * 16 + 8) = o[1];
     }
 #pragma unroll
-    for (int c = 0; c < 17; ++c) red[c][threadIdx.x] = acc[c];
+    for (int c = 0; c < NR; ++c) red[c][threadIdx.x] = acc[c];
     __syncthreads();
-    if (threadIdx.x < 17) {
+    if (threadIdx.x < NR) {
         float t = 0.f;
         for (int j = 0; j < 256; ++j) t += red[threadIdx.x][j];
-        part[(int64_t)blockIdx.x * 17 + threadIdx.x] = t;
+        if (threadIdx.x < 17) part[(int64_t)blockIdx.x * 17 + threadIdx.x] = t;
+        else bias_part[(int64_t)blockIdx.x * 16 + threadIdx.x - 17] = t;
     }
-    (void)C;
 }
 
 // Discriminator input of two sets of P pixels: z[i] = (x[p] channels 0..3,
@@ -2843,23 +2872,25 @@ hipError_t depth_map_scan_fwd(const uint16_t* e, const uint16_t* w, const float*
     return hipGetLastError();
 }
 
-hipError_t depth_scan_bwd(const float* g, int ld, int c_off, float* g_skip, uint16_t* dp, float* part,
-                          float* bias_grad, int N, int H, int W, float scale, hipStream_t s)
+hipError_t depth_scan_bwd(const float* g, int ld, int c_off, uint16_t* dp, float* part, float* bias_grad, int N,
+                          int H, int W, float scale, hipStream_t s)
 {
     if (ld % 4 || c_off % 4 || c_off + kScanC > ld) return hipErrorInvalidValue;
     const int blocks = depth_scan_blocks(N, W);
-    hipLaunchKernelGGL(k_depth_scan_bwd, dim3((unsigned)blocks), dim3(256), 0, s, g, ld, c_off, g_skip, dp, part, N,
-                       H, W, scale);
+    hipLaunchKernelGGL(k_depth_scan_bwd, dim3((unsigned)blocks), dim3(256), 0, s, g, ld, c_off, dp, part, N, H, W,
+                       scale);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return reduce_parts(part, kScanC, blocks, bias_grad, s);
 }
 
-hipError_t proj_bwd(const uint16_t* dp, const uint16_t* x, const uint16_t* w, float* g, int64_t P, int KC, int C,
-                    float* part, float* dw, hipStream_t s)
+hipError_t proj_bwd(const uint16_t* dp, const uint16_t* x, const uint16_t* w, const float* gs, int ld,
+                    const uint16_t* u, float* g, uint16_t* dpre, int64_t P, int KC, int C, float* part,
+                    float* bias_part, float* dw, hipStream_t s)
 {
-    if (KC != 8 || C != 16 || P < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_proj_bwd<8, 16>), dim3(kProjBlocks), dim3(256), 0, s, dp, x, w, g, P, part);
+    if (KC != 8 || C != 16 || P < 1 || ld < C || ld % 4) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_proj_bwd<8, 16>), dim3(kProjBlocks), dim3(256), 0, s, dp, x, w, gs, ld, u, g, dpre, P, part,
+                       bias_part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return reduce_parts(part, KC * C, kProjBlocks, dw, s);
@@ -2896,11 +2927,11 @@ hipError_t head_fwd(const uint16_t* x, const uint16_t* w, const float* b, float*
     return hipGetLastError();
 }
 
-hipError_t head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float* dx, int64_t P, int C, float* part,
-                    int blocks, float* dwb, hipStream_t s)
+hipError_t head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float* dx, uint16_t* dpre, int64_t P,
+                    float* part, float* bias_part, int blocks, float* dwb, hipStream_t s)
 {
     const int64_t per = (P + blocks - 1) / blocks;
-    hipLaunchKernelGGL(k_head_bwd, dim3(blocks), dim3(256), 0, s, x, w, g, dx, P, C, per, part);
+    hipLaunchKernelGGL(k_head_bwd, dim3(blocks), dim3(256), 0, s, x, w, g, dx, dpre, P, per, part, bias_part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return reduce_parts(part, 17, blocks, dwb, s);

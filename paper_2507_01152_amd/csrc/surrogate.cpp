@@ -420,18 +420,32 @@ sg_status backward(sg_ctx* c, Surrogate& s, int n)
     bool written[kNumT] = {};
     const int64_t P = (int64_t)n * s.H * s.W;
     float* grad = (float*)s.grad.p;
-    const int hb = blocks_for(P);
-    SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)hb * (kHeadC + 1)), "head workspace"));
-    SG_TRY(check(head_bwd((const uint16_t*)s.act[D0].p, (const uint16_t*)s.wb.p + s.head_w, (const float*)s.gy.p,
-                          (float*)s.gact[D0].p, P, kHeadC, (float*)s.parts.p, hb, grad + s.head_w, c->stream),
-                 "head backward"));
-    written[D0] = true;
     static_assert(kNumL <= kMaxReduceSegs, "one bias segment per layer");
     ReduceSegs bseg;
     bseg.count = 0;
     int64_t boff = 0;
     int bfirst = 0;
     SG_TRY(check(s.bias_parts.ensure(sizeof(float) * 1024 * (size_t)bias_count()), "bias partials"));
+    // the bias gradient of layer L in `blocks` (<= 1024) partials, reduced with the other layers' after the loop
+    auto bias_segment = [&](int L, int blocks) -> float* {
+        ReduceSeg& rs = bseg.s[bseg.count++];
+        rs.part_off = boff;
+        rs.out_off = s.b_off[L];
+        rs.n = kLayers[L].Co;
+        rs.splits = blocks;
+        rs.first = bfirst;
+        boff += (int64_t)blocks * rs.n;
+        bfirst += rs.n;
+        return (float*)s.bias_parts.p + rs.part_off;
+    };
+    // the head's gradients and the last layer's masked one
+    const int hb = blocks_for(P);
+    SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)hb * (kHeadC + 1)), "head workspace"));
+    SG_TRY(check(head_bwd((const uint16_t*)s.act[D0].p, (const uint16_t*)s.wb.p + s.head_w, (const float*)s.gy.p,
+                          (float*)s.gact[D0].p, (uint16_t*)s.dpre.p, P, (float*)s.parts.p,
+                          bias_segment(kNumL - 1, hb), hb, grad + s.head_w, c->stream),
+                 "head backward"));
+    written[D0] = true;
     for (int L = kNumL - 1; L >= 0; --L) {
         const LayerDef& d = kLayers[L];
         const ConvShape sh = layer_shape(s, L, n);
@@ -439,38 +453,29 @@ sg_status backward(sg_ctx* c, Surrogate& s, int n)
         const int64_t n_out = tensor_elems(s, d.out, n);
         const int64_t rows = n_out / d.Co;
         if (go == kScanDst) {
-            // depth integral: dp (bf16, in dscan), its bias gradient, and the skip copy of
-            // S0's first channels into E0's gradient; then the 1x1 map's two products
+            // depth integral: dp (bf16, in dscan) and its bias gradient; then the 1x1 map's two products, E0's
+            // gradient (with the skip's part) and this layer's masked one
             const int sb = depth_scan_blocks(n, s.W);
             SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)sb * kScanC), "depth integral workspace"));
-            SG_TRY(check(depth_scan_bwd((const float*)s.gact[kScanDst].p, kTC[kScanDst], kScanOff,
-                                        (float*)s.gact[kScanSrc].p, (uint16_t*)s.dscan.p, (float*)s.parts.p,
-                                        grad + s.proj_b, n, s.H, s.W, kScanScale, c->stream),
+            SG_TRY(check(depth_scan_bwd((const float*)s.gact[kScanDst].p, kTC[kScanDst], kScanOff, (uint16_t*)s.dscan.p,
+                                        (float*)s.parts.p, grad + s.proj_b, n, s.H, s.W, kScanScale, c->stream),
                          "depth integral backward"));
-            SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)proj_bwd_blocks() * kScanC * kTC[kScanSrc]),
-                         "depth map workspace"));
+            const int pb = proj_bwd_blocks();
+            SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)pb * kScanC * kTC[kScanSrc]), "depth map workspace"));
             SG_TRY(check(proj_bwd((const uint16_t*)s.dscan.p, (const uint16_t*)s.act[kScanSrc].p,
-                                  (const uint16_t*)s.wb.p + s.proj_w, (float*)s.gact[kScanSrc].p,
-                                  (int64_t)n * s.H * s.W, kScanC, kTC[kScanSrc], (float*)s.parts.p, grad + s.proj_w,
+                                  (const uint16_t*)s.wb.p + s.proj_w, (const float*)s.gact[kScanDst].p, kTC[kScanDst],
+                                  (const uint16_t*)s.act[d.out].p, (float*)s.gact[kScanSrc].p, (uint16_t*)s.dpre.p, P,
+                                  kScanC, kTC[kScanSrc], (float*)s.parts.p, bias_segment(L, pb), grad + s.proj_w,
                                   c->stream),
                          "depth map backward"));
             written[kScanSrc] = true;
+        } else if (L < kNumL - 1) {   // ReLU mask and the bias gradient's partials
+            const int mb = blocks_for(rows * d.Co / 2, 1024);   // about four rows per thread
+            SG_TRY(check(mask_colsum((const float*)s.gact[go].p, kTC[go], (const uint16_t*)s.act[d.out].p,
+                                     (uint16_t*)s.dpre.p, rows, d.Co, bias_segment(L, mb), mb, nullptr, c->stream),
+                         "relu mask and bias partials"));
         }
-        // ReLU mask; the bias gradient's per-block partials are reduced with the other layers' after the loop
-        const int mb = blocks_for(rows * d.Co / 2, 1024);   // about four rows per thread
-        ReduceSeg& rs = bseg.s[bseg.count++];
-        rs.part_off = boff;
-        rs.out_off = s.b_off[L];
-        rs.n = d.Co;
-        rs.splits = mb;
-        rs.first = bfirst;
-        boff += (int64_t)mb * d.Co;
-        bfirst += d.Co;
-        SG_TRY(check(mask_colsum((const float*)s.gact[go].p, kTC[go], (const uint16_t*)s.act[d.out].p,
-                                 (uint16_t*)s.dpre.p, rows, d.Co, (float*)s.bias_parts.p + rs.part_off, mb, nullptr,
-                                 c->stream),
-                     "relu mask and bias partials"));
-        if (d.skip >= 0 && go != kScanDst) {   // (S0's skip copy is done by the depth integral's backward)
+        if (d.skip >= 0 && go != kScanDst) {   // (S0's part is added by the depth map's backward)
             // out2 = out + skip: the skip tensor receives the same gradient
             SG_TRY(check(hipMemcpyAsync(s.gact[d.skip].p, s.gact[go].p, sizeof(float) * n_out,
                                         hipMemcpyDeviceToDevice, c->stream),

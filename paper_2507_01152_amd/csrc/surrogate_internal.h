@@ -196,17 +196,19 @@ hipError_t add_channel(float* gy, const float* dz, int ld, int c, int64_t P, hip
 // out [N][H][W][ld]
 hipError_t depth_map_scan_fwd(const uint16_t* e, const uint16_t* w, const float* b, uint16_t* out, int N, int H,
                               int W, float scale, int ld, int c_off, hipStream_t s);
-// its backward from g [N][H][W][ld] (FP32): dp (bf16, [N][H][W][8]), the channels [0, c_off) copied to
-// g_skip [N][H][W][c_off], bias_grad[8] = column sums of dp; part holds depth_scan_blocks(N, W) * 8 floats
+// its backward from g [N][H][W][ld] (FP32): dp (bf16, [N][H][W][8]) and bias_grad[8] = column sums of dp; part
+// holds depth_scan_blocks(N, W) * 8 floats
 int depth_scan_blocks(int N, int W);
-// backward of the 1x1 map p = W x (KC = 8 map channels, C = 16 input channels, W bf16 [KC][C]) over
-// P pixels: g [P][C] += dp W (FP32) and dw [KC][C] = sum of dp^T x (FP32, fixed order); part holds
-// proj_bwd_blocks() * KC * C floats
+hipError_t depth_scan_bwd(const float* g, int ld, int c_off, uint16_t* dp, float* part, float* bias_grad, int N,
+                          int H, int W, float scale, hipStream_t s);
+// backward of the 1x1 map p = W x (KC = 8 map channels, C = 16 input channels, W bf16 [KC][C]) and of the sum u + x
+// whose gradient is gs [P][ld] (first C channels), over P pixels: g [P][C] = gs + dp W (FP32), dpre [P][C] =
+// bf16(gs [u > 0]), dw [KC][C] = sum of dp^T x (FP32, fixed order) and, in bias_part, proj_bwd_blocks() partials
+// of dpre's column sums; part holds proj_bwd_blocks() * KC * C floats
 int proj_bwd_blocks();
-hipError_t proj_bwd(const uint16_t* dp, const uint16_t* x, const uint16_t* w, float* g, int64_t P, int KC, int C,
-                    float* part, float* dw, hipStream_t s);
-hipError_t depth_scan_bwd(const float* g, int ld, int c_off, float* g_skip, uint16_t* dp, float* part,
-                          float* bias_grad, int N, int H, int W, float scale, hipStream_t s);
+hipError_t proj_bwd(const uint16_t* dp, const uint16_t* x, const uint16_t* w, const float* gs, int ld,
+                    const uint16_t* u, float* g, uint16_t* dpre, int64_t P, int KC, int C, float* part,
+                    float* bias_part, float* dw, hipStream_t s);
 hipError_t colsum_bf16(const uint16_t* x, int64_t rows, int cols, float* part, int blocks, float* out,
                        hipStream_t s);
 hipError_t sum_parts(const float* part, int64_t n, int splits, float* out, hipStream_t s);
@@ -224,8 +226,9 @@ struct ReduceSegs {
 };
 hipError_t reduce_segments(const float* part, float* out, const ReduceSegs& t, hipStream_t s);
 hipError_t head_fwd(const uint16_t* x, const uint16_t* w, const float* b, float* y, int64_t P, int C, hipStream_t s);
-hipError_t head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float* dx, int64_t P, int C, float* part,
-                    int blocks, float* dwb, hipStream_t s);
+// backward of the head over P pixels of 16 channels (see k_head_bwd); part: blocks * 17 floats, bias_part: blocks * 16
+hipError_t head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float* dx, uint16_t* dpre, int64_t P,
+                    float* part, float* bias_part, int blocks, float* dwb, hipStream_t s);
 hipError_t l1_loss(const float* yhat, const float* y, int64_t n, float* grad, float* part, int blocks, float* loss,
                    hipStream_t s);
 // Adam: the step counters and per-step scalars live on the device (coef = {lr, c1, c2, disc c1, disc c2});
