@@ -639,7 +639,7 @@ __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
                 const int col = n_base + wn * TN + j * 16 + (lane & 15);
-                pre[i][j] = (a.accumulate && col < g.N && row < g.M) ? a.out_f32[(row >> 2) * g.C + col] : 0.f;
+                pre[i][j] = (a.add && col < g.N && row < g.M) ? a.add[(row >> 2) * g.C + col] : 0.f;
             }
         }
 #pragma unroll
@@ -649,12 +649,12 @@ __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
             for (int j = 0; j < FN; ++j) {
                 const int col = n_base + wn * TN + j * 16 + (lane & 15);
                 const float v = (acc[i][j][0] + acc[i][j][1]) + (acc[i][j][2] + acc[i][j][3]);
-                if (col < g.N && row < g.M) a.out_f32[(row >> 2) * g.C + col] = a.accumulate ? pre[i][j] + v : v;
+                if (col < g.N && row < g.M) a.out_f32[(row >> 2) * g.C + col] = a.add ? pre[i][j] + v : v;
             }
         }
         return;
     }
-    if (MODE == kDgrad && a.accumulate) {
+    if (MODE == kDgrad && a.add) {
         // per row tile, the old values are all loaded before the tile's first store (a load issued
         // after a store waits for it)
 #pragma unroll
@@ -668,7 +668,7 @@ __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
                 const int col = n_base + wn * TN + j * 16 + (lane & 15);
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    pre[j][r] = (col < g.N && px[r] >= 0) ? a.out_f32[px[r] * g.C + col] : 0.f;
+                    pre[j][r] = (col < g.N && px[r] >= 0) ? a.add[px[r] * g.C + col] : 0.f;
             }
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
@@ -878,7 +878,7 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 #pragma unroll
                     for (int pr = 0; pr < 2; ++pr) {
                         const int wc = ((wo0 + h * 16 + 4 * lk) >> 1) + pr;
-                        pv[j][h][pr] = (hc < Hc && wc < Wc) ? a.out_f32[((n * Hc + hc) * Wc + wc) * CO + 16 * j + lr]
+                        pv[j][h][pr] = (hc < Hc && wc < Wc) ? a.add[((n * Hc + hc) * Wc + wc) * CO + 16 * j + lr]
                                                             : 0.f;
                     }
         }
@@ -896,6 +896,8 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
                     float sum = (y00 + y01) + (y10 + y11);
                     if constexpr (ACC) sum = pv[j][h][pr] + sum;
                     if (hc < Hc && wc < Wc) a.out_f32[((n * Hc + hc) * Wc + wc) * CO + 16 * j + lr] = sum;
+                    // (for dpre: [TH / 2 * kTileW / 2][CO])
+                    sO[(wave * (kTileW / 2) + h * 8 + 2 * lk + pr) * CO + 16 * j + lr] = f2bf(sum);
                 }
     }
     // (one instantiation of the loop per activation; two outputs of a lane, neighbouring pixels of
@@ -905,8 +907,8 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 #pragma unroll
     for (int gi = 0; gi < 4; ++gi) {
         const int rr = 2 * wave + (gi >> 1), ho = ho0 + rr;
-        // ACC (an FP32 output accumulated into, a.accumulate): the old values of this row group,
-        // all loaded before its stores (a load issued after a store waits for it)
+        // ACC (a.add is added to the FP32 output): its values for this row group, all loaded before the
+        // stores (a load issued after a store waits for it)
         float prev[ACC ? FN : 1][4];
         if constexpr (ACC) {
 #pragma unroll
@@ -914,8 +916,8 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int wo = wo0 + (gi & 1) * 16 + 4 * lk + q;
-                    prev[j][q] = (!pool && ho < g.Ho && wo < g.Wo)
-                                     ? a.out_f32[((n * g.Ho + ho) * g.Wo + wo) * CO + 16 * j + lr]
+                    prev[j][q] = (ho < g.Ho && wo < g.Wo)
+                                     ? a.add[((n * g.Ho + ho) * g.Wo + wo) * CO + 16 * j + lr]
                                      : 0.f;
                 }
         }
@@ -925,28 +927,78 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 #pragma unroll
             for (int q = 0; q < 4; q += 2) {
                 const int cc = (gi & 1) * 16 + 4 * lk + q;
-                const float y0 = activate_c<ACT>(acc[gi][j][q] + bias_r[j]);
-                const float y1 = activate_c<ACT>(acc[gi][j][q + 1] + bias_r[j]);
+                float y0 = activate_c<ACT>(acc[gi][j][q] + bias_r[j]);
+                float y1 = activate_c<ACT>(acc[gi][j][q + 1] + bias_r[j]);
+                if constexpr (ACC) {
+                    y0 = prev[j][q] + y0;
+                    y1 = prev[j][q + 1] + y1;
+                }
                 const uint32_t pk = pack_bf16x2(y0, y1);
                 sO[(rr * kTileW + cc) * CO + co] = (uint16_t)pk;
                 sO[(rr * kTileW + cc + 1) * CO + co] = (uint16_t)(pk >> 16);
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     const int wo = wo0 + cc + t;
-                    if (a.out_f32 && !pool && ho < g.Ho && wo < g.Wo) {
-                        float yo = t ? y1 : y0;
-                        if constexpr (ACC) yo = prev[j][q + t] + yo;
-                        a.out_f32[((n * g.Ho + ho) * g.Wo + wo) * CO + co] = yo;
-                    }
+                    if (a.out_f32 && ho < g.Ho && wo < g.Wo)
+                        a.out_f32[((n * g.Ho + ho) * g.Wo + wo) * CO + co] = t ? y1 : y0;
                 }
             }
         }
     }
     };
-    if (a.relu == 1) write_tile(std::integral_constant<int, 1>{});
+    if (pool) {
+    } else if (a.relu == 1) write_tile(std::integral_constant<int, 1>{});
     else if (a.relu == 2) write_tile(std::integral_constant<int, 2>{});
     else write_tile(std::integral_constant<int, 0>{});
     __syncthreads();
+    if (a.dpre) {
+        // the masked gradient of the layer below, bf16(out_f32 [mask > 0]), and this block's column sums of it.  A
+        // pass of its own (k_mask_colsum) reads out_f32 again: 16 -> 16 channels on 2097152 pixels 38 + 55 us, here 65
+        const int tw = pool ? kTileW / 2 : kTileW, th = pool ? TH / 2 : TH;
+        const int Hp = pool ? g.Ho >> 1 : g.Ho, Wp = pool ? g.Wo >> 1 : g.Wo;
+        const int hp0 = pool ? ho0 >> 1 : ho0, wp0 = pool ? wo0 >> 1 : wo0;
+        const int c8 = tid % CO8 * 8;   // the same for every chunk of a thread
+        int64_t op[CO8];
+        u32x4 mv[CO8];
+#pragma unroll
+        for (int u = 0; u < CO8; ++u) {
+            const int pix = (tid + NT * u) / CO8, rr = pix / tw, h = hp0 + rr, w = wp0 + pix - rr * tw;
+            const bool in = (int)(rr < th) & (int)(h < Hp) & (int)(w < Wp);
+            op[u] = in ? (((int64_t)n * Hp + h) * Wp + w) * CO + c8 : -1;
+            mv[u] = in ? *reinterpret_cast<const u32x4*>(a.mask + op[u]) : zero;
+        }
+        float sum[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sum[q] = 0.f;
+#pragma unroll
+        for (int u = 0; u < CO8; ++u) {
+            if (op[u] < 0) continue;
+            u32x4 v = *reinterpret_cast<const u32x4*>(&sO[(tid + NT * u) / CO8 * CO + c8]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float lo = __uint_as_float(mv[u][q] << 16), hi = __uint_as_float(mv[u][q] & 0xFFFF0000u);
+                v[q] = (lo > 0.f ? v[q] & 0xFFFFu : 0u) | (hi > 0.f ? v[q] & 0xFFFF0000u : 0u);
+                sum[2 * q] += __uint_as_float(v[q] << 16);
+                sum[2 * q + 1] += __uint_as_float(v[q] & 0xFFFF0000u);
+            }
+            *reinterpret_cast<u32x4*>(a.dpre + op[u]) = v;
+        }
+        float* red = reinterpret_cast<float*>(sW);   // [waves][CO] (the weights were last read before the barriers above)
+        static_assert(sizeof(sW) >= NT / 64 * CO * sizeof(float), "column sums in the weights' space");
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+#pragma unroll
+            for (int m = CO8; m < 64; m <<= 1) sum[q] += __shfl_xor(sum[q], m);
+            if (lane < CO8) red[wave * CO + c8 + q] = sum[q];
+        }
+        __syncthreads();
+        if (tid < CO) {
+            float t = 0.f;
+            for (int w = 0; w < NT / 64; ++w) t += red[w * CO + tid];
+            a.colsum[(int64_t)blockIdx.x * CO + tid] = t;
+        }
+        return;
+    }
     const int ld2 = a.ld_out2 ? a.ld_out2 : CO;
     // 16-byte output chunks: thread tid takes chunks tid + NT u; the skip tensor's chunks are all
     // loaded before the first store
@@ -2531,10 +2583,9 @@ template <int C, int CO, bool UP, bool DIL = false>
 hipError_t launch_tile(const ConvGeom& g, const ConvArgs& a, hipStream_t s)
 {
     constexpr int TH = kTileH;
-    const int64_t tiles = (int64_t)((g.Ho + TH - 1) / TH) * ((g.Wo + kTileW - 1) / kTileW);
-    const int64_t blocks = tiles * (g.Kw / ((int64_t)g.Ho * g.Wo));   // Kw = N * Ho * Wo
+    const int64_t blocks = conv_tile_blocks(g.Kw / ((int64_t)g.Ho * g.Wo), g.Ho, g.Wo);   // Kw = N * Ho * Wo
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
-    if (a.out_f32 && a.accumulate) {   // data gradients accumulated into (never upsampled)
+    if (a.out_f32 && a.add) {   // data gradients added to something (never upsampled)
         if constexpr (UP) return hipErrorInvalidValue;
         else hipLaunchKernelGGL((k_conv3x3_tile<C, CO, false, DIL, true, TH>), dim3((unsigned)blocks), dim3(32 * TH), 0, s,
                                 g, a);
@@ -2604,8 +2655,13 @@ hipError_t launch_dgrad_tile(const ConvGeom& f, const ConvArgs& a, hipStream_t s
 }
 }  // namespace
 
-hipError_t dgrad_tile(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, int accumulate,
-                      hipStream_t s)
+int64_t conv_tile_blocks(int64_t N, int H, int W)
+{
+    return N * ((H + kTileH - 1) / kTileH) * ((W + kTileW - 1) / kTileW);
+}
+
+hipError_t dgrad_tile(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, const float* add,
+                      const DpreArgs& m, hipStream_t s)
 {
     if (!dgrad_tile_supported(g)) return hipErrorInvalidValue;
     const int Hin = g.up ? 2 * g.H : g.H, Win = g.up ? 2 * g.W : g.W;
@@ -2625,7 +2681,10 @@ hipError_t dgrad_tile(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt,
     a.b = wt;
     a.flip = 1;
     a.out_f32 = dx;
-    a.accumulate = accumulate;
+    a.add = add;
+    a.mask = m.mask;
+    a.dpre = m.dpre;
+    a.colsum = m.colsum;
     a.pool2 = g.up;   // an upsampled layer's gradient at its stored input resolution
     const bool dil = g.stride == 2;
     if (f.Co == 16) return dil ? launch_dgrad_tile<16, true>(f, a, s) : launch_dgrad_tile<16, false>(f, a, s);
@@ -2638,7 +2697,7 @@ bool dgrad_parity_supported(const ConvGeom& g)
            g.H >= 2 && g.W >= 2;
 }
 
-hipError_t dgrad_parity(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, int accumulate,
+hipError_t dgrad_parity(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, const float* add,
                         hipStream_t s)
 {
     if (!dgrad_parity_supported(g)) return hipErrorInvalidValue;
@@ -2661,7 +2720,7 @@ hipError_t dgrad_parity(const ConvGeom& g, const uint16_t* dy, const uint16_t* w
     a.a = dy;
     a.b = wt;
     a.out_f32 = dx;
-    a.accumulate = accumulate;
+    a.add = add;
     return conv_gemm(kDgrad, c, a, 1, s);
 }
 
@@ -2708,6 +2767,7 @@ hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits,
     if (a.extra && (mode != kFwd || !conv_tile_supported(g) || !a.out2_bf16 || a.extra_c < 8 || a.extra_c % 8 ||
                     g.Co + a.extra_c > a.ld_out2))
         return hipErrorInvalidValue;
+    if (a.dpre) return hipErrorInvalidValue;   // (the tiled data gradient's only)
     if (mode == kFwd && conv_tile_supported(g))
         return g.Co == 16 ? launch_tile_co<16>(g, a, s) : launch_tile_co<32>(g, a, s);
     if (mode == kFwd && halo_supported(g))

@@ -78,7 +78,7 @@ struct Surrogate {
     int64_t step = 0;
     int cap = 0, cap_grad = 0, last_n = 0;
     DevBuf act[kNumT], gact[kNumT];
-    DevBuf dpre, parts, yhat, target, gy, loss, psnr, idx;
+    DevBuf dpre[2], parts, yhat, target, gy, loss, psnr, idx;
     DevBuf bias_parts;   // per-block bias-gradient partials of every layer of a backward pass, reduced at its end
     DevBuf dscan;   // bf16 gradient at the depth map's output (the integral's backward), n x H x W x kScanC
     DevBuf out32;   // FP32 frames of bf16 inference
@@ -131,14 +131,6 @@ Surrogate* find_surr(sg_ctx* c, int32_t id)
     if (!c) return nullptr;
     auto it = c->surrogates.find(id);
     return it == c->surrogates.end() ? nullptr : it->second.get();
-}
-
-// output channels of all generator layers (the bias-gradient outputs of a backward pass)
-int bias_count()
-{
-    int n = 0;
-    for (int L = 0; L < kNumL; ++L) n += kLayers[L].Co;
-    return n;
 }
 
 ConvShape layer_shape(const Surrogate& s, int L, int n)
@@ -218,21 +210,24 @@ sg_status wgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* x, const uint16_
     return SG_OK;
 }
 
-// data gradient of one conv into dx (stored input resolution)
-sg_status dgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* dy, const uint16_t* wt, float* dx, int accumulate)
+// data gradient of one conv into dx (stored input resolution), plus add unless null; m: see dgrad_tile (only where
+// that serves the layer)
+sg_status dgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* dy, const uint16_t* wt, float* dx, const float* add,
+                const DpreArgs& m = DpreArgs())
 {
     ConvGeom g = geom_of(sh, 1);
     // few channels: the tiled forward conv of dy with mirrored taps (an upsampled layer's 2 x 2 sums in
     // its epilogue)
-    if (dgrad_tile_supported(g)) return check(dgrad_tile(g, dy, wt, dx, accumulate, c->stream), "dgrad launch");
+    if (dgrad_tile_supported(g)) return check(dgrad_tile(g, dy, wt, dx, add, m, c->stream), "dgrad launch");
+    if (m.dpre) return check(hipErrorInvalidValue, "dgrad launch");
     if (dgrad_parity_supported(g))   // stride 2, wider: one GEMM per output parity class, one launch
-        return check(dgrad_parity(g, dy, wt, dx, accumulate, c->stream), "dgrad launch");
+        return check(dgrad_parity(g, dy, wt, dx, add, c->stream), "dgrad launch");
     ConvArgs a;
     std::memset(&a, 0, sizeof(a));
     a.a = dy;
     a.b = wt;
     a.out_f32 = dx;
-    a.accumulate = accumulate;
+    a.add = add;
     return check(conv_gemm(1, g, a, 1, c->stream), "dgrad launch");
 }
 
@@ -273,7 +268,7 @@ sg_status ensure_capacity(Surrogate& s, int n, bool grads)
             SG_TRY(check(s.gact[t].ensure(sizeof(float) * tensor_elems(s, t, n)), "gradient buffers"));
         int64_t mx = 0;
         for (int t = 1; t < kNumT; ++t) mx = std::max(mx, tensor_elems(s, t, n));
-        SG_TRY(check(s.dpre.ensure(sizeof(uint16_t) * mx), "dpre buffer"));
+        for (DevBuf& b : s.dpre) SG_TRY(check(b.ensure(sizeof(uint16_t) * mx), "dpre buffers"));
         SG_TRY(check(s.dscan.ensure(sizeof(uint16_t) * (size_t)n * s.H * s.W * kScanC), "depth map gradient"));
         SG_TRY(check(s.gy.ensure(sizeof(float) * (int64_t)n * s.H * s.W), "output grad"));
         s.cap_grad = n;
@@ -417,7 +412,8 @@ sg_status forward(sg_ctx* c, Surrogate& s, int n)
 
 sg_status backward(sg_ctx* c, Surrogate& s, int n)
 {
-    bool written[kNumT] = {};
+    // gradient from a tensor's skip connection, added by the data gradient of the conv that reads it
+    const float* skip_g[kNumT] = {};
     const int64_t P = (int64_t)n * s.H * s.W;
     float* grad = (float*)s.grad.p;
     static_assert(kNumL <= kMaxReduceSegs, "one bias segment per layer");
@@ -425,8 +421,11 @@ sg_status backward(sg_ctx* c, Surrogate& s, int n)
     bseg.count = 0;
     int64_t boff = 0;
     int bfirst = 0;
-    SG_TRY(check(s.bias_parts.ensure(sizeof(float) * 1024 * (size_t)bias_count()), "bias partials"));
-    // the bias gradient of layer L in `blocks` (<= 1024) partials, reduced with the other layers' after the loop
+    int64_t nparts = 0;   // of a layer: at most 1024, or one per block of the tiled data gradient that writes them
+    for (int L = 0; L < kNumL; ++L)
+        nparts += kLayers[L].Co * std::max<int64_t>(1024, conv_tile_blocks(n, s.H >> kTL[kLayers[L].out], s.W >> kTL[kLayers[L].out]) * 4);
+    SG_TRY(check(s.bias_parts.ensure(sizeof(float) * nparts), "bias partials"));
+    // the bias gradient of layer L in `blocks` partials, reduced with the other layers' after the loop
     auto bias_segment = [&](int L, int blocks) -> float* {
         ReduceSeg& rs = bseg.s[bseg.count++];
         rs.part_off = boff;
@@ -442,10 +441,11 @@ sg_status backward(sg_ctx* c, Surrogate& s, int n)
     const int hb = blocks_for(P);
     SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)hb * (kHeadC + 1)), "head workspace"));
     SG_TRY(check(head_bwd((const uint16_t*)s.act[D0].p, (const uint16_t*)s.wb.p + s.head_w, (const float*)s.gy.p,
-                          (float*)s.gact[D0].p, (uint16_t*)s.dpre.p, P, (float*)s.parts.p,
+                          (float*)s.gact[D0].p, (uint16_t*)s.dpre[0].p, P, (float*)s.parts.p,
                           bias_segment(kNumL - 1, hb), hb, grad + s.head_w, c->stream),
                  "head backward"));
-    written[D0] = true;
+    int db = 0;             // the masked gradient of the layer at hand is in dpre[db]
+    bool masked = true;     // and has been written there already
     for (int L = kNumL - 1; L >= 0; --L) {
         const LayerDef& d = kLayers[L];
         const ConvShape sh = layer_shape(s, L, n);
@@ -464,31 +464,36 @@ sg_status backward(sg_ctx* c, Surrogate& s, int n)
             SG_TRY(check(s.parts.ensure(sizeof(float) * (size_t)pb * kScanC * kTC[kScanSrc]), "depth map workspace"));
             SG_TRY(check(proj_bwd((const uint16_t*)s.dscan.p, (const uint16_t*)s.act[kScanSrc].p,
                                   (const uint16_t*)s.wb.p + s.proj_w, (const float*)s.gact[kScanDst].p, kTC[kScanDst],
-                                  (const uint16_t*)s.act[d.out].p, (float*)s.gact[kScanSrc].p, (uint16_t*)s.dpre.p, P,
+                                  (const uint16_t*)s.act[d.out].p, (float*)s.gact[kScanSrc].p, (uint16_t*)s.dpre[db].p, P,
                                   kScanC, kTC[kScanSrc], (float*)s.parts.p, bias_segment(L, pb), grad + s.proj_w,
                                   c->stream),
                          "depth map backward"));
-            written[kScanSrc] = true;
-        } else if (L < kNumL - 1) {   // ReLU mask and the bias gradient's partials
+            skip_g[kScanSrc] = (const float*)s.gact[kScanSrc].p;
+        } else if (!masked) {   // ReLU mask and the bias gradient's partials
             const int mb = blocks_for(rows * d.Co / 2, 1024);   // about four rows per thread
             SG_TRY(check(mask_colsum((const float*)s.gact[go].p, kTC[go], (const uint16_t*)s.act[d.out].p,
-                                     (uint16_t*)s.dpre.p, rows, d.Co, bias_segment(L, mb), mb, nullptr, c->stream),
+                                     (uint16_t*)s.dpre[db].p, rows, d.Co, bias_segment(L, mb), mb, nullptr, c->stream),
                          "relu mask and bias partials"));
         }
-        if (d.skip >= 0 && go != kScanDst) {   // (S0's part is added by the depth map's backward)
-            // out2 = out + skip: the skip tensor receives the same gradient
-            SG_TRY(check(hipMemcpyAsync(s.gact[d.skip].p, s.gact[go].p, sizeof(float) * n_out,
-                                        hipMemcpyDeviceToDevice, c->stream),
-                         "skip gradient"));
-            written[d.skip] = true;
-        }
-        SG_TRY(wgrad(c, sh, (const uint16_t*)s.act[d.in].p, (const uint16_t*)s.dpre.p, grad + s.w_off[L], nullptr,
+        // out2 = out + skip: the skip tensor receives the same gradient (S0's part is in E0's already)
+        if (d.skip >= 0 && go != kScanDst) skip_g[d.skip] = (const float*)s.gact[go].p;
+        SG_TRY(wgrad(c, sh, (const uint16_t*)s.act[d.in].p, (const uint16_t*)s.dpre[db].p, grad + s.w_off[L], nullptr,
                      s.parts));
-        if (L > 0) {
-            SG_TRY(dgrad(c, sh, (const uint16_t*)s.dpre.p, (const uint16_t*)s.wt.p + s.w_off[L],
-                         (float*)s.gact[d.in].p, written[d.in] ? 1 : 0));
-            written[d.in] = true;
+        if (L == 0) break;
+        // d.in is the output (or skip-added output) of layer L - 1; where the tiled kernel computes its gradient, that
+        // layer's masked one comes with it
+        const LayerDef& e = kLayers[L - 1];
+        DpreArgs m;
+        if (kTC[d.in] == e.Co && dgrad_tile_supported(geom_of(sh, 1))) {
+            const int64_t tb = conv_tile_blocks(n, sh.Hin(), sh.Win());
+            m.mask = (const uint16_t*)s.act[e.out].p;
+            m.dpre = (uint16_t*)s.dpre[db ^ 1].p;
+            m.colsum = bias_segment(L - 1, (int)tb);
         }
+        SG_TRY(dgrad(c, sh, (const uint16_t*)s.dpre[db].p, (const uint16_t*)s.wt.p + s.w_off[L],
+                     (float*)s.gact[d.in].p, skip_g[d.in], m));
+        masked = m.dpre != nullptr;
+        if (masked) db ^= 1;
     }
     return check(reduce_segments((const float*)s.bias_parts.p, grad, bseg, c->stream), "bias gradients");
 }
@@ -668,7 +673,7 @@ sg_status disc_backward(sg_ctx* c, Surrogate& s, const uint16_t* z, int frames, 
             SG_TRY(wgrad(c, sh, x, (const uint16_t*)s.d_dpre.p, grad + s.dw_off[L], nullptr, s.parts));
         if (L > 0 || input_grad)
             SG_TRY(dgrad(c, sh, (const uint16_t*)s.d_dpre.p, (const uint16_t*)s.d_wt.p + s.dw_off[L],
-                         (float*)s.d_g[L].p + disc_at(s, L, off), 0));
+                         (float*)s.d_g[L].p + disc_at(s, L, off), nullptr));
     }
     return SG_OK;
 }
@@ -803,7 +808,7 @@ extern "C" sg_status sg_conv_backward_data(sg_ctx* c, const sg_conv_desc* d, con
     const int taps = sh.k * sh.k;
     SG_TRY(check(c->op_wt.ensure(sizeof(uint16_t) * (size_t)sh.Co * taps * sh.C), "weight workspace"));
     SG_TRY(check(transpose_w(w, (uint16_t*)c->op_wt.p, sh.Co, taps, sh.C, c->stream), "weight transpose"));
-    return dgrad(c, sh, dy, (const uint16_t*)c->op_wt.p, dx, accumulate ? 1 : 0);
+    return dgrad(c, sh, dy, (const uint16_t*)c->op_wt.p, dx, accumulate ? dx : nullptr);
 }
 
 extern "C" sg_status sg_conv_backward_weight(sg_ctx* c, const sg_conv_desc* d, const uint16_t* x, const uint16_t* dy,
@@ -972,7 +977,7 @@ namespace {
 // every buffer a training step touches: a captured step stays valid while none of them moved
 std::vector<const void*> buffer_ptrs(const Surrogate& s)
 {
-    std::vector<const void*> v = {s.master.p, s.mom1.p, s.mom2.p, s.grad.p, s.wb.p, s.wt.p, s.dpre.p,
+    std::vector<const void*> v = {s.master.p, s.mom1.p, s.mom2.p, s.grad.p, s.wb.p, s.wt.p, s.dpre[0].p, s.dpre[1].p,
                                   s.parts.p, s.yhat.p, s.target.p, s.gy.p, s.loss.p, s.dscan.p, s.steps.p, s.coef.p,
                                   s.segs.p, s.hist.p, s.bias_parts.p, s.d_master.p, s.d_mom1.p, s.d_mom2.p, s.d_grad.p, s.d_wb.p,
                                   s.d_wt.p, s.d_logits.p, s.d_glog.p, s.d_dpre.p, s.d_bias_scratch.p, s.d_segs.p};

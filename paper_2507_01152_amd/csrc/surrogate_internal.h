@@ -60,7 +60,7 @@ struct ConvArgs {
     int32_t ld_out2;         // channels per pixel of out2 (0: Co); out2 may be wider than the conv's output
     uint16_t* out_bf16;      // forward
     float* out_f32;          // forward (optional), data gradient, weight gradient partials
-    int32_t accumulate;      // data gradient: add into out_f32
+    const float* add;        // data gradient: added to out_f32 (its own old values or another tensor; may be null)
     int64_t k_chunk;         // weight gradient: pixels per split (multiple of 32)
     // forward, tiled 3x3 path only (conv_tile_supported): fused 1x1 head with one output,
     // head_out[pixel] = head_b[0] + sum_co head_w[co] * bf16(out[pixel][co])
@@ -77,6 +77,11 @@ struct ConvArgs {
     // tiled 3x3 path only, with out_f32: the output's 2 x 2 blocks summed into one pixel of a half-size
     // out_f32 (the data gradient of an upsampled input); Ho and Wo even
     int32_t pool2;
+    // tiled data gradient only, unless dpre is null: dpre = bf16(out_f32 [mask > 0]) (bf16 tensors of out_f32's
+    // shape) and each block's column sums of dpre, colsum[block][Co]
+    const uint16_t* mask;
+    uint16_t* dpre;
+    float* colsum;
 };
 
 // convolution shape of one layer (per batch)
@@ -156,15 +161,22 @@ bool conv_tile_supported(const ConvGeom& g);
 // data gradient of a 3x3 pad-1 conv (g: the layer's mode-1 geometry; stride 1, or stride 2 with even input
 // sizes) as a forward tiled conv of dy with mirrored taps, over dy dilated by zeros for stride 2: dx
 // [N][H][W][C] FP32 at the stored input resolution (an upsampled layer's fine-resolution gradient summed
-// over 2 x 2 blocks in the epilogue), written or accumulated
+// over 2 x 2 blocks in the epilogue), plus add unless null; and the masked gradient of the layer below unless m.dpre is
+// null (see ConvArgs; conv_tile_blocks(N, Hin, Win) partial column sums)
+struct DpreArgs {
+    const uint16_t* mask = nullptr;
+    uint16_t* dpre = nullptr;
+    float* colsum = nullptr;
+};
+int64_t conv_tile_blocks(int64_t N, int H, int W);   // blocks of the tiled conv of N H x W outputs
 bool dgrad_tile_supported(const ConvGeom& g);
 // data gradient of a stride-2, pad-1 3x3 conv (g: mode-1 geometry) as four implicit GEMMs, one per output
 // parity class, each over only the taps that reach it (a quarter of the full gather's products)
 bool dgrad_parity_supported(const ConvGeom& g);
-hipError_t dgrad_parity(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, int accumulate,
+hipError_t dgrad_parity(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, const float* add,
                         hipStream_t s);
-hipError_t dgrad_tile(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, int accumulate,
-                      hipStream_t s);
+hipError_t dgrad_tile(const ConvGeom& g, const uint16_t* dy, const uint16_t* wt, float* dx, const float* add,
+                      const DpreArgs& m, hipStream_t s);
 int wgrad_tile_m(int M);
 // direct 3x3 weight gradient (stride 1 or 2, pad 1; C in {8, 16, 24, 32} or a multiple of 32, Co in {16, 32}
 // or a multiple of 32, the wider ones for outputs at least 16 wide): gx x gy x gz blocks (gy input and gz
