@@ -1240,7 +1240,7 @@ __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, Co
 // tile with a halo of two pixels and both weights (DMA), computes the 18 x 34 pixels of the tensor between that
 // its 16 x 32 outputs need into LDS (bf16, zero outside the image, the second conv's padding) and continues from
 // there; the halo costs a fifth of the first conv again.  K order and roundings are k_conv3x3_tile's: same bits.
-// 41943040 pixels, 8 -> 16 -> 16 channels: 333 + 453 us as two passes, 549 us here; 32 upsampled -> 16 (+ 8) -> 16
+// 33554432 pixels, 8 -> 16 -> 16 channels: 333 + 453 us as two passes, 549 us here; 32 upsampled -> 16 (+ 8) -> 16
 // and the head: 759 + 545 and 54 us for the clamp, 1140 us here (LDS reads bound it now: a 16-channel product
 // needs one read each).  64 upsampled -> 32 -> 32 on a quarter of the pixels takes 131 KB of LDS, one block per
 // compute unit, and is slower (893 against 386 + 266 us), so those stay apart.
@@ -2513,20 +2513,35 @@ __global__ void k_transpose_w(const uint16_t* w, uint16_t* wt, int Co, int taps,
     }
 }
 
-// PSNR of clamp(yhat frame idx[b], 0, 1) against target frame b (peak 1)
-__global__ void k_psnr_idx(const float* yhat, const float* y, const int32_t* idx, int64_t frame, float* psnr)
+// PSNR of clamp(yhat frame idx[b], 0, 1) against target frame b (peak 1).  One block per frame, few of them: bound
+// by the latency of its loads, so 1024 threads with four pixels each in flight (8 frames of 32768 pixels: with 256
+// threads and one 54 us, now 9)
+__global__ __launch_bounds__(1024) void k_psnr_idx(const float* __restrict__ yhat, const float* __restrict__ y,
+                                                   const int32_t* __restrict__ idx, int64_t frame,
+                                                   float* __restrict__ psnr)
 {
-    __shared__ float red[256];
+    constexpr int NT = 1024, U = 4;
+    __shared__ float red[NT];
     const float* a = yhat + (int64_t)idx[blockIdx.x] * frame;
     const float* b = y + (int64_t)blockIdx.x * frame;
     float s = 0.f;
-    for (int64_t i = threadIdx.x; i < frame; i += blockDim.x) {
-        const float d = fminf(fmaxf(a[i], 0.f), 1.f) - b[i];
-        s += d * d;
+    for (int64_t i0 = threadIdx.x; i0 < frame; i0 += U * NT) {
+        float av[U], bv[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t i = min(i0 + k * NT, frame - 1);
+            av[k] = a[i];
+            bv[k] = b[i];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const float d = fminf(fmaxf(av[k], 0.f), 1.f) - bv[k];
+            if (i0 + k * NT < frame) s += d * d;
+        }
     }
     red[threadIdx.x] = s;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
+    for (int st = NT / 2; st > 0; st >>= 1) {
         if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
         __syncthreads();
     }
@@ -3073,7 +3088,7 @@ hipError_t psnr_indexed(const float* yhat, const float* y, const int32_t* idx, i
                         float* psnr, hipStream_t s)
 {
     if (n_frames <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_psnr_idx, dim3(n_frames), dim3(256), 0, s, yhat, y, idx, frame, psnr);
+    hipLaunchKernelGGL(k_psnr_idx, dim3(n_frames), dim3(1024), 0, s, yhat, y, idx, frame, psnr);
     return hipGetLastError();
 }
 

