@@ -2409,27 +2409,26 @@ __global__ void k_adam_coef(int64_t* steps, float* coef, float lr, float b1, flo
 
 // Adam over a parameter vector made of segments (one launch for all of a
 // network's tensors): block b works on kAdamChunk elements of the segment
-// whose block0 <= b; a weight segment also refreshes its bf16 copy and,
-// with a transpose, the [Ci][taps][Co] copy of the data gradient
-constexpr int kAdamChunk = 2048;
+// whose block0 <= b; a weight segment also refreshes its bf16 copy.  One with
+// a transpose (the [Ci][taps][Co] copy of the data gradient) is dealt out in
+// tiles of 32 output x 32 input channels of one tap, so that the transpose is
+// written in runs of 64 bytes: written element by element, each in a line of
+// its own that blocks on several XCDs share, 2.4 million parameters took 47 us,
+// now 15.
+constexpr int kAdamChunk = 2048, kAdamTile = 32;
 __global__ __launch_bounds__(256) void k_adam_multi(const AdamSeg* __restrict__ segs, int nseg, float* w, float* m,
                                                     float* v, const float* __restrict__ g, uint16_t* wb, uint16_t* wt,
                                                     const float* __restrict__ coef, int ci, float b1, float b2,
                                                     float eps)
 {
     __shared__ int s_seg;
-    if (threadIdx.x == 0) {
-        int k = 0;
-        while (k + 1 < nseg && segs[k + 1].block0 <= (int)blockIdx.x) ++k;
-        s_seg = k;
-    }
+    __shared__ uint16_t tile[kAdamTile][kAdamTile + 1];
+    for (int k = threadIdx.x; k < nseg; k += 256)   // (one thread walking the table waited for each entry)
+        if (segs[k].block0 <= (int)blockIdx.x && (k + 1 == nseg || segs[k + 1].block0 > (int)blockIdx.x)) s_seg = k;
     __syncthreads();
     const AdamSeg sg = segs[s_seg];
     const float lr = coef[0], c1 = coef[ci], c2 = coef[ci + 1];
-    const int64_t base = (int64_t)((int)blockIdx.x - sg.block0) * kAdamChunk;
-    const int64_t end = min(base + (int64_t)kAdamChunk, sg.n);
-    for (int64_t j = base + threadIdx.x; j < end; j += 256) {
-        const int64_t i = sg.off + j;
+    auto update = [&](int64_t i) __attribute__((always_inline)) -> float {
         const float gi = g[i];
         const float mi = b1 * m[i] + (1.f - b1) * gi;
         const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
@@ -2437,18 +2436,34 @@ __global__ __launch_bounds__(256) void k_adam_multi(const AdamSeg* __restrict__ 
         v[i] = vi;
         const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
         w[i] = wi;
-        if (sg.bf16) {
-            const uint16_t bb = f2bf(wi);
-            wb[i] = bb;
-            if (sg.transpose) {
-                // j = (co * taps + t) * Ci + ci  ->  (ci * taps + t) * Co + co
-                const int cc = (int)(j % sg.Ci);
-                const int64_t q = j / sg.Ci;
-                const int t = (int)(q % sg.taps);
-                const int co = (int)(q / sg.taps);
-                wt[sg.off + ((int64_t)cc * sg.taps + t) * sg.Co + co] = bb;
-            }
+        return wi;
+    };
+    const uint32_t b = (uint32_t)blockIdx.x - (uint32_t)sg.block0;
+    if (!sg.transpose) {
+        const int64_t base = (int64_t)b * kAdamChunk;
+        const int64_t end = min(base + (int64_t)kAdamChunk, sg.n);
+        for (int64_t j = base + threadIdx.x; j < end; j += 256) {
+            const float wi = update(sg.off + j);
+            if (sg.bf16) wb[sg.off + j] = f2bf(wi);
         }
+        return;
+    }
+    // element (co, t, ci) at (co * taps + t) * Ci + ci, transposed at (ci * taps + t) * Co + co
+    const uint32_t nci = ((uint32_t)sg.Ci + kAdamTile - 1) / kAdamTile, q = b / nci, tc = q / (uint32_t)sg.taps;
+    const int ci0 = (int)(b - q * nci) * kAdamTile, t = (int)(q - tc * (uint32_t)sg.taps), co0 = (int)tc * kAdamTile;
+    for (int e = threadIdx.x; e < kAdamTile * kAdamTile; e += 256) {
+        const int r = e / kAdamTile, c = e % kAdamTile;
+        if (co0 + r >= sg.Co || ci0 + c >= sg.Ci) continue;
+        const int64_t i = sg.off + ((int64_t)(co0 + r) * sg.taps + t) * sg.Ci + ci0 + c;
+        const uint16_t bb = f2bf(update(i));
+        wb[i] = bb;
+        tile[r][c] = bb;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < kAdamTile * kAdamTile; e += 256) {
+        const int c = e / kAdamTile, r = e % kAdamTile;
+        if (co0 + r >= sg.Co || ci0 + c >= sg.Ci) continue;
+        wt[sg.off + ((int64_t)(ci0 + c) * sg.taps + t) * sg.Co + co0 + r] = tile[r][c];
     }
 }
 
@@ -3046,7 +3061,11 @@ hipError_t add_channel(float* gy, const float* dz, int ld, int c, int64_t P, hip
     return hipGetLastError();
 }
 
-int adam_blocks(int64_t n) { return (int)((n + kAdamChunk - 1) / kAdamChunk); }
+int adam_blocks(const AdamSeg& a)
+{
+    if (!a.transpose) return (int)((a.n + kAdamChunk - 1) / kAdamChunk);
+    return (a.Co + kAdamTile - 1) / kAdamTile * a.taps * ((a.Ci + kAdamTile - 1) / kAdamTile);
+}
 
 hipError_t adam_coef(int64_t* steps, float* coef, float lr, float b1, float b2, int disc, hipStream_t s)
 {

@@ -521,7 +521,7 @@ void add_seg(std::vector<AdamSeg>& t, int& blocks, int64_t off, int64_t n, int C
     a.bf16 = bf16 ? 1 : 0;
     a.transpose = transpose ? 1 : 0;
     t.push_back(a);
-    blocks += adam_blocks(n);
+    blocks += adam_blocks(a);
 }
 
 hipError_t upload_segs(DevBuf& d, const std::vector<AdamSeg>& t)

@@ -244,14 +244,14 @@ hipError_t head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float*
 hipError_t l1_loss(const float* yhat, const float* y, int64_t n, float* grad, float* part, int blocks, float* loss,
                    hipStream_t s);
 // Adam: the step counters and per-step scalars live on the device (coef = {lr, c1, c2, disc c1, disc c2});
-// one launch updates all segments of a parameter vector (blocks = sum of adam_blocks(n) over segments)
+// one launch updates all segments of a parameter vector (blocks = sum of adam_blocks over segments)
 struct AdamSeg {
     int64_t off, n;          // element range of the segment in the parameter vector
     int32_t block0;          // first block of the segment
     int32_t Co, taps, Ci;    // weight layout [Co][taps][Ci] (transpose only)
-    int32_t bf16, transpose; // refresh the bf16 copy; also its [Ci][taps][Co] transpose
+    int32_t bf16, transpose; // refresh the bf16 copy; also (with it) its [Ci][taps][Co] transpose
 };
-int adam_blocks(int64_t n);
+int adam_blocks(const AdamSeg& a);   // (n = Co taps Ci with a transpose)
 hipError_t adam_coef(int64_t* steps, float* coef, float lr, float b1, float b2, int disc, hipStream_t s);
 hipError_t adam_multi(const AdamSeg* segs, int nseg, int blocks, float* w, float* m, float* v, const float* g,
                       uint16_t* wb, uint16_t* wt, const float* coef, int ci, float b1, float b2, float eps,
