@@ -1070,18 +1070,22 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 // pixels x 32 channels; K runs over taps and channels in the GEMM's order, so the results are its bits.  Bound by
 // LDS reads (six for eight products) and the steps' latency; 131072 pixels of 128 -> 64 upsampled 28.4 -> 23.5 us,
 // of 64 -> 64 22.6 -> 15.8 us.
+// MODE kDgrad, the data gradient of such a layer: a is dy, b the [Ci][9][Co] copy, tap (r, s) reads dy at
+// (2 - r, 2 - s) of the halo; FP32 output plus add, with pool2 (an upsampled input's gradient) summed over 2 x 2
+// pixels, a lane's four sums.  Against the GEMM, 131072 pixels: 64 -> 64 28.0 -> 20.5 us, 128 -> 64 upsampled 38.1 ->
+// 26.0 us (with stores that test the image's edge one by one it was no faster than the GEMM).
 // The 16 rows of an MFMA operand are 2 x 8 pixels in 2 x 2 quads (row 4 q + 2 dy + dx): with UP four of them read
 // one or two stored pixels.
 constexpr int kHaloT = 16, kHaloN = 64, kHaloK = 64, kHaloThreads = 512;
 
-template <int C, bool UP>
+template <int MODE, int C, bool UP>
 __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, ConvArgs a)
 {
     constexpr int XC = UP ? kHaloT / 2 + 2 : kHaloT + 2, C8 = C / 8;   // staged rows and columns
     constexpr int NX = XC * XC * C8, NXP = (NX + 63) / 64 * 64;        // 16-byte chunks of the halo
     constexpr int SW = kHaloN * kHaloK;                                // bf16 of a weight stage
     constexpr int TP = kHaloN + 8;                                     // row of the output tile
-    constexpr int OPS = NXP * 8 + 3 * SW, OUT = kHaloT * kHaloT * TP;
+    constexpr int OPS = NXP * 8 + 3 * SW, OUT = MODE == kFwd ? kHaloT * kHaloT * TP : 0;
     static_assert(C % kHaloK == 0 && (kHaloN * kHaloK) / 8 == kHaloThreads, "one weight chunk per thread and step");
     __shared__ __attribute__((aligned(16))) uint16_t smem[OPS > OUT ? OPS : OUT];
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1119,7 +1123,7 @@ __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, Co
     auto issue = [&](int kt, int st) __attribute__((always_inline)) { dma16(wsrc + kt * kHaloK, sW + st * SW + wv * 512); };
     float bias_r[2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) bias_r[j] = a.bias ? a.bias[n_base + wn * 32 + j * 16 + lr] : 0.f;
+    for (int j = 0; j < 2; ++j) bias_r[j] = (MODE == kFwd && a.bias) ? a.bias[n_base + wn * 32 + j * 16 + lr] : 0.f;
     f32x4 acc[4][2];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -1134,7 +1138,7 @@ __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, Co
     int st = 0, st2 = 2, kt = 0;
 #pragma unroll 1
     for (int t = 0; t < 9; ++t) {
-        const int r = t / 3, s = t % 3;
+        const int r = MODE == kDgrad ? 2 - t / 3 : t / 3, s = MODE == kDgrad ? 2 - t % 3 : t % 3;
         // staged pixel of row tile 0 and its key; those of the others follow (i % 2: 8 columns on, UP 4; i / 2: 2
         // rows on, UP 1)
         const int sr = UP ? 2 * wm + ((rb + r + 1) >> 1) : 4 * wm + rb + r;
@@ -1174,6 +1178,48 @@ __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, Co
     }
     // lane (lr, lk), element e of acc[i][j]: output pixel (4 wm + 2 (i / 2) + e / 2, 8 (i % 2) + 2 lk + e % 2),
     // channel n_base + 32 wn + 16 j + lr
+    if constexpr (MODE == kDgrad) {
+        // (whole tiles only, so no store is conditional; what is added is all loaded before the first store)
+        const int64_t Co = g.Co;
+        const int ch = n_base + wn * 32 + lr;
+        if (a.pool2) {
+            const int W2 = g.Wo >> 1;
+            const int64_t o0 = (((int64_t)n * (g.Ho >> 1) + ho0 / 2 + 2 * wm) * W2 + wo0 / 2 + lk) * Co + ch;
+            float pre[4][2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    pre[i][j] = a.add ? a.add[o0 + ((i >> 1) * W2 + 4 * (i & 1)) * Co + 16 * j] : 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const float v = (acc[i][j][0] + acc[i][j][1]) + (acc[i][j][2] + acc[i][j][3]);
+                    a.out_f32[o0 + ((i >> 1) * W2 + 4 * (i & 1)) * Co + 16 * j] = a.add ? pre[i][j] + v : v;
+                }
+            return;
+        }
+        const int64_t o0 = (((int64_t)n * g.Ho + ho0 + 4 * wm) * g.Wo + wo0 + 2 * lk) * Co + ch;
+        auto at = [&](int i, int j, int e) __attribute__((always_inline)) {
+            return o0 + ((2 * (i >> 1) + (e >> 1)) * g.Wo + 8 * (i & 1) + (e & 1)) * Co + 16 * j;
+        };
+        if (a.add) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j][e] = a.add[at(i, j, e)] + acc[i][j][e];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a.out_f32[at(i, j, e)] = acc[i][j][e];
+        return;
+    }
     uint16_t* sT = smem;
     __syncthreads();
     auto write_tile = [&](auto act_c) __attribute__((always_inline)) {
@@ -2774,16 +2820,16 @@ bool halo_supported(const ConvGeom& g)
     return blocks >= 256 && !(g.C == 128 && !g.up && blocks >= 1024);
 }
 
-template <bool UP>
+template <int MODE, bool UP>
 hipError_t launch_halo(const ConvGeom& g, const ConvArgs& a, hipStream_t s)
 {
     const int64_t blocks = halo_blocks(g);
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
     const dim3 gr((unsigned)blocks), bl(kHaloThreads);
-    if (g.C == 64) hipLaunchKernelGGL((k_conv3x3_halo<64, UP>), gr, bl, 0, s, g, a);
-    else if (g.C == 128) hipLaunchKernelGGL((k_conv3x3_halo<128, UP>), gr, bl, 0, s, g, a);
+    if (g.C == 64) hipLaunchKernelGGL((k_conv3x3_halo<MODE, 64, UP>), gr, bl, 0, s, g, a);
+    else if (g.C == 128) hipLaunchKernelGGL((k_conv3x3_halo<MODE, 128, UP>), gr, bl, 0, s, g, a);
     else {
-        if constexpr (UP) hipLaunchKernelGGL((k_conv3x3_halo<256, UP>), gr, bl, 0, s, g, a);
+        if constexpr (UP) hipLaunchKernelGGL((k_conv3x3_halo<MODE, 256, UP>), gr, bl, 0, s, g, a);
         else return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -2801,7 +2847,23 @@ hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits,
     if (mode == kFwd && conv_tile_supported(g))
         return g.Co == 16 ? launch_tile_co<16>(g, a, s) : launch_tile_co<32>(g, a, s);
     if (mode == kFwd && halo_supported(g))
-        return g.up ? launch_halo<true>(g, a, s) : launch_halo<false>(g, a, s);
+        return g.up ? launch_halo<kFwd, true>(g, a, s) : launch_halo<kFwd, false>(g, a, s);
+    if (mode == kDgrad && g.stride == 1 && g.kh == 3 && g.kw == 3 && g.pad == 1) {
+        ConvGeom f = g;   // the forward conv of dy
+        f.C = g.Co;
+        f.Co = g.C;
+        f.H = g.Ho;
+        f.W = g.Wo;
+        f.Ho = g.up ? 2 * g.H : g.H;
+        f.Wo = g.up ? 2 * g.W : g.W;
+        f.up = 0;
+        f.Kw = (g.Kw / ((int64_t)g.Ho * g.Wo)) * f.Ho * f.Wo;
+        if (f.Ho % kHaloT == 0 && f.Wo % kHaloT == 0 && halo_supported(f)) {
+            ConvArgs d = a;
+            d.pool2 = g.up;
+            return launch_halo<kDgrad, false>(f, d, s);
+        }
+    }
     if (mode == kWgrad) {
         if (g.M <= 16) return launch_gemm<kWgrad, 16, 128, 1, 4>(g, a, splits, s);
         if (g.M <= 32) return launch_gemm<kWgrad, 32, 128, 1, 4>(g, a, splits, s);
