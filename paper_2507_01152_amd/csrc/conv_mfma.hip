@@ -2459,7 +2459,7 @@ __global__ void k_adam_coef(int64_t* steps, float* coef, float lr, float b1, flo
 // a transpose (the [Ci][taps][Co] copy of the data gradient) is dealt out in
 // tiles of 32 output x 32 input channels of one tap, so that the transpose is
 // written in runs of 64 bytes: written element by element, each in a line of
-// its own that blocks on several XCDs share, 2.4 million parameters took 47 us,
+// its own that blocks on several XCDs share, 1.8 million parameters took 47 us,
 // now 15.
 constexpr int kAdamChunk = 2048, kAdamTile = 32;
 __global__ __launch_bounds__(256) void k_adam_multi(const AdamSeg* __restrict__ segs, int nseg, float* w, float* m,
