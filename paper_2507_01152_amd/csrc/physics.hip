@@ -566,16 +566,12 @@ __device__ void ray_scanline(const PhysArgs& a, const EnvDev& e, const VolDev& v
 }
 
 // Work items of the ray kernel: block b takes item b first (no atomic), then
-// the items that its counter hands out (QueueDev).  The counter's blocks are
-// b % kRayQueues, + kRayQueues, ...: their first items precede its further ones.
+// the items that its counter hands out (QueueDev, ray_item).
 __device__ __forceinline__ int next_item(QueueDev* q, int* s_item)
 {
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int g = (int)blockIdx.x % kRayQueues;
-        const int blocks = ((int)gridDim.x - g + kRayQueues - 1) / kRayQueues;
-        *s_item = g + kRayQueues * (blocks + atomicAdd(&q->q[g].next, 1));
-    }
+    if (threadIdx.x == 0)
+        *s_item = ray_item((int)blockIdx.x, (int)gridDim.x, atomicAdd(&q->q[blockIdx.x % kRayQueues].next, 1));
     __syncthreads();
     return *s_item;
 }
@@ -1190,8 +1186,8 @@ int psf_grid(int tx, int max_rlat, int n_cu)
 hipError_t launch_ray(const PhysArgs& a, QueueDev* q, int grid, hipStream_t s)
 {
     if (a.n_ray <= 0) return hipSuccess;
-    if (grid > a.n_ray) grid = a.n_ray;
     if (grid < 1) return hipErrorInvalidConfiguration;
+    grid = ray_blocks(grid, a.n_ray);
     const void* fn = a.multiscale ? ray_fn<true>(ray_label_only(a), ray_debug(a)) : ray_fn<false>(ray_label_only(a), ray_debug(a));
     void* args[] = {const_cast<PhysArgs*>(&a), &q};
     const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, 0, s);

@@ -95,6 +95,21 @@ struct QueueDev {
         int32_t pad[31];
     } q[kRayQueues];
 };
+// blocks of a ray kernel launch: one per item up to the resident ones, but at least one per counter, whose items
+// nobody takes otherwise (a small share of a GPU, or the chunked pipeline on one, may keep fewer resident; the
+// blocks beyond those run as the first ones leave)
+__host__ __device__ inline int ray_blocks(int resident, int n_ray)
+{
+    const int want = resident > kRayQueues ? resident : kRayQueues;
+    return want < n_ray ? want : n_ray;
+}
+// item that block b of `blocks` takes when its counter has handed out `taken` items: the first items of the
+// counter's blocks, b % kRayQueues, + kRayQueues, ..., precede them
+__host__ __device__ inline int ray_item(int b, int blocks, int taken)
+{
+    const int g = b % kRayQueues;
+    return g + kRayQueues * ((blocks - g + kRayQueues - 1) / kRayQueues + taken);
+}
 
 struct PhysArgs {
     const EnvDev* envs;
