@@ -143,7 +143,7 @@ PhysArgs plan_args(sg_ctx* c, Plan* p, float* out)
 // upload or the reconstruction kernels around it the queue stood still for 6 to
 // 8 us on either side.  Every chunk holds at least one env, so each ray kernel
 // is followed by a PSF kernel that clears its counter.
-hipError_t enqueue_step(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEvent_t* ev = nullptr)
+hipError_t enqueue_kernels(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEvent_t* ev)
 {
     QueueDev* q = (QueueDev*)p->d_queue.p;
     const int K = p->shape.chunks;
@@ -173,6 +173,20 @@ hipError_t enqueue_step(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEvent_
     if (e == hipSuccess) e = hipEventRecord(p->ev_join, p->aux);
     if (e == hipSuccess) e = hipStreamWaitEvent(s, p->ev_join, 0);
     if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
+    return e;
+}
+
+// the step's kernels; a step cut short leaves what a whole one does: everything joined to stream s (PSF kernels on
+// the second stream may still read the fields that the next step writes) and, after that, counters at zero (a ray
+// kernel may have run whose PSF kernel did not)
+hipError_t enqueue_step(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEvent_t* ev = nullptr)
+{
+    const hipError_t e = enqueue_kernels(c, p, out, s, ev);
+    if (e == hipSuccess) return e;
+    if (p->shape.chunks > 1 && (hipEventRecord(p->ev_join, p->aux) != hipSuccess ||
+                                hipStreamWaitEvent(s, p->ev_join, 0) != hipSuccess))
+        (void)hipStreamSynchronize(p->aux);
+    (void)launch_queue_reset((QueueDev*)p->d_queue.p, kMaxChunks, s);
     return e;
 }
 
@@ -322,11 +336,7 @@ extern "C" sg_status sg_batch_step_profiled(sg_ctx* c, int32_t id, float* out, f
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
     hipError_t e = hipSuccess;
     for (int i = 0; i < 3 && e == hipSuccess; ++i) e = hipEventCreate(&ev[i]);
-    if (e == hipSuccess) {
-        e = enqueue_step(c, p, out, c->stream, ev);
-        // a step cut short may leave a ray counter that no PSF kernel cleared
-        if (e != hipSuccess) (void)launch_queue_reset((QueueDev*)p->d_queue.p, kMaxChunks, c->stream);
-    }
+    if (e == hipSuccess) e = enqueue_step(c, p, out, c->stream, ev);
     if (e == hipSuccess) e = hipEventSynchronize(ev[2]);
     if (e == hipSuccess) e = hipEventElapsedTime(ms_ray, ev[0], ev[1]);
     if (e == hipSuccess) e = hipEventElapsedTime(ms_psf, ev[1], ev[2]);
@@ -343,10 +353,7 @@ extern "C" sg_status sg_batch_step(sg_ctx* c, int32_t id, float* out)
     sg_status s = step_checks(c, p);
     if (s != SG_OK) return s;
     const hipError_t e = enqueue_step(c, p, out, c->stream);
-    if (e == hipSuccess) return SG_OK;
-    // a step cut short may leave a ray counter that no PSF kernel cleared
-    (void)launch_queue_reset((QueueDev*)p->d_queue.p, kMaxChunks, c->stream);
-    return hip_fail(e, "step");
+    return e == hipSuccess ? SG_OK : hip_fail(e, "step");
 }
 
 extern "C" sg_status sg_batch_status(sg_ctx* c, int32_t id, int32_t* n_bad)
