@@ -440,14 +440,20 @@ extern "C" sg_status sg_autotune(sg_ctx* c, int32_t id, const char* cache_path)
     float best_us = 1e30f;
     for (const LaunchShape& shp : kShapes) {
         if (apply_shape(c, p, shp) != SG_OK) continue;
-        for (int w = 0; w < 3; ++w) (void)enqueue_step(c, p, (float*)scratch_out.p, c->stream);
-        const int reps = 10;
-        (void)hipEventRecord(t0, c->stream);
-        for (int r = 0; r < reps; ++r) (void)enqueue_step(c, p, (float*)scratch_out.p, c->stream);
-        (void)hipEventRecord(t1, c->stream);
-        if (hipEventSynchronize(t1) != hipSuccess) continue;
+        const int warm = 3, reps = 10;
+        hipError_t le = hipSuccess;   // a shape that cannot be launched is no candidate
+        for (int r = 0; r < warm + reps && le == hipSuccess; ++r) {
+            if (r == warm) le = hipEventRecord(t0, c->stream);
+            if (le == hipSuccess) le = enqueue_step(c, p, (float*)scratch_out.p, c->stream);
+        }
+        if (le == hipSuccess) le = hipEventRecord(t1, c->stream);
+        if (le == hipSuccess) le = hipEventSynchronize(t1);
         float ms = 0.f;
-        (void)hipEventElapsedTime(&ms, t0, t1);
+        if (le == hipSuccess) le = hipEventElapsedTime(&ms, t0, t1);
+        if (le != hipSuccess) {
+            (void)hipStreamSynchronize(c->stream);   // the next shape's work lists replace this one's
+            continue;
+        }
         const float us = 1000.f * ms / reps;
         if (us < best_us) {
             best_us = us;

@@ -197,10 +197,46 @@ static int failed_step()
     return 0;
 }
 
+// a launch shape whose steps fail is neither the tuner's choice nor in its cache, and leaves nothing behind
+static int failed_tuning(const char* cache)
+{
+    World w(8);
+    const int id = w.plan();
+    CHECK(id >= 0);
+    g_fail_tx = 64;
+    CHECK(sg_autotune(w.c, id, cache) == SG_OK);
+    g_fail_tx = 0;
+    int32_t spw, tx, ty, ch;
+    CHECK(sg_batch_config(w.c, id, &spw, &tx, &ty, &ch) == SG_OK && tx != 64);
+    CHECK(w.counters_zero(id));
+    std::ifstream f(cache);
+    std::string line;
+    int lines = 0;
+    while (std::getline(f, line)) {
+        ++lines;
+        CHECK(line.find("\"tx\": 64") == std::string::npos);
+    }
+    CHECK(lines == 1);
+    // every shape fails: the plan keeps its own, and nothing more is cached
+    World v(9);
+    const int iv = v.plan();
+    CHECK(sg_batch_set_config(v.c, iv, 8, 16, 1) == SG_OK);
+    g_fail_tx = -1;
+    CHECK(sg_autotune(v.c, iv, cache) == SG_OK);
+    g_fail_tx = 0;
+    CHECK(sg_batch_config(v.c, iv, &spw, &tx, &ty, &ch) == SG_OK && spw == 8 && tx == 16 && ch == 1);
+    CHECK(v.counters_zero(iv));
+    std::ifstream again(cache);
+    while (std::getline(again, line)) --lines;
+    CHECK(lines == 0);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string s = argc > 1 ? argv[1] : "";
     if (s == "failed_step") return failed_step();
+    if (s == "failed_tuning") return failed_tuning(argv[2]);
     std::printf("unknown scenario\n");
     return 2;
 }

@@ -28,3 +28,7 @@ def program(tmp_path_factory):
 
 def test_failed_step_leaves_nothing_behind(program):
     program("failed_step")
+
+
+def test_tuner_skips_shapes_that_fail(program, tmp_path):
+    program("failed_tuning", str(tmp_path / "tune.jsonl"))
