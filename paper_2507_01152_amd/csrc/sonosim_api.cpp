@@ -296,6 +296,15 @@ extern "C" sg_status sg_create(sg_ctx** out, int32_t device, void* stream)
         delete c;
         return hip_fail(e, "noise table upload");
     }
+    // the work counters start at zero, and every PSF kernel clears them for the next call.  Cleared here and not in
+    // the first call: that one may be recorded into a graph instead of run
+    e = c->queue.ensure(sizeof(QueueDev));
+    if (e == hipSuccess) e = hipMemset(c->queue.p, 0, sizeof(QueueDev));
+    if (e == hipSuccess) e = hipDeviceSynchronize();   // whatever stream the first call uses
+    if (e != hipSuccess) {
+        delete c;
+        return hip_fail(e, "work counters");
+    }
     *out = c;
     return SG_OK;
 }
@@ -572,10 +581,6 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
     std::memcpy(h + o_psf, tiles.data(), sizeof(ItemPsf) * tiles.size());
     if ((e = c->params.ensure(total)) != hipSuccess) return hip_fail(e, "hipMalloc params");
     if ((e = c->fields.ensure(sizeof(float) * 3 * (size_t)scr)) != hipSuccess) return hip_fail(e, "hipMalloc scratch");
-    if (!c->queue.p) {   // the work counter starts at zero; every PSF kernel clears it for the next call
-        if ((e = c->queue.ensure(sizeof(QueueDev))) == hipSuccess) e = launch_queue_reset((QueueDev*)c->queue.p, 1, c->stream);
-        if (e != hipSuccess) return hip_fail(e, "hipMalloc queue");
-    }
     if (slot) {
         e = launch_upload(c->params.p, h, total, c->stream);
         if (e == hipSuccess) e = hipEventRecord(slot->ev, c->stream);

@@ -232,10 +232,24 @@ static int failed_tuning(const char* cache)
     return 0;
 }
 
+// the counters of single calls are at zero once the context is there, whether or not its first call runs (a call
+// that a graph records does not)
+static int first_call()
+{
+    World w(2);
+    CHECK(w.c->queue.p);
+    for (const auto& q : ((const QueueDev*)w.c->queue.p)->q) CHECK(q.next == 0);
+    g_ops.clear();
+    CHECK(sg_simulate(w.c, w.n, w.vids.data(), w.probes.data(), w.poses.data(), w.out.data(), w.offs.data(), nullptr) == SG_OK);
+    for (const Op& o : g_ops) CHECK(o.what != "reset");
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string s = argc > 1 ? argv[1] : "";
     if (s == "failed_step") return failed_step();
+    if (s == "first_call") return first_call();
     if (s == "failed_tuning") return failed_tuning(argv[2]);
     std::printf("unknown scenario\n");
     return 2;

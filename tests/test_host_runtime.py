@@ -32,3 +32,7 @@ def test_failed_step_leaves_nothing_behind(program):
 
 def test_tuner_skips_shapes_that_fail(program, tmp_path):
     program("failed_tuning", str(tmp_path / "tune.jsonl"))
+
+
+def test_counters_are_clear_before_the_first_call(program):
+    program("first_call")
