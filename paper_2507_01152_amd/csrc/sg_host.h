@@ -23,24 +23,20 @@ struct DevBuf {
     hipError_t ensure(size_t bytes);   // grow-only; synchronises the device before a regrow
 };
 
-struct PinnedBuf {
-    void* p = nullptr;
-    size_t cap = 0;
-    hipEvent_t ev = nullptr;           // recorded after the last upload from this buffer
-    PinnedBuf() = default;
-    PinnedBuf(const PinnedBuf&) = delete;
-    PinnedBuf& operator=(const PinnedBuf&) = delete;
-    ~PinnedBuf();
-    hipError_t acquire(size_t bytes);  // waits for the previous upload, then grows
-};
-
-// Uploads of launch parameters and poses take the slots in turn, so a call waits for the upload of
-// kStagingSlots calls ago, not for the previous one.
+// Pinned staging of uploads (launch parameters, poses): kStagingSlots parts of one allocation, taken in turn, so a
+// call waits for the upload of kStagingSlots calls ago, not for the previous one.
 constexpr int kStagingSlots = 4;
 struct PinnedRing {
-    PinnedBuf slot[kStagingSlots];
-    int at = 0;
-    PinnedBuf& next() { return slot[at = (at + 1) % kStagingSlots]; }
+    void* p = nullptr;
+    size_t cap = 0;                           // bytes of a slot
+    hipEvent_t ev[kStagingSlots] = {};        // recorded after the last upload from each slot
+    int at = 0;                               // the slot last taken
+    PinnedRing() = default;
+    PinnedRing(const PinnedRing&) = delete;
+    PinnedRing& operator=(const PinnedRing&) = delete;
+    ~PinnedRing();
+    hipError_t acquire(size_t bytes, void** slot);   // the next slot, grown if need be (waits for its previous upload)
+    hipError_t uploaded(hipStream_t s);              // to be called when the slot's upload is enqueued
 };
 
 struct HostVolume {

@@ -18,6 +18,7 @@ struct Op {
     const void* b;   // event or counter
 };
 static std::vector<Op> g_ops;
+static std::vector<const void*> g_waited;   // events the host waited for
 static int g_pinned = 0;                   // pinned allocations
 static int g_fail_psf_at = -1;             // the PSF launch that fails (counted from 0), -1: none
 static int g_psf = 0;
@@ -63,7 +64,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
     *(size_t*)e = g_ops.size();   // "time": operations so far
     return op("record", s, e), hipSuccess;
 }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) { return g_waited.push_back(e), hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) { return *ms = 0.01f * (float)(*(size_t*)b - *(size_t*)a), hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { return op("wait", s, e), hipSuccess; }
 }
@@ -245,11 +246,43 @@ static int first_call()
     return 0;
 }
 
+// uploads past the by-value limit: one pinned allocation for a series of calls, slots in turn, each waited for
+// before it is written again, also where the sizes grow
+static int staging()
+{
+    World w(40);   // 3840 bytes of poses
+    const int id = w.plan();
+    CHECK(id >= 0);
+    g_pinned = 0;
+    for (int k = 0; k < 9; ++k) {
+        w.poses[12 * k + 3] = 0.5 * k;
+        g_ops.clear();
+        g_waited.clear();
+        CHECK(sg_batch_set_poses(w.c, id, w.poses.data()) == SG_OK);
+        CHECK(!std::memcmp(w.c->plans[id]->d_poses.p, w.poses.data(), 96 * 40));
+        // the event waited for is the one recorded after this slot's upload, and each slot has its own
+        CHECK(g_ops.size() == 2 && g_ops[0].what == "upload" && g_ops[1].what == "record");
+        CHECK(k < kStagingSlots || (!g_waited.empty() && g_waited.front() == g_ops[1].b));
+    }
+    CHECK(g_pinned == 1);
+    World v(200);
+    const int iv = v.plan();
+    g_pinned = 0;
+    for (int k = 0; k < 9; ++k) {
+        CHECK(sg_simulate(v.c, v.n, v.vids.data(), v.probes.data(), v.poses.data(), v.out.data(), v.offs.data(), nullptr) == SG_OK);
+        CHECK(sg_batch_set_poses(v.c, iv, v.poses.data()) == SG_OK);
+        CHECK(!std::memcmp(v.c->plans[iv]->d_poses.p, v.poses.data(), 96 * 200));
+    }
+    CHECK(g_pinned == 1);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string s = argc > 1 ? argv[1] : "";
     if (s == "failed_step") return failed_step();
     if (s == "first_call") return first_call();
+    if (s == "staging") return staging();
     if (s == "failed_tuning") return failed_tuning(argv[2]);
     std::printf("unknown scenario\n");
     return 2;

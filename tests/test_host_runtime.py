@@ -36,3 +36,7 @@ def test_tuner_skips_shapes_that_fail(program, tmp_path):
 
 def test_counters_are_clear_before_the_first_call(program):
     program("first_call")
+
+
+def test_pinned_staging_is_allocated_once(program):
+    program("staging")
