@@ -1850,6 +1850,23 @@ __global__ void k_mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out,
     }
 }
 
+// Frames replaced after an audit: frame pairs[k].y of out (and, unless null, of its bf16 copy) becomes frame
+// pairs[k].x of src, for every k in one launch (blockIdx.x = k).  Bound by the copy's
+// memory traffic; launched frame by frame, 256 of 1024 frames of 128 x 256 added 1.75 ms to an inference, now 0.10
+__global__ __launch_bounds__(256) void k_replace_frames(const float* __restrict__ src, const int2* __restrict__ pairs,
+                                                        int64_t frame, float* __restrict__ out,
+                                                        uint16_t* __restrict__ out_bf16)
+{
+    const int2 p = pairs[blockIdx.x];
+    const float* a = src + p.x * frame;
+    const int64_t o = p.y * frame;
+    for (int64_t i = (int64_t)blockIdx.y * 256 + threadIdx.x; i < frame; i += (int64_t)gridDim.y * 256) {
+        const float v = a[i];
+        out[o + i] = v;
+        if (out_bf16) out_bf16[o + i] = f2bf(v);
+    }
+}
+
 // Masked output gradient and bias-gradient partials in one pass over a
 // [rows][C] matrix: out = bf16(g * [y > 0]) (y may be null: no mask; out may
 // be null: g is already bf16 in gb), part[block][c] = sum of the block's rows
@@ -3053,6 +3070,16 @@ int proj_bwd_blocks() { return kProjBlocks; }
 hipError_t mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out, int64_t n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_mask_to_bf16, dim3((unsigned)grid_for(n)), dim3(256), 0, s, g, y, out, n);
+    return hipGetLastError();
+}
+
+hipError_t replace_frames(const float* src, const int2* pairs, int n, int64_t frame, float* out, uint16_t* out_bf16,
+                          hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    const int64_t by = std::min<int64_t>(64, (frame + 1023) / 1024);   // about four pixels a thread
+    hipLaunchKernelGGL(k_replace_frames, dim3((unsigned)n, (unsigned)by), dim3(256), 0, s, src, pairs, frame, out,
+                       out_bf16);
     return hipGetLastError();
 }
 

@@ -1278,17 +1278,15 @@ sg_status infer_impl(sg_ctx* c, Surrogate* s, int32_t n, const int32_t* vol_ids,
         if (out_bf16) SG_TRY(check(mask_to_bf16(out, nullptr, out_bf16, n * HW, c->stream), "bf16 frames"));
         *n_fallback = n;
     } else {
-        int nf = 0;
-        for (int i = 0; i < n_audit; ++i) {
-            if (!fb[i]) continue;
-            SG_TRY(check(hipMemcpyAsync(out + (int64_t)av[i] * HW, (const float*)s->target.p + (int64_t)i * HW,
-                                        sizeof(float) * HW, hipMemcpyDeviceToDevice, c->stream),
-                         "fallback copy"));
-            if (out_bf16)
-                SG_TRY(check(mask_to_bf16(out + (int64_t)av[i] * HW, nullptr, out_bf16 + (int64_t)av[i] * HW, HW,
-                                          c->stream),
-                             "bf16 frame"));
-            ++nf;
+        std::vector<int2> rep;   // (audited frame, frame it replaces)
+        for (int i = 0; i < n_audit; ++i)
+            if (fb[i]) rep.push_back(make_int2(i, av[i]));
+        const int nf = (int)rep.size();
+        if (nf > 0) {
+            SG_TRY(check(s->idx.ensure((sizeof(int2) * nf + 15) & ~size_t(15)), "fallback index"));
+            SG_TRY(upload(c, s->idx.p, rep.data(), sizeof(int2) * nf, "fallback index upload"));
+            SG_TRY(check(replace_frames((const float*)s->target.p, (const int2*)s->idx.p, nf, HW, out, out_bf16, c->stream),
+                         "fallback frames"));
         }
         *n_fallback = nf;
     }

@@ -190,6 +190,9 @@ int64_t wgrad_tile_part_floats(const WgradTilePlan& p);
 hipError_t wgrad_tile(const ConvGeom& g, const uint16_t* x, const uint16_t* dy, float* part, const WgradTilePlan& p,
                       float* dw, hipStream_t s);
 hipError_t mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out, int64_t n, hipStream_t s);
+// frame pairs[k].y of out (and of out_bf16 unless null) = frame pairs[k].x of src, k < n (device arrays)
+hipError_t replace_frames(const float* src, const int2* pairs, int n, int64_t frame, float* out, uint16_t* out_bf16,
+                          hipStream_t s);
 // out = bf16(g * (y > 0 ? 1 : slope)) over [rows][C] (y null: out = bf16(g)) and bias_grad[c] = sum of
 // out's column c (C <= 256); g has ldg floats per row (0: C)
 hipError_t mask_colsum(const float* g, int ldg, const uint16_t* y, uint16_t* out, int64_t rows, int C, float* part,
