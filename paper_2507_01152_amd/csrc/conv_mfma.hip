@@ -2888,32 +2888,24 @@ hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits,
     }
     // data gradient: four parity classes (g.par == 4), one per grid z
     const int nz = mode == kDgrad && g.par == 4 ? 4 : 1;
-    // the largest tile that still gives two blocks per compute unit: a larger tile fetches fewer operand bytes
-    // per product, but below that compute units stand idle and too few waves hide the operands' latency.  3x3
-    // layers of 128 -> 128 channels, forward, 128 x 128 / 128 x 64 / 64 x 64 tiles: 131072 pixels (1024 blocks
-    // of the largest) 58 / 72 / 86 us, 32768 pixels (256) 23 / 20 / 21 us, 16384 pixels (128) 22 / 17 / 16 us;
-    // 256 -> 256 channels on 4096 pixels (64): 38 / 28 / 23 us, 32 x 64 tiles 23 us, on 1024 pixels 37 / 27 /
-    // 22 / 19 us.
-    auto fills = [&](int bm, int bn) {
-        return ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * nz >= 512;
-    };
+    const GemmTile t = gemm_tile(g.M, g.N, nz);
     if (mode == kFwd) {
-        if (g.N <= 16)
-            return fills(256, 16) ? launch_gemm<kFwd, 256, 16, 4, 1>(g, a, 1, s) : launch_gemm<kFwd, 64, 16, 4, 1>(g, a, 1, s);
-        if (g.N <= 32)
-            return fills(128, 32) ? launch_gemm<kFwd, 128, 32, 4, 1>(g, a, 1, s) : launch_gemm<kFwd, 64, 32, 4, 1>(g, a, 1, s);
-        if (g.N > 64 && fills(128, 128)) return launch_gemm<kFwd, 128, 128, 2, 2>(g, a, 1, s);
-        if (fills(128, 64)) return launch_gemm<kFwd, 128, 64, 2, 2>(g, a, 1, s);
-        if (fills(64, 64)) return launch_gemm<kFwd, 64, 64, 1, 4>(g, a, 1, s);
+        if (t.bn == 16)
+            return t.bm == 256 ? launch_gemm<kFwd, 256, 16, 4, 1>(g, a, 1, s) : launch_gemm<kFwd, 64, 16, 4, 1>(g, a, 1, s);
+        if (t.bn == 32)
+            return t.bm == 128 ? launch_gemm<kFwd, 128, 32, 4, 1>(g, a, 1, s) : launch_gemm<kFwd, 64, 32, 4, 1>(g, a, 1, s);
+        if (t.bn == 128) return launch_gemm<kFwd, 128, 128, 2, 2>(g, a, 1, s);
+        if (t.bm == 128) return launch_gemm<kFwd, 128, 64, 2, 2>(g, a, 1, s);
+        if (t.bm == 64) return launch_gemm<kFwd, 64, 64, 1, 4>(g, a, 1, s);
         return launch_gemm<kFwd, 32, 64, 1, 4>(g, a, 1, s);
     }
-    if (g.N <= 16)
-        return fills(256, 16) ? launch_gemm<kDgrad, 256, 16, 4, 1>(g, a, nz, s) : launch_gemm<kDgrad, 64, 16, 4, 1>(g, a, nz, s);
-    if (g.N <= 32)
-        return fills(128, 32) ? launch_gemm<kDgrad, 128, 32, 4, 1>(g, a, nz, s) : launch_gemm<kDgrad, 64, 32, 4, 1>(g, a, nz, s);
-    if (g.N > 64 && fills(128, 128)) return launch_gemm<kDgrad, 128, 128, 2, 2>(g, a, nz, s);
-    if (fills(128, 64)) return launch_gemm<kDgrad, 128, 64, 2, 2>(g, a, nz, s);
-    if (fills(64, 64)) return launch_gemm<kDgrad, 64, 64, 2, 2>(g, a, nz, s);
+    if (t.bn == 16)
+        return t.bm == 256 ? launch_gemm<kDgrad, 256, 16, 4, 1>(g, a, nz, s) : launch_gemm<kDgrad, 64, 16, 4, 1>(g, a, nz, s);
+    if (t.bn == 32)
+        return t.bm == 128 ? launch_gemm<kDgrad, 128, 32, 4, 1>(g, a, nz, s) : launch_gemm<kDgrad, 64, 32, 4, 1>(g, a, nz, s);
+    if (t.bn == 128) return launch_gemm<kDgrad, 128, 128, 2, 2>(g, a, nz, s);
+    if (t.bm == 128) return launch_gemm<kDgrad, 128, 64, 2, 2>(g, a, nz, s);
+    if (t.bm == 64) return launch_gemm<kDgrad, 64, 64, 2, 2>(g, a, nz, s);
     return launch_gemm<kDgrad, 32, 64, 1, 4>(g, a, nz, s);
 }
 

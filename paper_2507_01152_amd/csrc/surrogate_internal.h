@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "conv_rules.h"
+
 namespace sg {
 
 // Division by a fixed divisor d (1 <= d < 2^31) for dividends n < 2^31 by one

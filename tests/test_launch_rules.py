@@ -21,6 +21,35 @@ def _run(tmp_path, name, body, headers=("sg_internal.h",)):
     return r.stdout
 
 
+# pixels, channels, classes: the tile measured fastest, or within 5 % of it (whole rounds of one and two blocks per
+# compute unit, ragged second rounds, every width)
+GEMM_TILES = [(32550, 128, 1, 128, 128), (35340, 128, 1, 128, 128), (65100, 128, 1, 128, 128), (25947, 128, 1, 128, 128),
+              (14880, 512, 1, 128, 128), (11904, 512, 1, 128, 128), (14880, 136, 1, 128, 128), (32550, 256, 1, 128, 128),
+              (56730, 72, 1, 128, 128), (131072, 128, 1, 128, 128), (131000, 1024, 1, 128, 128), (17670, 192, 1, 128, 64),
+              (21390, 192, 1, 128, 64), (8928, 136, 1, 64, 64), (6944, 256, 1, 64, 64), (11904, 128, 1, 64, 64),
+              (2976, 512, 1, 64, 64), (2976, 128, 4, 64, 64), (1488, 136, 1, 32, 64), (589, 136, 1, 32, 64), (63, 1024, 1, 32, 64),
+              (1, 72, 1, 32, 64), (131072, 64, 1, 128, 64), (65100, 64, 1, 128, 64), (56730, 64, 1, 128, 64), (32550, 64, 1, 64, 64),
+              (25947, 40, 1, 64, 64), (5000, 64, 1, 32, 64),
+              (8137, 64, 4, 64, 64), (130200, 32, 1, 128, 32), (56730, 24, 1, 128, 32), (26000, 32, 1, 64, 32),
+              (130200, 8, 1, 256, 16), (130200, 16, 1, 256, 16), (33000, 16, 1, 64, 16)]
+
+
+def test_gemm_tiles(tmp_path):
+    out = _run(tmp_path, "tiles", """
+int main()
+{
+    const long c[][3] = {%s};
+    for (auto& x : c) {
+        const GemmTile t = gemm_tile(x[0], x[1], (int)x[2]);
+        std::printf("%%d %%d\\n", t.bm, t.bn);
+    }
+    return 0;
+}
+""" % ", ".join("{%d, %d, %d}" % t[:3] for t in GEMM_TILES), ("conv_rules.h",))
+    got = [tuple(map(int, l.split())) for l in out.split("\n") if l]
+    assert got == [t[3:] for t in GEMM_TILES], [(t, g) for t, g in zip(GEMM_TILES, got) if g != t[3:]]
+
+
 def test_every_ray_item_has_a_block(tmp_path):
     """Each item is taken by one block, however few blocks a GPU keeps resident."""
     _run(tmp_path, "items", """
