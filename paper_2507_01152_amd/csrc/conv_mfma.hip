@@ -1076,7 +1076,7 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 // 26.0 us (with stores that test the image's edge one by one it was no faster than the GEMM).
 // The 16 rows of an MFMA operand are 2 x 8 pixels in 2 x 2 quads (row 4 q + 2 dy + dx): with UP four of them read
 // one or two stored pixels.
-constexpr int kHaloT = 16, kHaloN = 64, kHaloK = 64, kHaloThreads = 512;
+constexpr int kHaloK = 64, kHaloThreads = 512;   // (kHaloT, kHaloN: conv_rules.h)
 
 template <int MODE, int C, bool UP>
 __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, ConvArgs a)
@@ -2818,29 +2818,20 @@ hipError_t dgrad_parity(const ConvGeom& g, const uint16_t* dy, const uint16_t* w
 }
 
 namespace {
-int64_t halo_blocks(const ConvGeom& g)
-{
-    return (int64_t)((g.Ho + kHaloT - 1) / kHaloT) * ((g.Wo + kHaloT - 1) / kHaloT) *
-           (g.Kw / ((int64_t)g.Ho * g.Wo)) * (g.Co / kHaloN);   // Kw = N * Ho * Wo
-}
-
-// The halo kernel's layers.  Its blocks are large: below one per compute unit the GEMM's smaller tiles are as fast
-// (128 -> 64 upsampled, 128 blocks 13.4 against 12.9 us, 256 blocks 15.0 against 18.0, 4096 blocks 164 against 214).
-// 128 channels not upsampled take 107 KB of LDS, one block per compute unit: with many blocks the GEMM's 128 x 128
-// tiles are faster again (128 -> 128, 256 blocks 15.0 against 18.4 us, 512 28.2 against 30.0, 2048 106 against 102).
-bool halo_supported(const ConvGeom& g)
+// the halo kernel's layers: g is the forward conv (of dy as data gradient)
+bool halo_supported(const ConvGeom& g, bool dgrad)
 {
     const bool shape = g.kh == 3 && g.kw == 3 && g.stride == 1 && g.pad == 1 && g.Co % kHaloN == 0 &&
                        g.Ho == (g.up ? 2 * g.H : g.H) && g.Wo == (g.up ? 2 * g.W : g.W);
     if (!shape || g.Wo < kHaloT || g.Ho < kHaloT || !(g.C == 64 || g.C == 128 || (g.C == 256 && g.up))) return false;
-    const int64_t blocks = halo_blocks(g);
-    return blocks >= 256 && !(g.C == 128 && !g.up && blocks >= 1024);
+    if (dgrad && (g.Ho % kHaloT || g.Wo % kHaloT)) return false;
+    return halo_pays(dgrad, g.C, g.Co, g.up != 0, g.Kw / ((int64_t)g.Ho * g.Wo), g.Ho, g.Wo);   // Kw = N * Ho * Wo
 }
 
 template <int MODE, bool UP>
 hipError_t launch_halo(const ConvGeom& g, const ConvArgs& a, hipStream_t s)
 {
-    const int64_t blocks = halo_blocks(g);
+    const int64_t blocks = halo_blocks(g.Co, g.Kw / ((int64_t)g.Ho * g.Wo), g.Ho, g.Wo);
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
     const dim3 gr((unsigned)blocks), bl(kHaloThreads);
     if (g.C == 64) hipLaunchKernelGGL((k_conv3x3_halo<MODE, 64, UP>), gr, bl, 0, s, g, a);
@@ -2863,7 +2854,7 @@ hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits,
     if (a.dpre) return hipErrorInvalidValue;   // (the tiled data gradient's only)
     if (mode == kFwd && conv_tile_supported(g))
         return g.Co == 16 ? launch_tile_co<16>(g, a, s) : launch_tile_co<32>(g, a, s);
-    if (mode == kFwd && halo_supported(g))
+    if (mode == kFwd && halo_supported(g, false))
         return g.up ? launch_halo<kFwd, true>(g, a, s) : launch_halo<kFwd, false>(g, a, s);
     if (mode == kDgrad && g.stride == 1 && g.kh == 3 && g.kw == 3 && g.pad == 1) {
         ConvGeom f = g;   // the forward conv of dy
@@ -2875,7 +2866,7 @@ hipError_t conv_gemm(int mode, const ConvGeom& g, const ConvArgs& a, int splits,
         f.Wo = g.up ? 2 * g.W : g.W;
         f.up = 0;
         f.Kw = (g.Kw / ((int64_t)g.Ho * g.Wo)) * f.Ho * f.Wo;
-        if (f.Ho % kHaloT == 0 && f.Wo % kHaloT == 0 && halo_supported(f)) {
+        if (halo_supported(f, true)) {
             ConvArgs d = a;
             d.pool2 = g.up;
             return launch_halo<kDgrad, false>(f, d, s);

@@ -38,4 +38,32 @@ inline GemmTile gemm_tile(int64_t M, int64_t N, int nz)
     return b64 >= 128 ? GemmTile{64, 64} : GemmTile{32, 64};
 }
 
+// Blocks of the halo kernel: 16 x 16 output pixels of an image for 64 channels, each computed whole.
+constexpr int kHaloT = 16, kHaloN = 64;
+inline int64_t halo_blocks(int Co, int64_t images, int Ho, int Wo)
+{
+    return (int64_t)((Ho + kHaloT - 1) / kHaloT) * ((Wo + kHaloT - 1) / kHaloT) * images * (Co / kHaloN);
+}
+// Whether that kernel is faster than the GEMM (C input channels, those of dy as data gradient).  Below one block per
+// compute unit (256) the GEMM's smaller tiles are as fast (128 -> 64 upsampled, 128 blocks 13.4 against 12.9 us).  Its time
+// goes with the rounds of 256 blocks, the GEMM's with the output pixels, so what decides is the share of useful pixels in
+// whole rounds: half of them up to two rounds, 0.64 beyond (us, halo against GEMM; 64 -> 64: 256 images of 16 x 16, one
+// round, 10.3 and 12.0, 72 of 24 x 24, two rounds, 0.32, 11.8 and 10.2, 130 of them, three rounds, 0.38, 17.6 and 14.1;
+// 128 -> 64: 16 of 50 x 50, one round, 0.61, 12.8 and 14.8, 32 of 40 x 40, two rounds, 0.39, 22.9 and 15.8; 256 -> 64
+// upsampled: 16 of 50 x 50 19.4 and 23.8, 72 of 18 x 18, two rounds, 0.18, 28.7 and 18.9; 128 -> 64 upsampled, 4200 blocks 140
+// and 182).  128 channels not upsampled take 107 KB of LDS, one block per compute unit: with 128 outputs and more, where
+// the GEMM has its 128 x 128 tiles, one round or two nearly full ones (128 -> 128: 256 blocks 13.8 and 17.7, 330 23.9 and
+// 22.2, 504 of 0.94 24.2 and 27.3, 800 46.6 and 44.2), with 64 up to 1024 blocks.  As data gradient it takes whole tiles only and wins at any share
+// (128 -> 128, 290 blocks 26.2 and 27.4; 64 -> 64, 580 blocks 15.6 and 19.3).
+inline bool halo_pays(bool dgrad, int C, int Co, bool up, int64_t images, int Ho, int Wo)
+{
+    const int64_t blocks = halo_blocks(Co, images, Ho, Wo), rounds = (blocks + 255) / 256;
+    const bool wide = C == 128 && !up;
+    if (blocks < 256 || (wide && blocks >= 1024)) return false;
+    if (dgrad) return true;
+    const int64_t useful = images * Ho * Wo * (Co / kHaloN), whole = rounds * 256 * kHaloT * kHaloT;
+    if (wide && Co > kHaloN && rounds > 1) return rounds == 2 && 5 * useful >= 4 * whole;
+    return rounds <= 2 ? 2 * useful >= whole : 25 * useful >= 16 * whole;
+}
+
 }  // namespace sg

@@ -50,6 +50,32 @@ int main()
     assert got == [t[3:] for t in GEMM_TILES], [(t, g) for t, g in zip(GEMM_TILES, got) if g != t[3:]]
 
 
+# forward (0) or data gradient (1), channels in and out, upsampled, images, output size: whether the halo kernel was
+# faster than the GEMM (the lines of the rule aside, by 5 % or more)
+HALO = [(0, 64, 64, 0, 256, 16, 16, 1), (0, 64, 64, 0, 64, 17, 17, 0), (0, 64, 64, 0, 72, 17, 17, 0), (0, 64, 64, 0, 64, 31, 31, 1),
+        (0, 64, 64, 0, 72, 24, 24, 0), (0, 64, 64, 0, 130, 24, 24, 0), (0, 64, 64, 0, 26, 20, 68, 0), (0, 64, 64, 0, 525, 18, 30, 0),
+        (0, 64, 64, 0, 255, 16, 16, 0), (0, 64, 64, 0, 4200, 16, 16, 1), (0, 64, 128, 0, 32, 20, 68, 0), (0, 64, 128, 0, 16, 64, 64, 1),
+        (0, 128, 64, 0, 32, 20, 68, 0), (0, 128, 64, 0, 32, 40, 40, 0), (0, 128, 64, 0, 16, 50, 50, 1), (0, 128, 64, 0, 1008, 16, 16, 1),
+        (0, 128, 64, 0, 1024, 16, 16, 0), (0, 128, 64, 0, 200, 18, 30, 0), (0, 128, 128, 0, 64, 17, 17, 0), (0, 128, 128, 0, 32, 40, 40, 0),
+        (0, 128, 128, 0, 8, 100, 100, 0), (0, 128, 128, 0, 128, 16, 16, 1), (0, 128, 128, 0, 165, 16, 16, 0), (0, 128, 128, 0, 6, 96, 104, 1), (0, 128, 128, 0, 400, 24, 16, 0),
+        (0, 128, 512, 0, 16, 48, 20, 0), (0, 64, 64, 1, 200, 18, 18, 0), (0, 64, 64, 1, 64, 32, 32, 1), (0, 128, 64, 1, 200, 18, 30, 0),
+        (0, 128, 64, 1, 64, 32, 32, 1), (0, 256, 64, 1, 72, 18, 18, 0), (0, 256, 64, 1, 16, 50, 50, 1), (0, 256, 128, 1, 525, 18, 18, 0),
+        (1, 64, 64, 0, 290, 16, 16, 1), (1, 128, 128, 0, 300, 16, 16, 1), (1, 128, 64, 0, 1024, 16, 16, 0), (1, 64, 128, 0, 100, 16, 16, 0)]
+
+
+def test_halo_kernel_where_it_pays(tmp_path):
+    out = _run(tmp_path, "halo", """
+int main()
+{
+    const int c[][7] = {%s};
+    for (auto& x : c) std::printf("%%d\\n", (int)halo_pays(x[0], x[1], x[2], x[3], x[4], x[5], x[6]));
+    return 0;
+}
+""" % ", ".join("{%s}" % ", ".join(map(str, t[:7])) for t in HALO), ("conv_rules.h",))
+    got = [int(l) for l in out.split()]
+    assert got == [t[7] for t in HALO], [t for t, g in zip(HALO, got) if g != t[7]]
+
+
 def test_every_ray_item_has_a_block(tmp_path):
     """Each item is taken by one block, however few blocks a GPU keeps resident."""
     _run(tmp_path, "items", """
