@@ -98,7 +98,8 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
     static_assert(sizeof(ItemRay) == sizeof(ItemPsf), "one item array");
     const int64_t item_cap = (int64_t)((kParamBytes - o_items) / sizeof(ItemRay));
 
-    int64_t pool_used = 0, scr = 0, scanlines = 0;
+    int64_t pool_used = 0, scr = 0;
+    Extent extent;
     int n_int = 0, max_rlat = 0, multiscale = 0, any_ct = 0;
     for (int i = 0; i < n; ++i) {
         for (int k = 0; k < 12; ++k)
@@ -117,7 +118,7 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
                 return fail(SG_ERANGE, "env %d plane %d: image plane outside the fixed-point range (|Q16| > 2^30)",
                             i, j);
             scr += (int64_t)probes[i].W * ed.ld;
-            scanlines += probes[i].W;
+            extent.add(probes[i].W, probes[i].H);
             max_rlat = std::max(max_rlat, ed.rlat);
             ++n_int;
         }
@@ -135,7 +136,7 @@ extern "C" sg_status sg_simulate_noalloc(sg_ctx* c, int32_t n, const int32_t* vo
         return x < y;
     });
     // work lists of sg_simulate's launch shape
-    const LaunchShape shape = default_shape(scanlines, c->n_cu);
+    const LaunchShape shape = default_shape(extent, max_rlat, c->n_cu);
     const int tile = shape.tx, group = kRayWaves * shape.spw;
     ItemRay* rays = reinterpret_cast<ItemRay*>(g_stage + o_items);
     int64_t nr = 0;

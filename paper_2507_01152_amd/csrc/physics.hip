@@ -1132,17 +1132,14 @@ const void* psf_fn(int tx)
     return nullptr;
 }
 
-// resident blocks per compute unit; `known` keeps the answer of each (kernel, LDS size), the same on every
-// gfx950 (the query costs a single call about 2 us per kernel)
-int blocks_per_cu(const void* fn, int threads, size_t lds, std::atomic<int>& known)
+// resident blocks per compute unit (0: the kernel does not fit)
+int blocks_per_cu(const void* fn, int threads, size_t lds)
 {
-    int n = known.load(std::memory_order_relaxed);
-    if (n > 0) return n;
-    n = 0;
-    if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds) != hipSuccess) return 0;
-    known.store(n, std::memory_order_relaxed);
-    return n;
+    int n = 0;
+    return fn && hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds) == hipSuccess ? n : 0;
 }
+
+constexpr size_t kLdsBytes = 160 * 1024;   // of a compute unit
 
 // PSF block size: one wave per 8-column strip of the tile
 constexpr int psf_threads(int tx) { return tx / kSx * kWave; }
@@ -1171,8 +1168,12 @@ const void* ray_fn(bool label_only, bool debug)
 int ray_grid(int n_cu, bool multiscale, bool label_only, bool debug)
 {
     const void* fn = multiscale ? ray_fn<true>(label_only, debug) : ray_fn<false>(label_only, debug);
+    // the answer of each instantiation is kept, the same on every gfx950 (the query costs a single call about 2 us)
     static std::atomic<int> known[8];
-    return blocks_per_cu(fn, kThreads, 0, known[4 * multiscale + 2 * label_only + debug]) * n_cu;
+    std::atomic<int>& k = known[4 * multiscale + 2 * label_only + debug];
+    int n = k.load(std::memory_order_relaxed);
+    if (n < 1) k.store(n = blocks_per_cu(fn, kThreads, 0), std::memory_order_relaxed);
+    return n * n_cu;
 }
 
 int psf_grid(int tx, int max_rlat, int n_cu)
@@ -1180,7 +1181,16 @@ int psf_grid(int tx, int max_rlat, int n_cu)
     static std::atomic<int> known[3][kMaxPsfRadius + 1];
     if (!psf_tile_supported(tx)) return 0;
     std::atomic<int>& k = known[tx == 16 ? 0 : (tx == 32 ? 1 : 2)][max_rlat < 0 ? 0 : std::min(max_rlat, kMaxPsfRadius)];
-    return blocks_per_cu(psf_fn(tx), psf_threads(tx), psf_lds_bytes(tx, max_rlat), k) * n_cu;
+    int n = k.load(std::memory_order_relaxed);
+    if (n < 1) {
+        // LDS is handed out in units of 1280 bytes, which the occupancy query leaves out: tiles of 32 with radius 20
+        // fit twice, not three times, and a grid of surplus blocks ran part of its tiles in a second batch (256 frames
+        // of 128 x 200: 125 us, now 105)
+        const size_t lds = psf_lds_bytes(tx, max_rlat), unit = 1280, taps = sizeof(float) * kTaps;
+        n = std::min(blocks_per_cu(psf_fn(tx), psf_threads(tx), lds), (int)(kLdsBytes / ((lds + taps + unit - 1) / unit * unit)));
+        k.store(n, std::memory_order_relaxed);
+    }
+    return n * n_cu;
 }
 
 hipError_t launch_ray(const PhysArgs& a, QueueDev* q, int grid, hipStream_t s)

@@ -133,16 +133,49 @@ int probe_planes(const sg_probe& p);                 // image planes of a probe 
 double plane_elevation(const sg_probe& p, int j);   // elevation b of plane j, mm
 void build_items(const std::vector<EnvDev>& envs, const std::vector<int>& order, int spw, int tx,
                  std::vector<ItemRay>& rays, std::vector<ItemPsf>& tiles);
-// launch shape of a call, and of a plan before it is tuned: `scanlines` of all planes together.  Fewer scanlines
+// what the planes of a call or plan come to
+struct Extent {
+    int64_t scanlines = 0, tiles64 = 0, tiles32 = 0;   // PSF tiles of 64 and of 32 scanlines
+    void add(int W, int H)
+    {
+        scanlines += W;
+        tiles64 += (int64_t)((W + 63) / 64) * ((H + 63) / 64);
+        tiles32 += (int64_t)((W + 31) / 32) * ((H + 63) / 64);
+    }
+};
+// PSF tile width: 64 scanlines, which stage the smallest halo, from one frame (PSF kernel 7.8 against 8.3 us with 32) to
+// 256 of 128 x 256 (34 against 39 us), unless 32 come out ahead by more than the halo costs:
+//  * tiles that all fit at once, each on a compute unit of its own, with a radius past 16, where the tap loop's length
+//    counts (one frame of 200 x 200, radius 24: 17.2 and 16.4 us);
+//  * more tiles than fit at once, by the rounds of resident blocks (8 waves of a 64-wide block, 4 of a 32-wide one; a
+//    round with more waves on a unit takes longer, 3 % each measured): frames of 32 scanlines and fewer, where half of
+//    the waves of a 64-wide block have no column (256 of 24 x 256: 16.6 and 15.0 us), radii that leave one block of 64 on a
+//    unit but three of 32 (256 of 256 x 256, radius 16: 180 and 140 us), widths that fill 32s better (256 of
+//    200 x 200, radius 24: 220 and 194 us).  Within 10 % of each other it stays at 64 (256 of 128 x 200, radius 20: 106
+//    and 105 us; 256 of 65 x 256: 30.6 and 31.5 us).
+template <class Resident>   // resident(width): blocks that fit on the GPU at once
+inline int psf_tile(const Extent& x, int max_rlat, int n_cu, Resident resident)
+{
+    const int resident64 = resident(64);
+    if (resident64 < 1) return 32;
+    if (max_rlat > 16 && x.tiles32 <= n_cu) return 32;
+    if (x.tiles64 <= resident64) return 64;
+    auto cost = [&](int64_t tiles, int at_once, int waves) {
+        const double rounds = (double)tiles / at_once;
+        return (rounds < 1.0 ? 1.0 : rounds) * (1.0 + 0.03 * ((double)waves * at_once / n_cu - 8.0));
+    };
+    return cost(x.tiles32, resident(32), 4) < 0.9 * cost(x.tiles64, resident64, 8) ? 32 : 64;
+}
+// launch shape of a call, and of a plan before it is tuned.  Fewer scanlines
 // per ray item spread a small call over the GPU (64 frames of 128 x 256: 31, 33, 39 us of ray kernel with 4, 8,
 // 16), more save item changes once every resident block (about six per compute unit) has several items (256
-// volumetric probes, 12,800 items of 4: 62, 49, 47 us).  Tiles of 64 scanlines are the fastest from one frame
-// (8.2 against 8.5 us with 32) to 256 (32 against 39 us).
-inline LaunchShape default_shape(int64_t scanlines, int n_cu)
+// volumetric probes, 12,800 items of 4: 62, 49, 47 us).
+inline LaunchShape default_shape(const Extent& x, int max_rlat, int n_cu)
 {
-    const int64_t items = scanlines / kRayWaves, resident = 6 * (int64_t)n_cu;
+    const int64_t items = x.scanlines / kRayWaves, resident = 6 * (int64_t)n_cu;
     LaunchShape s;
     s.spw = items <= 2 * resident ? 1 : (items <= 6 * resident ? 2 : 4);
+    s.tx = psf_tile(x, max_rlat, n_cu, [&](int tx) { return psf_grid(tx, max_rlat, n_cu); });
     return s;
 }
 sg_status sync_volumes(sg_ctx* c);

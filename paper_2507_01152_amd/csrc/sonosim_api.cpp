@@ -522,7 +522,8 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
     // one internal env per image plane (volumetric probes have several)
     std::vector<EnvDev> envs;
     std::vector<float> pool;
-    int64_t scr = 0, scanlines = 0;
+    int64_t scr = 0;
+    Extent extent;
     int max_rlat = 0, max_px = 0, multiscale = 0, any_ct = 0;
     for (int i = 0; i < n; ++i) {
         for (int k = 0; k < 12; ++k)
@@ -541,7 +542,7 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
                 return fail(SG_ERANGE, "env %d plane %d: image plane outside the fixed-point range (|Q16| > 2^30)",
                             i, j);
             scr += (int64_t)probes[i].W * ed.ld;
-            scanlines += probes[i].W;
+            extent.add(probes[i].W, probes[i].H);
             max_rlat = std::max(max_rlat, ed.rlat);
             max_px = std::max(max_px, probes[i].W * probes[i].H);
             envs.push_back(ed);
@@ -559,7 +560,7 @@ sg_status stage_physics(sg_ctx* c, int32_t n, const int32_t* vol_ids, const sg_p
     });
     std::vector<ItemRay> rays;
     std::vector<ItemPsf> tiles;
-    const LaunchShape shape = default_shape(scanlines, c->n_cu);
+    const LaunchShape shape = default_shape(extent, max_rlat, c->n_cu);
     build_items(envs, order, shape.spw, shape.tx, rays, tiles);
 
     // one staging block: envs | taps | ray items | psf items

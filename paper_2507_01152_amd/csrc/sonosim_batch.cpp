@@ -252,7 +252,7 @@ extern "C" sg_status sg_batch_plan_create(sg_ctx* c, int32_t n, const int32_t* v
     p->vol_ids.assign(vol_ids, vol_ids + n);
     p->probes.assign(probes, probes + n);
     p->out_offsets.assign(out_offsets, out_offsets + n);
-    int64_t scanlines = 0;
+    Extent extent;
     for (int i = 0; i < n; ++i) {   // one internal env per image plane
         if (out_offsets[i] < 0) return fail(SG_EINVAL, "env %d: negative output offset", i);
         for (int j = 0; j < probe_planes(probes[i]); ++j) {
@@ -264,10 +264,10 @@ extern "C" sg_status sg_batch_plan_create(sg_ctx* c, int32_t n, const int32_t* v
             p->max_rax = std::max(p->max_rax, ed.rax);
             p->max_rlat = std::max(p->max_rlat, ed.rlat);
             p->envs.push_back(ed);
+            extent.add(probes[i].W, probes[i].H);
         }
         p->multiscale |= c->vols[vol_ids[i]].dev.scales > 1;
         p->any_ct |= c->vols[vol_ids[i]].dev.ct != nullptr;
-        scanlines += (int64_t)probe_planes(probes[i]) * probes[i].W;
     }
     p->n_envs = (int32_t)p->envs.size();
     const int ni = p->n_envs;
@@ -290,7 +290,7 @@ extern "C" sg_status sg_batch_plan_create(sg_ctx* c, int32_t n, const int32_t* v
     if (e == hipSuccess) e = hipMemset(p->d_poses.p, 0, sizeof(double) * 12 * n);
     if (e == hipSuccess) e = hipMemset(p->d_queue.p, 0, sizeof(QueueDev) * kMaxChunks);   // steps leave them at 0
     if (e != hipSuccess) return hip_fail(e, "plan upload");
-    s = apply_shape(c, p.get(), default_shape(scanlines, c->n_cu));
+    s = apply_shape(c, p.get(), default_shape(extent, p->max_rlat, c->n_cu));
     if (s != SG_OK) return s;
     const int32_t id = c->next_plan++;
     c->plans[id] = std::move(p);
