@@ -107,8 +107,8 @@ __host__ __device__ inline int ray_blocks(int resident, int n_ray)
 // counter's blocks, b % kRayQueues, + kRayQueues, ..., precede them
 __host__ __device__ inline int ray_item(int b, int blocks, int taken)
 {
-    const int g = b % kRayQueues;
-    return g + kRayQueues * ((blocks - g + kRayQueues - 1) / kRayQueues + taken);
+    const uint32_t n = kRayQueues, g = (uint32_t)b % n;
+    return (int)(g + n * (((uint32_t)blocks - g + n - 1) / n + (uint32_t)taken));
 }
 
 struct PhysArgs {

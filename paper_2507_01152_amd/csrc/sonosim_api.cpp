@@ -302,7 +302,10 @@ extern "C" sg_status sg_create(sg_ctx** out, int32_t device, void* stream)
     }
     // the work counters start at zero, and every PSF kernel clears them for the next call.  Cleared here and not in
     // the first call: that one may be recorded into a graph instead of run
+    // The parameters' buffer is set up right behind them: where they lay apart, each kernel of a small call
+    // translated one more page (one frame of 16 x 256: 15.5 us a call, 16.0 apart)
     e = c->queue.ensure(sizeof(QueueDev));
+    if (e == hipSuccess) e = c->params.ensure(16384);
     if (e == hipSuccess) e = hipMemset(c->queue.p, 0, sizeof(QueueDev));
     if (e == hipSuccess) e = hipDeviceSynchronize();   // whatever stream the first call uses
     if (e != hipSuccess) {
