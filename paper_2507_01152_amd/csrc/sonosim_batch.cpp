@@ -137,8 +137,13 @@ PhysArgs plan_args(sg_ctx* c, Plan* p, float* out)
 // planes of the current poses, then persistent PSF kernel, which clears the
 // ray kernel's work counter for the next step) on stream s; optional events:
 // before the first ray kernel, after the last ray kernel, at the end of the
-// step.  With chunks, chunk k's PSF kernel waits for its ray kernel on the
-// plan's second stream, which the step joins at the end.  The two kernels are
+// step.  With chunks, the PSF kernel of every chunk but the last waits for its
+// ray kernel on the plan's second stream, which the step joins at the end; the
+// last one follows its ray kernel directly, and a step whose ray items all fit
+// at once stays on one stream: there is nothing to run beside, and each
+// hand-over between the streams costs 8 to 10 us (8 frames of 64 x 128 in 2 and 4
+// chunks 59 and 103 us with every PSF kernel handed over, now 34 and 65, 256
+// of 128 x 256 142 and 161, now 125 and 143).  The kernels are
 // launched as they are, not replayed from a graph: between a graph and the pose
 // upload or the reconstruction kernels around it the queue stood still for 6 to
 // 8 us on either side.  Every chunk holds at least one env, so each ray kernel
@@ -157,6 +162,7 @@ hipError_t enqueue_kernels(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEve
         if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
         return e;
     }
+    const bool beside = p->n_rays > p->grid_ray;
     for (int k = 0; k < K && e == hipSuccess; ++k) {
         PhysArgs a = plan_args(c, p, out);
         a.ray_items += p->ray_off[k];
@@ -165,13 +171,14 @@ hipError_t enqueue_kernels(sg_ctx* c, Plan* p, float* out, hipStream_t s, hipEve
         a.n_psf = p->tile_cnt[k];
         a.ray_queue = q + k;
         e = launch_ray(a, q + k, p->grid_ray, s);
-        if (e == hipSuccess) e = hipEventRecord(p->ev_ray[k], s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(p->aux, p->ev_ray[k], 0);
-        if (e == hipSuccess) e = launch_psf(a, p->shape.tx, k == K - 1 ? p->grid_psf_last : p->grid_psf, p->aux);
+        const bool last = k == K - 1, here = last || !beside;
+        if (e == hipSuccess && ev && last) e = hipEventRecord(ev[1], s);
+        if (e == hipSuccess && !here) e = hipEventRecord(p->ev_ray[k], s);
+        if (e == hipSuccess && !here) e = hipStreamWaitEvent(p->aux, p->ev_ray[k], 0);
+        if (e == hipSuccess) e = launch_psf(a, p->shape.tx, here ? p->grid_psf_last : p->grid_psf, here ? s : p->aux);
     }
-    if (e == hipSuccess && ev) e = hipEventRecord(ev[1], s);
-    if (e == hipSuccess) e = hipEventRecord(p->ev_join, p->aux);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, p->ev_join, 0);
+    if (e == hipSuccess && beside) e = hipEventRecord(p->ev_join, p->aux);
+    if (e == hipSuccess && beside) e = hipStreamWaitEvent(s, p->ev_join, 0);
     if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
     return e;
 }

@@ -181,7 +181,7 @@ static int failed_step()
     for (int profiled = 0; profiled < 2; ++profiled)
         for (int chunks = 1; chunks <= 4; chunks += 3)
             for (int at = 0; at < chunks; ++at) {
-                World w(8);
+                World w(800);   // (more ray items than fit at once: the chunked step uses its second stream)
                 const int id = w.plan();
                 CHECK(id >= 0 && sg_batch_set_config(w.c, id, 4, 64, chunks) == SG_OK && w.counters_zero(id));
                 g_ops.clear();
