@@ -1841,13 +1841,10 @@ __global__ __launch_bounds__(256) void k_proj_bwd(const uint16_t* __restrict__ d
 // ---------------------------------------------------------------------------
 // element-wise / reduction kernels
 
-// dPre = bf16(g * [y > 0]) (ReLU) or bf16(g) (no activation)
-__global__ void k_mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out, int64_t n)
+__global__ void k_to_bf16(const float* x, uint16_t* out, int64_t n)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float v = (y == nullptr || bf2f(y[i]) > 0.f) ? g[i] : 0.f;
-        out[i] = f2bf(v);
-    }
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = f2bf(x[i]);
 }
 
 // Frames replaced after an audit: frame pairs[k].y of out (and, unless null, of its bf16 copy) becomes frame
@@ -2290,32 +2287,10 @@ __global__ __launch_bounds__(256) void k_reduce_segments(const float* __restrict
     }
 }
 
-// 1x1 head with one output channel: y[p] = sum_c w[c] x[p][c] + b (C = 16)
-__global__ __launch_bounds__(256) void k_head_fwd(const uint16_t* x, const uint16_t* w, const float* b, float* y,
-                                                  int64_t P, int C)
-{
-    float wf[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) wf[c] = c < C ? bf2f(w[c]) : 0.f;
-    const float bias = b[0];
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < P; p += (int64_t)gridDim.x * blockDim.x) {
-        const uint4 v0 = *reinterpret_cast<const uint4*>(x + p * 16);
-        const uint4 v1 = *reinterpret_cast<const uint4*>(x + p * 16 + 8);
-        const uint16_t* h0 = reinterpret_cast<const uint16_t*>(&v0);
-        const uint16_t* h1 = reinterpret_cast<const uint16_t*>(&v1);
-        float s = 0.f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) s += wf[c] * bf2f(h0[c]);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) s += wf[8 + c] * bf2f(h1[c]);
-        y[p] = s + bias;
-    }
-}
-
 // head backward (C = 16): dx[p][c] = w[c] g[p] (FP32), the layer's masked gradient dpre = bf16(dx [x > 0]), and
 // per-block partials of dw[c] = sum_p x[p][c] g[p] (c < 16), db = sum_p g[p] (entry 16) and, in bias_part, of the
-// column sums of dpre.  Bound by memory (56 bytes in and out of a pixel's 16 channels); dpre in a pass of its own
-// (k_mask_colsum), 2097152 pixels took 54 + 55 us, now 73.
+// column sums of dpre.  Bound by memory (132 bytes a pixel: g, x, dx and dpre; 3.8 TB/s); dpre in a pass of
+// its own (k_mask_colsum), 2097152 pixels took 54 + 55 us, now 73.
 __global__ __launch_bounds__(256) void k_head_bwd(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
                                                   const float* __restrict__ g, float* __restrict__ dx,
                                                   uint16_t* __restrict__ dpre, int64_t P, int64_t rows_per_block,
@@ -2552,29 +2527,6 @@ __global__ void k_weights_to_bf16(const float* w, int64_t n, uint16_t* wb, uint1
             const int co = (int)(q / taps);
             wt[((int64_t)ci * taps + t) * Co + co] = b;
         }
-    }
-}
-
-// per-frame PSNR of clamp(yhat, 0, 1) against y (peak 1): one block per frame
-__global__ void k_psnr(const float* yhat, const float* y, int64_t frame, float* psnr)
-{
-    __shared__ float red[256];
-    const float* a = yhat + (int64_t)blockIdx.x * frame;
-    const float* b = y + (int64_t)blockIdx.x * frame;
-    float s = 0.f;
-    for (int64_t i = threadIdx.x; i < frame; i += blockDim.x) {
-        const float d = fminf(fmaxf(a[i], 0.f), 1.f) - b[i];
-        s += d * d;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const float mse = red[0] / (float)frame;
-        psnr[blockIdx.x] = mse > 0.f ? -10.f * log10f(mse) : 200.f;
     }
 }
 
@@ -3050,9 +3002,9 @@ hipError_t proj_bwd(const uint16_t* dp, const uint16_t* x, const uint16_t* w, co
 
 int proj_bwd_blocks() { return kProjBlocks; }
 
-hipError_t mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out, int64_t n, hipStream_t s)
+hipError_t to_bf16(const float* x, uint16_t* out, int64_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_mask_to_bf16, dim3((unsigned)grid_for(n)), dim3(256), 0, s, g, y, out, n);
+    hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)grid_for(n)), dim3(256), 0, s, x, out, n);
     return hipGetLastError();
 }
 
@@ -3081,12 +3033,6 @@ hipError_t colsum_bf16(const uint16_t* x, int64_t rows, int cols, float* part, i
 hipError_t sum_parts(const float* part, int64_t n, int splits, float* out, hipStream_t s)
 {
     return reduce_parts(part, n, splits, out, s);
-}
-
-hipError_t head_fwd(const uint16_t* x, const uint16_t* w, const float* b, float* y, int64_t P, int C, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_head_fwd, dim3((unsigned)grid_for(P)), dim3(256), 0, s, x, w, b, y, P, C);
-    return hipGetLastError();
 }
 
 hipError_t head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float* dx, uint16_t* dpre, int64_t P,
@@ -3180,13 +3126,6 @@ hipError_t psnr_indexed(const float* yhat, const float* y, const int32_t* idx, i
 {
     if (n_frames <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_psnr_idx, dim3(n_frames), dim3(1024), 0, s, yhat, y, idx, frame, psnr);
-    return hipGetLastError();
-}
-
-hipError_t psnr_frames(const float* yhat, const float* y, int n_frames, int64_t frame, float* psnr, hipStream_t s)
-{
-    if (n_frames <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_psnr, dim3(n_frames), dim3(256), 0, s, yhat, y, frame, psnr);
     return hipGetLastError();
 }
 

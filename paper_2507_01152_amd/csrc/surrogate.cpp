@@ -366,10 +366,8 @@ sg_status forward_frames(sg_ctx* c, Surrogate& s, int n, float* frames, uint16_t
 // training: every tensor is stored, also the pre-skip outputs of the decoder layers (ReLU masks of the backward)
 sg_status forward(sg_ctx* c, Surrogate& s, int n)
 {
-    bool head_fused = false;
     for (int L = 0; L < kNumL; ++L) {
         const LayerDef& d = kLayers[L];
-        const ConvShape sh = layer_shape(s, L, n);
         ConvArgs a;
         std::memset(&a, 0, sizeof(a));
         a.a = (const uint16_t*)s.act[d.in].p;
@@ -377,37 +375,24 @@ sg_status forward(sg_ctx* c, Surrogate& s, int n)
         a.bias = (const float*)s.master.p + s.b_off[L];
         a.relu = 1;
         a.out_bf16 = (uint16_t*)s.act[d.out].p;
-        if (L == kNumL - 1 && d.Co == kHeadC && conv_tile_supported(geom_of(sh, 0))) {
-            // the 1x1 head in the last conv's epilogue
+        if (L == kNumL - 1) {   // the 1x1 head in the last conv's epilogue
             a.head_w = (const uint16_t*)s.wb.p + s.head_w;
             a.head_b = (const float*)s.master.p + s.head_b;
             a.head_out = (float*)s.yhat.p;
-            head_fused = true;
         }
         if (d.skip >= 0) {
             a.skip = (const uint16_t*)s.act[d.skip].p;
             a.out2_bf16 = (uint16_t*)s.act[d.out2].p;
             a.ld_out2 = kTC[d.out2];
         }
-        const bool scan_here = d.out2 == kScanDst;
-        const bool scan_fused = scan_here && conv_tile_supported(geom_of(sh, 0));
-        if (scan_fused) {   // S0 = [U0 + E0, integral]: the conv writes whole pixels
+        if (d.out2 == kScanDst) {   // S0 = [U0 + E0, integral]: the conv writes whole pixels
             a.extra = (const uint16_t*)s.act[kScanTmp].p;
             a.extra_c = kScanC;
         }
-        SG_TRY(check(conv_gemm(0, geom_of(sh, 0), a, 1, c->stream), "forward conv"));
-        if (scan_here && !scan_fused)
-            SG_TRY(check(hipMemcpy2DAsync((uint16_t*)s.act[kScanDst].p + kScanOff, sizeof(uint16_t) * kTC[kScanDst],
-                                          s.act[kScanTmp].p, sizeof(uint16_t) * kScanC, sizeof(uint16_t) * kScanC,
-                                          (size_t)n * s.H * s.W, hipMemcpyDeviceToDevice, c->stream),
-                         "depth integral copy"));
+        SG_TRY(check(conv_gemm(0, geom_of(layer_shape(s, L, n), 0), a, 1, c->stream), "forward conv"));
         if (d.out == kScanSrc) SG_TRY(forward_scan(c, s, n));
     }
-    if (head_fused) return SG_OK;
-    return check(head_fwd((const uint16_t*)s.act[D0].p, (const uint16_t*)s.wb.p + s.head_w,
-                          (const float*)s.master.p + s.head_b, (float*)s.yhat.p, (int64_t)n * s.H * s.W, kHeadC,
-                          c->stream),
-                 "head forward");
+    return SG_OK;
 }
 
 sg_status backward(sg_ctx* c, Surrogate& s, int n)
@@ -1275,7 +1260,7 @@ sg_status infer_impl(sg_ctx* c, Surrogate* s, int32_t n, const int32_t* vol_ids,
         for (int i = 0; i < n; ++i) offs[i] = (int64_t)i * HW;
         SG_TRY(stage_physics(c, n, vol_ids, probes, poses, out, offs.data(), nullptr, a, info));
         SG_TRY(launch_physics(c, a, info));
-        if (out_bf16) SG_TRY(check(mask_to_bf16(out, nullptr, out_bf16, n * HW, c->stream), "bf16 frames"));
+        if (out_bf16) SG_TRY(check(to_bf16(out, out_bf16, n * HW, c->stream), "bf16 frames"));
         *n_fallback = n;
     } else {
         std::vector<int2> rep;   // (audited frame, frame it replaces)

@@ -191,7 +191,7 @@ bool wgrad_tile_plan(const ConvGeom& g, WgradTilePlan* plan);
 int64_t wgrad_tile_part_floats(const WgradTilePlan& p);
 hipError_t wgrad_tile(const ConvGeom& g, const uint16_t* x, const uint16_t* dy, float* part, const WgradTilePlan& p,
                       float* dw, hipStream_t s);
-hipError_t mask_to_bf16(const float* g, const uint16_t* y, uint16_t* out, int64_t n, hipStream_t s);
+hipError_t to_bf16(const float* x, uint16_t* out, int64_t n, hipStream_t s);
 // frame pairs[k].y of out (and of out_bf16 unless null) = frame pairs[k].x of src, k < n (device arrays)
 hipError_t replace_frames(const float* src, const int2* pairs, int n, int64_t frame, float* out, uint16_t* out_bf16,
                           hipStream_t s);
@@ -242,7 +242,6 @@ struct ReduceSegs {
     int32_t count;
 };
 hipError_t reduce_segments(const float* part, float* out, const ReduceSegs& t, hipStream_t s);
-hipError_t head_fwd(const uint16_t* x, const uint16_t* w, const float* b, float* y, int64_t P, int C, hipStream_t s);
 // backward of the head over P pixels of 16 channels (see k_head_bwd); part: blocks * 17 floats, bias_part: blocks * 16
 hipError_t head_bwd(const uint16_t* x, const uint16_t* w, const float* g, float* dx, uint16_t* dpre, int64_t P,
                     float* part, float* bias_part, int blocks, float* dwb, hipStream_t s);
@@ -265,7 +264,6 @@ hipError_t adam_multi(const AdamSeg* segs, int nseg, int blocks, float* w, float
 hipError_t loss_log(const float* loss, const int64_t* steps, float* hist, int R, hipStream_t s);
 hipError_t weights_to_bf16(const float* w, int64_t n, uint16_t* wb, uint16_t* wt, int Co, int taps, int Ci,
                            hipStream_t s);
-hipError_t psnr_frames(const float* yhat, const float* y, int n_frames, int64_t frame, float* psnr, hipStream_t s);
 hipError_t psnr_indexed(const float* yhat, const float* y, const int32_t* idx, int n_frames, int64_t frame,
                         float* psnr, hipStream_t s);
 hipError_t transpose_w(const uint16_t* w, uint16_t* wt, int Co, int taps, int Ci, hipStream_t s);
