@@ -180,7 +180,10 @@ sg_status wgrad(sg_ctx* c, const ConvShape& sh, const uint16_t* x, const uint16_
     // alone 131072 pixels of 64 channels got 32 blocks (23 us; 4.8 with 512) and 9805 of 72 got 3 (21.6 us; 4.0 with 44)
     const int cs_blocks = blocks_for(g.Kw * sh.Co / 2, 512);
     WgradTilePlan tp;
-    if (wgrad_tile_plan(g, &tp)) {   // stride 1: direct tiled kernel, one partial per block and channel group
+    // the direct tiled kernel (one partial per block and channel group) fetches its operands by DMA in whole 16-byte
+    // chunks; the GEMM's loads into registers take tensors that start anywhere
+    const bool aligned = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dy)) & 15) == 0;
+    if (aligned && wgrad_tile_plan(g, &tp)) {
         const size_t need = sizeof(float) * std::max<int64_t>(wgrad_tile_part_floats(tp), (int64_t)cs_blocks * sh.Co);
         SG_TRY(check(parts.ensure(need), "wgrad workspace"));
         SG_TRY(check(wgrad_tile(g, x, dy, (float*)parts.p, tp, dw, c->stream), "wgrad launch"));
