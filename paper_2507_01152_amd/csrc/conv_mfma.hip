@@ -708,8 +708,8 @@ __global__ __launch_bounds__(kThreads) void k_conv_gemm(ConvGeom g0, ConvArgs a)
 // all weights are staged in LDS once (by DMA, every chunk in flight at once),
 // and the MFMA operands are read from there, so each input pixel leaves global
 // memory once per tile instead of once per tap.  LDS pixel and weight rows are odd multiples of 16 bytes, so
-// the 16-byte operand reads of a wave are free of bank conflicts.  The output
-// tile is staged through LDS for 16-byte stores; the skip sum and a 1x1 head
+// neighbouring rows start in different bank groups (the bank conflicts left take
+// 7-25 % of the kernels' time by the counters).  The output tile is staged through LDS for 16-byte stores; the skip sum and a 1x1 head
 // with one output can be fused.
 // 16 x 32 tiles (eight waves): against 8 x 32 ones, the weights staged per
 // block serve twice the pixels and the halo adds 1/8 instead of 1/4 of the
@@ -1067,9 +1067,10 @@ __global__ __launch_bounds__(32 * TH) void k_conv3x3_tile(ConvGeom g, ConvArgs a
 // channels on 131072 pixels, at 15 TB/s: that, not the matrix cores, bounds it); here the tile's input with its
 // halo is fetched once into LDS (all C channels; with UP the stored pixels, 10 x 10 of them) and only the
 // weights stream, 64 K of the 64 channels a step, through a three-stage ring of LDS DMA.  Eight waves of 64
-// pixels x 32 channels; K runs over taps and channels in the GEMM's order, so the results are its bits.  Bound by
-// LDS reads (six for eight products) and the steps' latency; 131072 pixels of 128 -> 64 upsampled 28.4 -> 23.5 us,
-// of 64 -> 64 22.6 -> 15.8 us.
+// pixels x 32 channels; K runs over taps and channels in the GEMM's order, so the results are its bits.  No unit
+// is full: LDS (six reads for eight products) is busy 45-61 % of the time in large launches, the matrix cores 36-54 %,
+// the VALU 35-43 %, and the rest is the steps' latency; on 131072 pixels LDS and matrix cores are both under 30 %.
+// 131072 pixels of 128 -> 64 upsampled 28.4 -> 23.5 us, of 64 -> 64 22.6 -> 15.8 us.
 // MODE kDgrad, the data gradient of such a layer: a is dy, b the [Ci][9][Co] copy, tap (r, s) reads dy at
 // (2 - r, 2 - s) of the halo; FP32 output plus add, with pool2 (an upsampled input's gradient) summed over 2 x 2
 // pixels, a lane's four sums.  Against the GEMM, 131072 pixels: 64 -> 64 28.0 -> 20.5 us, 128 -> 64 upsampled 38.1 ->
@@ -1287,9 +1288,10 @@ __global__ __launch_bounds__(kHaloThreads, 4) void k_conv3x3_halo(ConvGeom g, Co
 // its 16 x 32 outputs need into LDS (bf16, zero outside the image, the second conv's padding) and continues from
 // there; the halo costs a fifth of the first conv again.  K order and roundings are k_conv3x3_tile's: same bits.
 // 33554432 pixels, 8 -> 16 -> 16 channels: 333 + 453 us as two passes, 549 us here; 32 upsampled -> 16 (+ 8) -> 16
-// and the head: 759 + 545 and 54 us for the clamp, 1140 us here (LDS reads bound it now: a 16-channel product
-// needs one read each).  64 upsampled -> 32 -> 32 on a quarter of the pixels takes 131 KB of LDS, one block per
-// compute unit, and is slower (893 against 386 + 266 us), so those stay apart.
+// and the head: 759 + 545 and 54 us for the clamp, 1140 us here.  Bound by LDS reads (a 16-channel product
+// needs one each; LDS busy 72-77 % of the time, nearly half of that bank conflicts) and by the VALU (73-76 %).
+// 64 upsampled -> 32 -> 32 on a quarter of the pixels takes 131 KB of LDS, one block per compute unit, and is
+// slower (893 against 386 + 266 us), so those stay apart.
 template <int C, bool UP, int CM, int EX, int CO>
 __global__ __launch_bounds__(512, 4) void k_conv3x3_pair(PairArgs a)
 {
@@ -1527,7 +1529,8 @@ __global__ __launch_bounds__(512, 4) void k_conv3x3_pair(PairArgs a)
 // The three column shifts of a row come from one set of reads by byte alignment.
 // A wave owns RW output rows and all 9 CI CO sums; at the end the four waves'
 // sums are added in wave order through LDS.
-// Bound by LDS accesses and the latency between a tile's phases, not by memory.
+// Bound by the latency between a tile's phases at one to two and a half waves per SIMD, not by memory: with 64
+// training pairs LDS is busy 10-14 % of the time, the VALU 15-31 %, the matrix cores 6-37 %.
 // With register transposes into channel planes (4-byte LDS stores, three of
 // them for each operand read, and 11 million bank-conflict cycles) 128 -> 64
 // channels on 131072 pixels, read upsampled, took 42 us, 64 -> 64 channels on
